@@ -26,7 +26,7 @@
  * thread per sorted slot, over the candidates of its 9 ranges in batches of
  * loads in flight; one block adding up the dead.  Cells that share a bucket
  * are far apart and fail the distance test; the decision is always the
- * distance test.  The 1 % margin in h keeps
+ * distance test.  Small swarms test every pair instead (k_coll_pairs).  The 1 % margin in h keeps
  * the neighbour property exact for |coordinates| < 2^16 h (about 22 km for
  * 0.17 m radii).
  */
@@ -562,6 +562,125 @@ __global__ void __launch_bounds__(256) k_coll_died(const int32_t* died_part, int
     }
 }
 
+/* Small swarms: every pair of agents, no grid.  The eight launches of the
+ * grid pass cost their latencies, whatever the number of agents (44-49 us
+ * from 1,000 to 20,000 agents); all n^2 / 2 pairs of 5,000 agents are 2 us of
+ * FP32 work.  A wave holds the agents i of TILES tiles of 64, one per lane
+ * and tile, and tests them against a tile of 64 agents j that its block
+ * keeps in LDS and every lane reads at the same address.  The blocks cover
+ * the tiles j from the block's own agents on, and a wave's ballots give both
+ * sides of every pair: the i that collide with some j of the tile, and the j
+ * that some i of the wave collides with.  Each is one 64-bit word, stored at
+ * hits[tile of the marked agents][other tile]: every word has one writer, so
+ * nothing is cleared beforehand, and the alive mask is only read here.
+ * k_coll_mark then joins the words of a tile.  A dead agent, and a slot past
+ * the end, takes a NaN position, which never passes the distance test.
+ *
+ * TILES: with one tile the LDS reads take longer than the tests, with two
+ * they do not, but a wave then takes twice as long, which shows while the
+ * waves do not fill the chip (1,000 / 5,000 / 8,000 / 10,000 / 16,000 agents:
+ * 10.4 / 14.4 / 17.9 / 23.8 / 44 us with one, 13.5 / 16.0 / 21.0 / 21.3 / 36
+ * with two): two from kPairsOneTile agents on.
+ * kPairsMaxAgents: where the pairs' n^2 meets the grid pass's latencies
+ * (16,000 agents: 36-38 us against 47-51; 20,000: 50-52 against 44-48). */
+constexpr int kPairBlock = 256;
+constexpr int kPairWaves = kPairBlock / 64;
+constexpr int64_t kPairsOneTile = 9216;
+#ifndef POTATO_PAIRS_MAX
+#define POTATO_PAIRS_MAX 16384
+#endif
+constexpr int64_t kPairsMaxAgents = POTATO_PAIRS_MAX;
+
+template <int TILES, bool ONE_RADIUS>
+__global__ void __launch_bounds__(kPairBlock) k_coll_pairs(const float* rows, int64_t ld, int32_t n,
+                                                           const uint8_t* alive, const uint8_t* type, int n_types,
+                                                           const float* radius, int32_t tiles,
+                                                           unsigned long long* hits) {
+#pragma clang fp contract(off)
+    constexpr int kBlockTiles = kPairWaves * TILES;
+    __shared__ float4 tile[64];
+    const int32_t jt = blockIdx.x;
+    const int32_t it0 = (int32_t)blockIdx.y * kBlockTiles;
+    if (jt < it0) return;                           /* the pairs of another block */
+    auto load = [&](int32_t i) {
+        float4 q = make_float4(__builtin_nanf(""), 0.0f, 0.0f, 0.0f);
+        if (i < n && alive[i])
+            q = make_float4(rows[i], rows[ld + i], rows[2 * ld + i],
+                            ONE_RADIUS ? radius[0] : radius[type_entry(type, (uint32_t)i, n_types)]);
+        return q;
+    };
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave == 0) tile[lane] = load(jt * 64 + lane);
+    float4 q[TILES];
+    int32_t it[TILES];
+#pragma unroll
+    for (int u = 0; u < TILES; ++u) {
+        it[u] = it0 + u * kPairWaves + wave;
+        q[u] = load(it[u] * 64 + lane);
+    }
+    __syncthreads();
+    const float rs1 = radius[0] + radius[0];
+    const float rr1 = rs1 * rs1;
+    unsigned long long row[TILES] = {};
+    uint32_t col[TILES][2] = {};
+    /* agent j of the tile against the wave's agents; own: the tile of the
+     * wave's that j itself is of (an agent does not collide with itself) */
+    auto test = [&](int own) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll 8
+            for (int j = 0; j < 32; ++j) {
+                const float4 p = tile[h * 32 + j];
+#pragma unroll
+                for (int u = 0; u < TILES; ++u) {
+                    const float ex = q[u].x - p.x, ey = q[u].y - p.y, ez = q[u].z - p.z;
+                    const float d2 = (ex * ex + ey * ey) + ez * ez;
+                    const float rs = q[u].w + p.w;
+                    unsigned long long m = __ballot(d2 < (ONE_RADIUS ? rr1 : rs * rs));
+                    if (own == u) m &= ~(1ull << (h * 32 + j));
+                    row[u] |= m;
+                    if (m) col[u][h] |= 1u << j;
+                }
+            }
+    };
+    static_assert(TILES <= 2, "one case per tile of the wave");
+    if (jt == it[0])
+        test(0);
+    else if (TILES > 1 && jt == it[TILES - 1])
+        test(TILES - 1);
+    else
+        test(-1);
+    if (lane != 0) return;
+#pragma unroll
+    for (int u = 0; u < TILES; ++u) {
+        if (it[u] >= tiles) continue;
+        hits[(int64_t)it[u] * tiles + jt] = row[u];
+        /* among the block's own tiles every wave tests every tile, so the
+         * other side's word is its own wave's */
+        if (jt >= it0 + kBlockTiles)
+            hits[(int64_t)jt * tiles + it[u]] = (unsigned long long)col[u][1] << 32 | col[u][0];
+    }
+}
+
+/* One block per tile of 64 agents: joins the tile's words, marks its agents
+ * dead and adds their number to *died (at most one atomic per 64 agents). */
+__global__ void __launch_bounds__(kPairBlock) k_coll_mark(const unsigned long long* hits, int32_t tiles,
+                                                          uint8_t* alive, unsigned long long* died) {
+    __shared__ unsigned long long part[kPairBlock / 64];
+    const unsigned long long* const words = hits + (int64_t)blockIdx.x * tiles;
+    unsigned long long m = 0;
+    for (int32_t t = threadIdx.x; t < tiles; t += kPairBlock) m |= words[t];
+    for (int off = 32; off > 0; off >>= 1) m |= __shfl_xor(m, off);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x / 64] = m;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    m = part[0];
+#pragma unroll
+    for (int u = 1; u < kPairBlock / 64; ++u) m |= part[u];
+    if (m >> threadIdx.x & 1ull) alive[(int64_t)blockIdx.x * 64 + threadIdx.x] = 0;
+    if (threadIdx.x == 0 && died && m) atomicAdd(died, (unsigned long long)__popcll(m));
+}
+
 }  // namespace
 
 namespace {
@@ -624,6 +743,11 @@ constexpr int64_t kNoAllocBytes = workspace_for(kNoAllocMaxAgents);
 
 }  // namespace
 
+/* the pairs' words, one per pair of tiles, fit the workspace */
+constexpr int64_t kPairTilesMax = (kPairsMaxAgents + 63) / 64;
+static_assert(kPairTilesMax * kPairTilesMax * 8 <= workspace_for(kPairsMaxAgents) && workspace_for(1) >= 8,
+              "hit words of the pairs pass (n^2 / 512 bytes against more than 80 n)");
+
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 int64_t collision_workspace_bytes(int64_t n) { return workspace_for(n); }
@@ -651,6 +775,19 @@ hipError_t collision_scratch(void** ptr, int64_t* bytes) {
 hipError_t launch_detect_collisions(const float* rows, int64_t ld, int64_t n, const uint8_t* type, int n_types,
                                     const float* radius_dev, float r_max, uint8_t* alive,
                                     unsigned long long* died, void* workspace, hipStream_t s) {
+    if (n <= kPairsMaxAgents) {
+        const int32_t tiles = (int32_t)((n + 63) / 64);
+        unsigned long long* hits = reinterpret_cast<unsigned long long*>(workspace);
+        const int two = n > kPairsOneTile ? 1 : 0;
+        const int32_t per_block = kPairWaves << two;
+        const dim3 grid((unsigned)tiles, (unsigned)((tiles + per_block - 1) / per_block));
+        auto* const fn = two ? (type ? k_coll_pairs<2, false> : k_coll_pairs<2, true>)
+                             : (type ? k_coll_pairs<1, false> : k_coll_pairs<1, true>);
+        hipLaunchKernelGGL(fn, grid, dim3(kPairBlock), 0, s, rows, ld, (int32_t)n, alive, type, n_types, radius_dev,
+                           tiles, hits);
+        hipLaunchKernelGGL(k_coll_mark, dim3((unsigned)tiles), dim3(kPairBlock), 0, s, hits, tiles, alive, died);
+        return hipGetLastError();
+    }
     const SortPlan q = sort_plan(n);
     const int64_t cells = q.parts * q.tiles;
     float4* tpos = reinterpret_cast<float4*>(workspace);

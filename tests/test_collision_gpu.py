@@ -278,3 +278,33 @@ def test_graph_replay_reads_the_current_mask(torch_dev):
     assert torch.equal(st[:, ::2], before[:, ::2])
     assert not torch.equal(st[:, 1::2], before[:, 1::2])
     sim.close()
+
+
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 255, 256, 257, 511, 513, 4097, 9216, 9217, 16383, 16384, 16385, 17000])
+@pytest.mark.parametrize("typed", [False, True])
+def test_detection_around_the_pairs_limits(oracle, torch_dev, n, typed):
+    """Sizes around the tiles of the all-pairs pass, its change from one tile
+    per wave to two and its limit, beyond which the grid takes over: random
+    pairs, a coincident cluster (at 16,385 and 17,000 agents larger than the
+    grid's LDS staging), dead agents, NaN, infinite and far positions.  The
+    decisions are those of the brute-force reference bit for bit, and a
+    second call finds nothing left."""
+    rng = np.random.default_rng(1000 + n)
+    side = (n / 4.0) ** (1.0 / 3.0)
+    pos = rng.uniform(0.0, side, size=(3, n))
+    if n > 64:
+        pos[:, : n // 3] = rng.uniform(0.0, side, size=(3, 1))
+        pos[0, n - 3] = np.nan
+        pos[1, n - 5] = np.inf
+        pos[2, n - 7] = -np.inf
+        pos[:, n - 9:n - 7] = 2.9e4
+    state = I.hover_state(rng.permuted(pos, axis=1) if n <= 64 else pos)
+    types = [I.base_type()] + ([I.base_type(arm=0.4), I.base_type(arm=0.05)] if typed else [])
+    ti = rng.integers(0, 5, n).astype(np.uint8) if typed else None      # 3 and 4 read as the last type
+    alive = (rng.random(n) > 0.1).astype(np.uint8)
+    got, died = gpu_detect(torch_dev, state, types, alive, ti)
+    ref, ref_died = oracle.detect_collisions(state, [t["radius"] for t in types], alive,
+                                             None if ti is None else np.minimum(ti, 2))
+    assert np.array_equal(got, ref) and died == ref_died
+    again, more = gpu_detect(torch_dev, state, types, got, ti)
+    assert np.array_equal(again, got) and more == 0
