@@ -594,10 +594,10 @@ potato_status potato_autotune(potato_ctx* ctx, const potato_state* state, const 
         if (e != hipSuccess) break;
         Plan P = make_plan(ctx, &ss, params, cmds, dt, n_agents, ckpt_scratch, ckpt_every);
         int per_cu = 0;
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rollout_kernel(P.v), b,
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, rollout_kernel(P.v, P.a), b,
                                                          rollout_lds_bytes(P.v, P.a, b));
         if (e != hipSuccess) break;
-        const int64_t full = (n_agents + b - 1) / b;
+        const int64_t full = ((rollout_lanes(P.v, P.a) ? 4 : 1) * n_agents + b - 1) / b;
         std::vector<int> grids = {0};
         for (int mult : {1, 2}) {
             const int64_t gsz = (int64_t)per_cu * n_cu * mult;

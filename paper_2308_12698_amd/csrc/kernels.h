@@ -107,8 +107,22 @@ __host__ __device__ constexpr int64_t group_lds_words(int block) {
 hipError_t launch_rollout(const Variant& v, const StepArgs& a, int block, int grid_blocks,
                           hipStream_t stream);
 
-/* Kernel function pointer of a variant (occupancy queries). */
-const void* rollout_kernel(const Variant& v);
+/* Kernel function pointer of a launch (occupancy queries). */
+const void* rollout_kernel(const Variant& v, const StepArgs& a);
+
+/* Swarms of at most kLaneAgents quadrotors take four lanes per agent: 16
+ * agents per wave, one wave on each of the chip's 1,024 SIMDs.  A wave that
+ * has its SIMD to itself issues one instruction per 4 clocks at best, so a
+ * step costs its instructions: 285 vector instructions against one agent
+ * per lane's 523, 0.537 us per closed-loop step against 0.940 (open loop
+ * 0.316 against 0.578), from 1,000 to 16,384 agents alike.  Two such waves
+ * on a SIMD take turns (0.977 us at 24,000 agents), one wave of one agent
+ * per lane does not mind how many of its lanes are used (0.940). */
+#ifndef POTATO_LANE_AGENTS
+#define POTATO_LANE_AGENTS 16384
+#endif
+constexpr int64_t kLaneAgents = POTATO_LANE_AGENTS;
+bool rollout_lanes(const Variant& v, const StepArgs& a);
 
 /* Adjoint: kernel pointer (occupancy queries) and launch of grid_blocks
  * blocks.  One agent per thread, kAdjBlock threads per block, tape

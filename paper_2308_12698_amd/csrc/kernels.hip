@@ -24,6 +24,8 @@
  *   KINDS the type table also holds cars and fixed-wing aircraft: a lane
  *         whose type is one of those runs its own step (vehicle_step.h)
  *         over rows 0-6 instead of the quadrotor's.
+ * k_rollout_lanes: the same for small swarms of quadrotors, four lanes per
+ * agent.
  * k_adjoint: reverse sweep of a checkpointed rollout, one agent per lane,
  * each segment recomputed into a per-wave tape and then reversed;
  * k_adjoint_pipe: the same sweep for small swarms, a recomputing and a
@@ -38,6 +40,7 @@
 
 #include "kernels.h"
 #include "quad_adjoint.h"
+#include "quad_lanes.h"
 #include "scan.h"
 #include "vehicle_step.h"
 
@@ -513,6 +516,147 @@ __global__ void __launch_bounds__(1024) POTATO_ROLLOUT_ATTR k_rollout(const Step
 
 }
 
+/* The rollout with four lanes per agent (quad_lanes.h): the small swarms'
+ * form of k_rollout, quadrotors only (kLaneAgents says up to where and what
+ * it measures).  Bound by the issue of one wave per SIMD: 4.5 clocks per
+ * vector instruction, 44 of the 285 per step being DPP moves that no other
+ * instruction could take in.  Type, processing order, per-agent gains, alive
+ * mask and snapshot are read before the step loop, so they are plain
+ * conditions here.  Agents are not grouped by budget: with a SIMD per wave
+ * the call ends with the longest budget either way. */
+template <int MODE, bool CKPT, bool CARRY>
+__global__ void __launch_bounds__(1024) k_rollout_lanes(const StepArgs A) {
+    static_assert(MODE == 1 || !CKPT, "checkpoints are written in closed loop");
+    static_assert(CARRY || !CKPT, "checkpoints hold the carries");
+    extern __shared__ float4 lds_raw[];
+    Limits* lim_lds = reinterpret_cast<Limits*>(lds_raw);
+    TypeConst* tab = reinterpret_cast<TypeConst*>(lds_raw + (sizeof(Limits) + 15) / 16);
+    stage_constants(A.table, A.n_types, A.lim, tab, lim_lds);
+    const Limits& lim = A.lim;
+    const int l = threadIdx.x & 3;
+    const bool xyz = l < 3;
+    const int c3 = xyz ? l : 0;                     /* lane 3 of a three-vector repeats lane 0's row */
+    const int64_t ld = A.ld;
+    const int64_t stride = ((int64_t)gridDim.x * blockDim.x) >> 2;
+    for (int64_t j = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 2; j < A.n; j += stride) {
+        const uint32_t i = A.perm ? order_entry(A.perm, (uint32_t)j, A.n) : (uint32_t)j;
+        const TypeConst& c = tab[A.type ? type_entry(A.type, i, A.n_types) : 0];
+        float* const R = A.rows + i;
+        float* const C = CARRY ? A.carry + i : nullptr;
+        auto row = [&](int k) -> float& { return R[k * ld]; };
+        auto crow = [&](int k) -> float& { return C[k * A.carry_ld]; };
+        const bool snapshot = !CKPT && A.snap != nullptr;
+        int64_t left = (int64_t)c.budget - A.step0;
+        left = left < 0 ? 0 : left;
+        const int steps = A.alive && !A.alive[i] ? 0 : left < A.n_steps ? (int)left : A.n_steps;
+        if (steps == 0) {
+            /* an agent that is not advanced keeps its stored position */
+            if (snapshot && xyz) A.snap[l * A.n + i] = row(l);
+            continue;
+        }
+        LaneAgent a{};
+        a.p = row(c3);
+        a.v = row(3 + c3);
+        a.q = row(xyz ? 7 + l : 6);
+        a.w = row(10 + c3);
+        a.d = row(13 + l);
+        if (CARRY) {
+            a.p_lo = crow(c3);
+            a.v_lo = crow(3 + c3);
+        }
+        if (MODE == 1) {
+            a.ip = row(17 + c3);
+            a.ia = row(20 + c3);
+            a.ir = row(23 + c3);
+            a.wprev = row(26 + c3);
+            a.J = row(29);
+            if (CARRY) {
+                a.J_lo = crow(6);
+                a.ip_lo = crow(7 + c3);
+            }
+        }
+        Gains g;
+        if (MODE == 1 && A.gains) {
+            const float* G = A.gains + i;
+            auto gain = [&](int k) { return G[k * A.gains_ld]; };
+            g = Gains{gain(0), gain(1), gain(2), gain(3), gain(4), gain(5), gain(6), gain(7), gain(8)};
+        } else {
+            g = Gains{c.gains[0], c.gains[1], c.gains[2], c.gains[3], c.gains[4],
+                      c.gains[5], c.gains[6], c.gains[7], c.gains[8]};
+        }
+        g.kdr_dt = g.kdr * lim.inv_dt;
+        const LaneConst lc = lane_const(c, g, l);
+        float dc = 0.0f, wp = 0.0f;
+        int64_t next_epoch_step = INT64_MAX;
+        int epoch = 0;
+        auto waypoint = [&]() { return A.wp[((int64_t)epoch * 3 + c3) * A.cmd_ld + i]; };
+        if (MODE == 0) {
+            dc = A.motor_cmd[l * A.cmd_ld + i];
+        } else {
+            if (A.resample > 0) {
+                const int64_t e0 = A.step0 / A.resample;
+                epoch = e0 < A.n_epochs - 1 ? (int)e0 : A.n_epochs - 1;
+                next_epoch_step = e0 < A.n_epochs - 1 ? (e0 + 1) * A.resample : INT64_MAX;
+            }
+            wp = waypoint();
+        }
+        int ck_next = 0, ck_slot = 0;
+        if (CKPT) {
+            ck_slot = (A.k0 + A.ckpt_every - 1) / A.ckpt_every;
+            ck_next = ck_slot * A.ckpt_every - A.k0;
+        }
+        for (int s = 0; s < steps; ++s) {
+            if (CKPT && s == ck_next) {
+                float* const O = A.ckpt + (int64_t)ck_slot * kCkptRows * ld + i;
+                auto out = [&](int k) -> float& { return O[k * ld]; };
+                if (xyz) {
+                    out(l) = a.p; out(3 + l) = a.v; out(10 + l) = a.w;
+                    out(17 + l) = a.ip; out(20 + l) = a.ia; out(23 + l) = a.ir; out(26 + l) = a.wprev;
+                    out(30 + l) = a.p_lo; out(33 + l) = a.v_lo; out(37 + l) = a.ip_lo;
+                } else {
+                    out(29) = a.J;
+                    out(36) = a.J_lo;
+                }
+                out(xyz ? 7 + l : 6) = a.q;
+                out(13 + l) = a.d;
+                ++ck_slot;
+                ck_next += A.ckpt_every;
+            }
+            if (MODE == 1) {
+                if (A.step0 + s == next_epoch_step) {
+                    ++epoch;
+                    wp = waypoint();
+                    next_epoch_step = epoch < A.n_epochs - 1 ? next_epoch_step + A.resample : INT64_MAX;
+                }
+                dc = lane_controller<CARRY>(lc, lim, a, wp);
+            }
+            lane_rk4<CARRY>(lc, lim, a, dc);
+        }
+        row(xyz ? 7 + l : 6) = a.q;
+        row(13 + l) = a.d;
+        if (xyz) {
+            row(l) = a.p;
+            row(3 + l) = a.v;
+            row(10 + l) = a.w;
+            if (CARRY) {
+                crow(l) = a.p_lo;
+                crow(3 + l) = a.v_lo;
+            }
+            if (MODE == 1) {
+                row(17 + l) = a.ip;
+                row(20 + l) = a.ia;
+                row(23 + l) = a.ir;
+                row(26 + l) = a.wprev;
+                if (CARRY) crow(7 + l) = a.ip_lo;
+            }
+            if (snapshot) A.snap[l * A.n + i] = a.p;
+        } else if (MODE == 1) {
+            row(29) = a.J;
+            if (CARRY) crow(6) = a.J_lo;
+        }
+    }
+}
+
 /* Reverse sweep of the checkpointed closed-loop rollout: one agent per lane
  * (grid-stride), cotangents and gain sums in registers, the recomputed
  * segment in this wave's tape blocks.  Two waves per SIMD: the hot loops
@@ -735,7 +879,17 @@ const void* kfn_carry(const Variant& v) {
 
 }  // namespace
 
-const void* rollout_kernel(const Variant& v) {
+bool rollout_lanes(const Variant& v, const StepArgs& a) { return !v.kinds && a.n <= kLaneAgents; }
+
+const void* rollout_kernel(const Variant& v, const StepArgs& a) {
+    if (rollout_lanes(v, a)) {
+#define POTATO_LANES(M, K, C) return reinterpret_cast<const void*>(&k_rollout_lanes<M, K, C>)
+        if (v.mode == 0) { if (v.carry) POTATO_LANES(0, false, true); POTATO_LANES(0, false, false); }
+        if (v.ckpt) POTATO_LANES(1, true, true);
+        if (v.carry) POTATO_LANES(1, false, true);
+        POTATO_LANES(1, false, false);
+#undef POTATO_LANES
+    }
     /* open loop: gains and checkpoints do not apply */
     if (v.mode == 0) {
         if (!v.het) return kfn_carry<0, false, false, false>(v);
@@ -781,7 +935,7 @@ hipError_t launch_adjoint(bool het, bool gains, bool perm, bool pipe, const AdjA
 }
 
 bool rollout_grouped(const Variant& v, const StepArgs& a) {
-    return v.het && !v.perm && !v.ckpt && a.n_groups >= 2;
+    return v.het && !v.perm && !v.ckpt && a.n_groups >= 2 && !rollout_lanes(v, a);
 }
 
 size_t rollout_lds_bytes(const Variant& v, const StepArgs& a, int block) {
@@ -815,8 +969,9 @@ static hipError_t fill_blocks(const void* fn, int block, size_t lds, int* out) {
 
 hipError_t launch_rollout(const Variant& v, const StepArgs& a, int block, int grid_blocks,
                           hipStream_t stream) {
-    const void* fn = rollout_kernel(v);
-    int64_t grid = grid_blocks > 0 ? grid_blocks : (a.n + block - 1) / block;
+    const void* fn = rollout_kernel(v, a);
+    const int64_t threads = rollout_lanes(v, a) ? 4 * a.n : a.n;
+    int64_t grid = grid_blocks > 0 ? grid_blocks : (threads + block - 1) / block;
     const size_t lds = rollout_lds_bytes(v, a, block);
     if (grid_blocks <= 0 && rollout_grouped(v, a)) {
         /* agents grouped per block: one round of blocks, as many as the

@@ -677,3 +677,96 @@ def test_autotune_cache_round_trip(torch_dev, tmp_path):
         out.append(x.cpu().numpy())
     sim.close()
     assert np.array_equal(out[0], out[1])
+
+
+LANE_KINDS = ("closed", "open", "uncompensated", "types", "order", "gains", "dead", "plain", "snapshot", "ckpt")
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 65, 1000, 16384])
+@pytest.mark.parametrize("kind", LANE_KINDS)
+def test_four_lanes_per_agent_give_the_bits_of_one(torch_dev, n, kind):
+    """Swarms of up to 16,384 quadrotors run four lanes per agent.  The same
+    agents inside a swarm of 16,600 run one lane per agent; states, carries,
+    snapshots and checkpoints must agree bit for bit: saturated and
+    inverted attitudes, clamped integrals, epoch changes, budgets that end
+    inside the call, out-of-range types, dead agents, NaN and infinite
+    states, a row stride beyond the agent count."""
+    torch, dev = torch_dev
+    from paper_2308_12698_amd.sim import Pipe, Simulator
+    N, steps, every = 16600, 37, 10
+    rng = np.random.default_rng(77)
+    s = np.zeros((30, N))
+    s[0:3] = rng.uniform(0.0, 50.0, (3, N))
+    s[3:6] = rng.normal(0.0, 2.0, (3, N))
+    s[6:10] = rng.normal(0.0, 1.0, (4, N)) + np.array([[2.0], [0.0], [0.0], [0.0]])
+    s[6:10] /= np.linalg.norm(s[6:10], axis=0)
+    s[10:13] = rng.normal(0.0, 2.0, (3, N))
+    s[13:17] = rng.normal(0.0, 80.0, (4, N))
+    s[17:20] = rng.uniform(-5.0, 5.0, (3, N))
+    s[20:26] = rng.uniform(-1.0, 1.0, (6, N))
+    s[26:29] = s[10:13] + rng.normal(0.0, 0.1, (3, N))
+    s[29] = rng.uniform(0.0, 1e6, N)
+    bad = np.arange(3, N, 97)
+    for k, i in enumerate(bad):
+        s[k % 30, i] = (np.nan, np.inf, -np.inf)[k % 3]
+    state = I.f32(s)
+    carry = I.f32(rng.normal(0.0, 1e-7, (10, N)))
+    wp = I.f32(rng.uniform(0.0, 50.0, (3, 3, N)))
+    cmd = I.f32(rng.uniform(-200.0, 200.0, (4, N)))
+    gains = I.f32(np.asarray(I.DEFAULT_GAINS)[:, None] * rng.uniform(0.5, 3.0, (9, N)))
+    types = [I.base_type()]
+    ti = None
+    if kind in ("types", "order", "ckpt"):
+        types = I.hetero_types()
+        for t, ty in enumerate(types):
+            ty["budget"] = 10 + 6 * t
+        ti = rng.integers(0, 10, N).astype(np.uint8)
+    alive = (rng.random(N) > 0.3).astype(np.uint8)
+    mode = 0 if kind == "open" else 1
+
+    def run(m):
+        """The first m agents of the swarm (a row stride of m + 5)."""
+        ld = m + 5
+
+        def up(a):
+            b = np.full(a.shape[:-1] + (ld,), 7.0, dtype=a.dtype)
+            b[..., :m] = a[..., :m]
+            return _dev(torch, dev, b)
+
+        st, ct = up(state), None if kind == "uncompensated" else up(carry)
+        tt = None if ti is None else _dev(torch, dev, ti[:m])
+        sim = Simulator(types, I.globals_f32(), mode=mode, form="plain" if kind == "plain" else "fused",
+                        steps_per_launch=16)
+        out = {}
+        if kind == "snapshot":
+            pipe = Pipe(sim, m)
+            snaps = torch.empty((3, 3, m), pin_memory=True)
+            pipe.push(wp[0, :, :m])
+            pipe.run(st, steps, 1e-3, snap_every=12, snaps=snaps, carry=ct, alive=_dev(torch, dev, alive[:m]))
+            pipe.wait_snapshots(3)
+            out["snaps"] = snaps.numpy().copy()
+        else:
+            ck = torch.full((4, 40, ld), 7.0, device=dev) if kind == "ckpt" else None
+            sim.step(st, steps, 1e-3, n_agents=m, type_idx=tt, carry=ct,
+                     perm=sim.order_by_type(tt) if kind in ("order", "ckpt") else None,
+                     gains=up(gains) if kind in ("gains", "ckpt") else None,
+                     motor_cmd=up(cmd) if mode == 0 else None, wp=up(wp) if mode == 1 else None,
+                     resample_every=15, step0=4, ckpt=ck, ckpt_every=every if kind == "ckpt" else 0,
+                     alive=_dev(torch, dev, alive[:m]) if kind == "dead" else None)
+            torch.cuda.synchronize()
+            if ck is not None:
+                out["ckpt"] = ck.cpu().numpy()
+        out["state"] = st.cpu().numpy()
+        if ct is not None:
+            out["carry"] = ct.cpu().numpy()
+        sim.close()
+        for a in out.values():
+            if a.shape[-1] == ld:
+                assert (a[..., m:] == 7.0).all()              # columns past the agents
+        return {k: a[..., :n] for k, a in out.items()}
+
+    one, four = run(N), run(n)
+    for k in one:
+        a, b = one[k], four[k]
+        same = (a.view(np.int32) == b.view(np.int32)) | (np.isnan(a) & np.isnan(b))
+        assert same.all(), (k, np.argwhere(~same)[:5])
