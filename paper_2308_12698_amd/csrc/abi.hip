@@ -668,11 +668,11 @@ struct AdjShape {
 
 bool adjoint_shape(potato_ctx* ctx, bool het, bool gains, bool perm, int64_t n, AdjShape& out) {
     int per_cu = 0, per_cu_pipe = 0, n_cu = 0;
-    const size_t lds = adjoint_lds_bytes(het, ctx->n_types);
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, adjoint_kernel(het, gains, perm, false), kAdjBlock,
-                                                     lds) != hipSuccess ||
+                                                     adjoint_lds_bytes(het, ctx->n_types, false)) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_pipe, adjoint_kernel(het, gains, perm, true),
-                                                     kAdjPipeBlock, lds) != hipSuccess ||
+                                                     kAdjPipeBlock,
+                                                     adjoint_lds_bytes(het, ctx->n_types, true)) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess)
         return false;
     n_cu = std::max(n_cu, 1);

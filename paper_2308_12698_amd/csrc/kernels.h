@@ -133,7 +133,7 @@ bool rollout_lanes(const Variant& v, const StepArgs& a);
 const void* adjoint_kernel(bool het, bool gains, bool perm, bool pipe);
 hipError_t launch_adjoint(bool het, bool gains, bool perm, bool pipe, const AdjArgs& a, int grid_blocks,
                           hipStream_t stream);
-size_t adjoint_lds_bytes(bool het, int n_types);
+size_t adjoint_lds_bytes(bool het, int n_types, bool pipe);
 constexpr int kAdjBlock = 256;
 constexpr int kAdjPipeBlock = 128;
 /* Use the pipelined adjoint for small swarms (1) or never (0). */

@@ -720,6 +720,7 @@ __global__ void __launch_bounds__(kAdjBlock)
                            A.n_epochs, A.resample, tape, tape_step, lb, lam, gk);
         store_adj(A.grad_x0, A.grad_mem, ld, bo, lam);
         if (A.grad_gains) {
+            kdr_from_sum(lim, gk);
 #pragma unroll
             for (int k = 0; k < 9; ++k) elem(A.grad_gains + k * ld, bo) = gk[k];
         }
@@ -744,6 +745,7 @@ __global__ void __launch_bounds__(kAdjPipeBlock)
     extern __shared__ float4 lds_raw[];
     Limits* lim_lds = reinterpret_cast<Limits*>(lds_raw);
     TypeConst* tab = reinterpret_cast<TypeConst*>(lds_raw + (sizeof(Limits) + 15) / 16);
+    float* const tails = reinterpret_cast<float*>(tab + A.n_types);      /* of two segments */
     stage_constants(A.table, A.n_types, A.lim, tab, lim_lds);
     const Limits& lim = A.lim;
     const int64_t ld = A.ld;
@@ -783,6 +785,8 @@ __global__ void __launch_bounds__(kAdjPipeBlock)
         g.kdr_dt = g.kdr * lim.inv_dt;
         WaypointCache wc{A.wp, A.cmd_ld, A.n_epochs, bo};
         AgentAdj lam;
+        Replay x{};                                /* the reversing wave's integrals and body rates */
+        float w[3] = {0.0f, 0.0f, 0.0f};
         float gk[9] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         if (!producer && valid) load_adj(A.grad_final, ld, bo, lam);
         /* iteration t: wave 0 recomputes segment n_seg_all - 1 - t into
@@ -793,18 +797,21 @@ __global__ void __launch_bounds__(kAdjPipeBlock)
                 const int seg = n_seg_all - 1 - t;
                 if (seg >= 0 && seg < n_seg)
                     recompute_segment(c, lim, g, A.ckpt, ld, bo, A.K, seg, steps, A.step0, A.resample, wc,
-                                      tape + (seg & 1) * buf_stride, tape_step, lb);
+                                      tape + (seg & 1) * buf_stride, tape_step, lb,
+                                      tails + (seg & 1) * kTailRows * 64);
             } else {
                 const int seg = n_seg_all - t;
                 if (t > 0 && seg < n_seg)
                     reverse_segment(c, lim, g, A.ckpt, ld, bo, A.K, seg, steps, A.step0, A.resample, wc,
-                                    tape + (seg & 1) * buf_stride, tape_step, lb, lam, gk);
+                                    tape + (seg & 1) * buf_stride, tape_step, lb,
+                                    tails + (seg & 1) * kTailRows * 64, x, w, lam, gk);
             }
             __syncthreads();
         }
         if (!producer && valid) {
             store_adj(A.grad_x0, A.grad_mem, ld, bo, lam);
             if (A.grad_gains) {
+                kdr_from_sum(lim, gk);
 #pragma unroll
                 for (int k = 0; k < 9; ++k) elem(A.grad_gains + k * ld, bo) = gk[k];
             }
@@ -911,8 +918,9 @@ const void* apfn() {
     return reinterpret_cast<const void*>(&k_adjoint_pipe<H, G, P>);
 }
 
-size_t adjoint_lds_bytes(bool het, int n_types) {
-    return ((sizeof(Limits) + 15) / 16) * 16 + (size_t)(het ? n_types : 1) * sizeof(TypeConst);
+size_t adjoint_lds_bytes(bool het, int n_types, bool pipe) {
+    return ((sizeof(Limits) + 15) / 16) * 16 + (size_t)(het ? n_types : 1) * sizeof(TypeConst) +
+           (pipe ? 2 * (size_t)kTailRows * 64 * sizeof(float) : 0);
 }
 
 const void* adjoint_kernel(bool het, bool gains, bool perm, bool pipe) {
@@ -929,7 +937,7 @@ const void* adjoint_kernel(bool het, bool gains, bool perm, bool pipe) {
 hipError_t launch_adjoint(bool het, bool gains, bool perm, bool pipe, const AdjArgs& a, int grid_blocks,
                           hipStream_t stream) {
     void* args[] = {const_cast<AdjArgs*>(&a)};
-    const size_t lds = adjoint_lds_bytes(het, a.n_types);
+    const size_t lds = adjoint_lds_bytes(het, a.n_types, pipe);
     return hipLaunchKernel(adjoint_kernel(het, gains, perm, pipe), dim3((unsigned)grid_blocks),
                            dim3((unsigned)(pipe ? kAdjPipeBlock : kAdjBlock)), args, lds, stream);
 }

@@ -4,17 +4,17 @@
  *
  * Forward step (quad_step.h): controller -> held rotor command dc; classical
  * RK4 over v, q, w, d (and p, J, which only integrate) with dc held;
- * quaternion renormalisation.  step_vjp() recomputes the forward
- * intermediates of one step from its step-start state and then applies the
+ * quaternion renormalisation.  step_vjp() recomputes the RK4
+ * stages of one step from its replayed start and then applies the
  * transposed derivatives in reverse order:
  *     renormalisation -> RK4 stages 4, 3, 2, 1 -> controller.
  * Non-smooth points take the derivative of the branch the forward pass
  * took: a clamp passes the cotangent inside its interval and stops it
  * outside; the error-quaternion sign is a constant; sqrt'(0) is taken as 0.
- * The branches are the forward's own decisions, recorded on the tape by the
- * recomputation (which replays the forward bit for bit), as is the rotor
- * command it held through the step; the reverse sweep does not decide any
- * branch itself.  The rounding carries of the forward integrator are not
+ * The branches are the forward's own decisions, recorded by the replay of
+ * the forward from its checkpoints (the same bits), as are the integrals
+ * after their update and the rotor command held through the step; the
+ * reverse sweep does not decide any branch itself.  The rounding carries of the forward integrator are not
  * differentiated (the represented value is row + carry, so both have the
  * same cotangent).
  */
@@ -31,85 +31,115 @@ struct AgentAdj {
     float ip[3], ia[3], ir[3], wprev[3];
 };
 
-/* Cotangent of the integrated rates of (v, q, w, d, J); the position rate
- * is v itself and is folded in by the caller.  qh holds half the cotangent
- * of the quaternion rate q o (0, w) / 2, i.e. the cotangent of q o (0, w),
- * so the kinematics need no factor. */
+/* Cotangent of a stage's rates of v, q and w, and of sum_i s_i's share in
+ * the cost.  h is the cotangent of q o (0, w), i.e. half that of the
+ * quaternion rate q o (0, w) / 2, so the kinematics need no factor. */
 struct RateAdj {
-    float v[3], qh[4], w[3], d[4], J;
+    float v[3], h[4], w[3], J;
 };
 
-/* Dynamic part of the state seen by the right-hand side. */
+/* Dynamic part of a stage's state that the Jacobian reads (it does not
+ * depend on the velocity: drag is linear). */
 struct Dyn {
-    float v[3], q[4], w[3], d[4];
+    float q[4], w[3], d[4];
 };
 
-/* Transpose of the Jacobian of the right-hand side (eqs. qd2-qd4, 2, 3 and
- * the rotor lag) at y, applied to mu.  Adds the state cotangent to
- * (lv, lq, lw, ld); the rotor-command cotangent, inv_tau times the
- * rotor-rate cotangent, is formed by the caller from the summed mu.d.
- * Products with inverse inertia use the per-type constants of the forward
- * step: (I_z - I_y)/I_x = gx etc., k_f L sin(a)/I_x = ax etc. */
-__device__ __forceinline__ void derivative_vjp(const TypeConst& c, const Dyn& y, const RateAdj& mu,
-                                               float lv[3], float lq[4], float lw[3], float ld[4]) {
-    const float* q = y.q;
-    const float* w = y.w;
-    float s[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s[i] = y.d[i] * (c.two_w + y.d[i]);
-    const float ssum = (s[0] + s[1]) + (s[2] + s[3]);
-    const float ftm = c.F0 + c.kf_m * ssum;
-    const float x2y2 = q[1] * q[1] + q[2] * q[2];
-    const float hbx = q[1] * q[3] + q[0] * q[2];      /* half of R(q) z, x and y */
-    const float hby = q[2] * q[3] - q[0] * q[1];
+/* Transpose of the Jacobian of the right-hand side (eqs. qd2-qd4, 2, 3) at y,
+ * applied to mu (ssum: y's sum of s_i, as rates() returns it): adds the stage state's cotangent to (lq, lw) and sets lsd
+ * to that of the stage's rotor deviations through thrust and torque (the
+ * rotor lag's own part is in closed form, see step_vjp).  With FIRST, lq and
+ * lw hold nothing yet.  The velocity's part is -(c_d/m) mu.v, left to the
+ * caller.  Products with inverse inertia use the per-type constants of the
+ * forward step: (I_z - I_y)/I_x = gx etc., k_f L sin(a)/I_x = ax etc. */
+template <bool FIRST>
+__device__ __forceinline__ void derivative_vjp(const TypeConst& c, const Dyn& y, float ssum, const RateAdj& mu,
+                                               float lq[4], float lw[3], float lsd[4]) {
+#pragma clang fp contract(off)
+    const float *q = y.q, *w = y.w, *d = y.d, *h = mu.h;
+    const float ftm2 = POTATO_FMA(c.kf_m2, ssum, c.F0_2);
+    const float bx2 = POTATO_FMA(q[0], q[2], q[1] * q[3]);
+    const float by2 = POTATO_FMA(q[2], q[3], -(q[0] * q[1]));
+    const float x2y2 = POTATO_FMA(q[1], q[1], q[2] * q[2]);
 
-    /* translational part: v' = 2 ftm (hbx, hby, 1/2 - x2y2) - (c_d/m) v - g z */
-    const float l_ftm = 2.0f * (mu.v[0] * hbx + mu.v[1] * hby - mu.v[2] * x2y2);
-    const float l_ssum = c.kf_m * (l_ftm + mu.v[2]) + mu.J;
-    const float m0 = 2.0f * ftm * mu.v[0], m1 = 2.0f * ftm * mu.v[1], m2 = 4.0f * ftm * mu.v[2];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) lv[i] -= c.cd_m * mu.v[i];
-    lq[0] += m0 * q[2] - m1 * q[1];
-    lq[1] += m0 * q[3] - m1 * q[0] - m2 * q[1];
-    lq[2] += m0 * q[0] + m1 * q[3] - m2 * q[2];
-    lq[3] += m0 * q[1] + m1 * q[2];
+    /* translational part: v' = ftm2 (bx2, by2, 1/2 - x2y2) - (c_d/m) v - g z */
+    const float l_ftm2 = POTATO_FMA(-mu.v[2], x2y2, POTATO_FMA(mu.v[1], by2, mu.v[0] * bx2));
+    const float l_ssum = POTATO_FMA(c.kf_m2, l_ftm2, POTATO_FMA(c.kf_m, mu.v[2], mu.J));
+    const float m0 = ftm2 * mu.v[0], m1 = ftm2 * mu.v[1], m2 = (ftm2 + ftm2) * mu.v[2];
+    auto first = [](float acc, float x, float y) { return FIRST ? x * y : POTATO_FMA(x, y, acc); };
+    lq[0] = POTATO_FMA(-m1, q[1], first(lq[0], m0, q[2]));
+    lq[1] = POTATO_FMA(-m2, q[1], POTATO_FMA(-m1, q[0], first(lq[1], m0, q[3])));
+    lq[2] = POTATO_FMA(-m2, q[2], POTATO_FMA(m1, q[3], first(lq[2], m0, q[0])));
+    lq[3] = POTATO_FMA(m1, q[2], first(lq[3], m0, q[1]));
 
-    /* quaternion kinematics q o (0, w), cotangent mu.qh */
-    const float* m = mu.qh;
-    lq[0] += w[0] * m[1] + w[1] * m[2] + w[2] * m[3];
-    lq[1] += -w[0] * m[0] - w[2] * m[2] + w[1] * m[3];
-    lq[2] += -w[1] * m[0] + w[2] * m[1] - w[0] * m[3];
-    lq[3] += -w[2] * m[0] - w[1] * m[1] + w[0] * m[2];
-    lw[0] += -q[1] * m[0] + q[0] * m[1] + q[3] * m[2] - q[2] * m[3];
-    lw[1] += -q[2] * m[0] - q[3] * m[1] + q[0] * m[2] + q[1] * m[3];
-    lw[2] += -q[3] * m[0] + q[2] * m[1] - q[1] * m[2] + q[0] * m[3];
+    /* quaternion kinematics q o (0, w) */
+    lq[0] = POTATO_FMA(w[2], h[3], POTATO_FMA(w[1], h[2], POTATO_FMA(w[0], h[1], lq[0])));
+    lq[1] = POTATO_FMA(w[1], h[3], POTATO_FMA(-w[2], h[2], POTATO_FMA(-w[0], h[0], lq[1])));
+    lq[2] = POTATO_FMA(-w[0], h[3], POTATO_FMA(w[2], h[1], POTATO_FMA(-w[1], h[0], lq[2])));
+    lq[3] = POTATO_FMA(w[0], h[2], POTATO_FMA(-w[1], h[1], POTATO_FMA(-w[2], h[0], lq[3])));
+    lw[0] = POTATO_FMA(-q[2], h[3], POTATO_FMA(q[3], h[2], POTATO_FMA(-q[1], h[0], first(lw[0], q[0], h[1]))));
+    lw[1] = POTATO_FMA(-q[3], h[1], POTATO_FMA(q[1], h[3], POTATO_FMA(-q[2], h[0], first(lw[1], q[0], h[2]))));
+    lw[2] = POTATO_FMA(-q[1], h[2], POTATO_FMA(q[2], h[1], POTATO_FMA(-q[3], h[0], first(lw[2], q[0], h[3]))));
 
     /* Euler's equations: w' = (ax (A + B), ay (P23 - P01), az (A - B)) - (gx w1 w2, gy w2 w0, gz w0 w1) */
     const float b0 = c.gx * mu.w[0], b1 = c.gy * mu.w[1], b2 = c.gz * mu.w[2];
-    lw[0] -= b1 * w[2] + b2 * w[1];
-    lw[1] -= b0 * w[2] + b2 * w[0];
-    lw[2] -= b0 * w[1] + b1 * w[0];
+    lw[0] = POTATO_FMA(-b2, w[1], POTATO_FMA(-b1, w[2], lw[0]));
+    lw[1] = POTATO_FMA(-b0, w[2], POTATO_FMA(-b2, w[0], lw[1]));
+    lw[2] = POTATO_FMA(-b1, w[0], POTATO_FMA(-b0, w[1], lw[2]));
 
     /* rotor model and allocation (eqs. 2, 3) through s_i = W_i^2 - w_ref^2 */
     const float tX = c.ax * mu.w[0], tY = c.ay * mu.w[1], tZ = c.az * mu.w[2];
     const float pz = l_ssum + tZ, mz = l_ssum - tZ, u = tX - tY, v = tX + tY;
-    const float lsv[4] = {pz + u, mz - v, pz - u, mz + v};
+    const float ls[4] = {pz + u, mz - v, pz - u, mz + v};
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        ld[i] += lsv[i] * (c.two_w + 2.0f * y.d[i]) - c.inv_tau * mu.d[i];
+    for (int i = 0; i < 4; ++i) lsd[i] = ls[i] * POTATO_FMA(2.0f, d[i], c.two_w);
 }
 
+/* All ones where branch bit POS is set (a bit-field extract: the compiler
+ * makes a comparison and a selection of every expression of it), and x there,
+ * +0 elsewhere. */
+template <int POS>
+__device__ __forceinline__ int32_t bit_mask(uint32_t bits) {
+    int32_t mask;
+    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(mask) : "v"(bits), "n"(POS));
+    return mask;
+}
+__device__ __forceinline__ float where(int32_t mask, float x) {
+    return __builtin_bit_cast(float, __builtin_bit_cast(int32_t, x) & mask);
+}
+
+/* What the reverse of one step reads of its forward: the step-start state,
+ * the controller's integrals after their update, the change of the body
+ * rates since the previous step, the rotor command held through the step
+ * and the branch decisions (kBit*). */
+struct Replay {
+    float p[3], v[3], q[4], w[3], d[4], ip[3], ia[3], ir[3], dw[3], dc[4];
+    uint32_t bits;
+};
+
 /*
- * Reverse of one step.  `a` is the step-start state (as the forward pass
- * saw it; its J and carries are not read), wp the waypoint of this step, k
- * the gains, dc the rotor command the forward controller held through the
- * step and bits its branch decisions (kBit*).  lam holds the cotangent of
+ * Reverse of one step.  `a` is its replay, wp the waypoint of this step and
+ * k the gains; on return a.ip, a.ia and a.ir are the integrals before the
+ * step, as far as they can be told from those after it (see kRefresh).  lam
+ * holds the cotangent of
  * the step-end state on entry and of the step-start state on return; gk
- * accumulates the gain cotangents.
+ * accumulates the gain cotangents, the last one (kdr) times dt: gk[8] is
+ * divided by dt once at the end of the sweep (kdr_from_sum).
+ *
+ * Bound by the tape's traffic and by instruction issue at the two waves per
+ * SIMD its registers allow, so it is written for few instructions, every one
+ * placed: sums accumulate in fused multiply-adds onto what is there already
+ * (no zero-initialised temporaries), the last reversed stage accumulates
+ * into lam itself, the rotor lag's cotangents come from its closed form
+ * (d_stage = dc + (d - dc) c_stage) instead of through the stages, and masks
+ * are bit-field extracts.  1,190 vector instructions became 980 (backward at
+ * 1,048,576 agents, K = 50: 59.0 to 57.7 us per step; the integrals left off
+ * the tape, 251 to 183 B per agent-step: 50.3).
  */
 __device__ __forceinline__ void step_vjp(const TypeConst& c, const Limits& L, const Gains& k,
-                                         const Agent& a, const float wp[3], const float dc[4],
-                                         uint32_t bits, AgentAdj& lam, float gk[9]) {
+                                         Replay& a, const float wp[3], AgentAdj& lam, float gk[9]) {
+#pragma clang fp contract(off)
+    const float* const dc = a.dc;
+    const uint32_t bits = a.bits;
     /* ---------------- RK4 forward, keeping the stage states ----------------
      * (the forward step's own arithmetic: rates() with the quaternion rate's
      * factor 1/2 on the step sizes, and the rotor lag's closed-form stage
@@ -117,272 +147,244 @@ __device__ __forceinline__ void step_vjp(const TypeConst& c, const Limits& L, co
     const float z = -(L.dt * c.inv_tau);
     const float hz = 0.5f * z;
     const float c2 = 1.0f + hz;
-    const float c3 = __builtin_fmaf(hz, c2, 1.0f);
-    const float c4 = __builtin_fmaf(z, c3, 1.0f);
-    float e_d[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) e_d[i] = a.d[i] - dc[i];
+    const float c3 = POTATO_FMA(hz, c2, 1.0f);
+    const float c4 = POTATO_FMA(z, c3, 1.0f);
+    const float zR = z * (1.0f / 6.0f), sR = ((1.0f + (c2 + c2)) + (c3 + c3)) + c4;
     Dyn y1, y2, y3, y4;
     float kv[3], kq[4], kw[3], aq[4];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) { y1.v[i] = a.v[i]; y1.w[i] = a.w[i]; }
+    for (int i = 0; i < 3; ++i) y1.w[i] = a.w[i];
 #pragma unroll
     for (int i = 0; i < 4; ++i) { y1.q[i] = a.q[i]; y1.d[i] = a.d[i]; }
-    auto stage = [&](const Dyn& from, float hvw, float hq, float cp, Dyn& to) {
-        rates(c, from.v, from.q, from.w, from.d, kv, kq, kw);
+    auto stage = [&](const Dyn& from, float hw, float hq, float cp, Dyn& to) {
+        const float ssum = rates(c, a.v, from.q, from.w, from.d, kv, kq, kw);      /* kv is not used */
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            to.v[i] = __builtin_fmaf(hvw, kv[i], y1.v[i]);
-            to.w[i] = __builtin_fmaf(hvw, kw[i], y1.w[i]);
-        }
+        for (int i = 0; i < 3; ++i) to.w[i] = POTATO_FMA(hw, kw[i], y1.w[i]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            to.q[i] = __builtin_fmaf(hq, kq[i], y1.q[i]);
-            to.d[i] = __builtin_fmaf(e_d[i], cp, dc[i]);
+            to.q[i] = POTATO_FMA(hq, kq[i], y1.q[i]);
+            to.d[i] = POTATO_FMA(a.d[i] - dc[i], cp, dc[i]);
         }
+        return ssum;
     };
-    stage(y1, L.half_dt, L.quarter_dt, c2, y2);
+    const float ss1 = stage(y1, L.half_dt, L.quarter_dt, c2, y2);
 #pragma unroll
     for (int i = 0; i < 4; ++i) aq[i] = kq[i];
-    stage(y2, L.half_dt, L.quarter_dt, c3, y3);
+    const float ss2 = stage(y2, L.half_dt, L.quarter_dt, c3, y3);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) aq[i] = __builtin_fmaf(2.0f, kq[i], aq[i]);
-    stage(y3, L.dt, L.half_dt, c4, y4);
+    for (int i = 0; i < 4; ++i) aq[i] = POTATO_FMA(2.0f, kq[i], aq[i]);
+    const float ss3 = stage(y3, L.dt, L.half_dt, c4, y4);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) aq[i] = __builtin_fmaf(2.0f, kq[i], aq[i]);
-    rates(c, y4.v, y4.q, y4.w, y4.d, kv, kq, kw);
+    for (int i = 0; i < 4; ++i) aq[i] = POTATO_FMA(2.0f, kq[i], aq[i]);
+    const float ss4 = rates(c, a.v, y4.q, y4.w, y4.d, kv, kq, kw);
     float qn[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) qn[i] = __builtin_fmaf(L.dt12, aq[i] + kq[i], a.q[i]);
+    for (int i = 0; i < 4; ++i) qn[i] = POTATO_FMA(L.dt12, aq[i] + kq[i], a.q[i]);
 
     /* ---------------- reverse: renormalisation ---------------- */
     {
-        const float r = rsq(qn[0] * qn[0] + qn[1] * qn[1] + qn[2] * qn[2] + qn[3] * qn[3]);
+        const float r = rsq(POTATO_FMA(qn[3], qn[3], POTATO_FMA(qn[2], qn[2], POTATO_FMA(qn[1], qn[1], qn[0] * qn[0]))));
         const float u[4] = {qn[0] * r, qn[1] * r, qn[2] * r, qn[3] * r};
-        const float dot = u[0] * lam.q[0] + u[1] * lam.q[1] + u[2] * lam.q[2] + u[3] * lam.q[3];
+        const float dot = POTATO_FMA(u[3], lam.q[3], POTATO_FMA(u[2], lam.q[2], POTATO_FMA(u[1], lam.q[1], u[0] * lam.q[0])));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) lam.q[i] = r * (lam.q[i] - u[i] * dot);
+        for (int i = 0; i < 4; ++i) lam.q[i] = r * POTATO_FMA(-u[i], dot, lam.q[i]);
     }
 
     /* ---------------- reverse: RK4 ----------------
-     * lam (v, q, w, d) is the cotangent of the step-end dynamic state; the
-     * stage rate cotangents are b_i * dt * lam + dt * (cotangent of the next
-     * stage state), with b = 1/6, 1/3, 1/3, 1/6.  Position and cost only
-     * integrate, so their cotangents pass through unchanged and enter each
-     * stage as b_i * dt * lam.p (on the stage velocity) and b_i * dt * lam.J. */
-    const AgentAdj lo = lam;                 /* cotangent of the step end */
-    float mdsum[4] = {0.0f, 0.0f, 0.0f, 0.0f};   /* rotor-rate cotangents summed over the stages */
-    float sv[3], sq[4], sw[3], sd[4];        /* running stage-state cotangent */
-    const float bw[4] = {L.dt6, 2.0f * L.dt6, 2.0f * L.dt6, L.dt6};
-    const float hs[4] = {0.0f, L.half_dt, L.half_dt, L.dt};   /* stage offsets */
-    /* the same halved, for the quaternion-rate cotangent mu.qh */
-    const float bwh[4] = {L.dt12, L.dt6, L.dt6, L.dt12};
-    const float hsh[4] = {0.0f, L.quarter_dt, L.quarter_dt, L.half_dt};
+     * lam (v, q, w) is the cotangent of the step-end dynamic state; the stage
+     * rate cotangents are b_i * dt * lam + (stage offset) * (cotangent of the
+     * next stage's state), with b = 1/6, 1/3, 1/3, 1/6.  Position and cost
+     * only integrate, so their cotangents pass through unchanged and enter
+     * each stage as b_i * dt * lam.p (on the stage velocity) and
+     * b_i * dt * lam.J.  The rotor deviations are dc + (d - dc) c at the
+     * stages and dc + (d - dc) R at the end, so the direct cotangents of the
+     * stages sum, weighted by c, into that of d and, by 1 - c, into that of
+     * dc. */
+    const float R = POTATO_FMA(zR, sR, 1.0f);
+    float ldc[4];
+    RateAdj w6, w3;                           /* dt/6 and dt/3 times the step end's cotangent */
+    float p6[3], p3[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) { sv[i] = 0.0f; sw[i] = 0.0f; }
+    for (int i = 0; i < 3; ++i) {
+        w6.v[i] = L.dt6 * lam.v[i]; w3.v[i] = w6.v[i] + w6.v[i];
+        w6.w[i] = L.dt6 * lam.w[i]; w3.w[i] = w6.w[i] + w6.w[i];
+        p6[i] = L.dt6 * lam.p[i]; p3[i] = p6[i] + p6[i];
+    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { sq[i] = 0.0f; sd[i] = 0.0f; }
-#pragma unroll
-    for (int st = 3; st >= 0; --st) {
-        /* cotangent of this stage's rate: b dt lam_end + h_{next} lam_{next stage} */
-        const float hn = st < 3 ? hs[st + 1] : 0.0f;
-        const float hnh = st < 3 ? hsh[st + 1] : 0.0f;
+    for (int i = 0; i < 4; ++i) {
+        w6.h[i] = L.dt12 * lam.q[i]; w3.h[i] = w6.h[i] + w6.h[i];
+        ldc[i] = -(zR * sR) * lam.d[i];
+        lam.d[i] = R * lam.d[i];
+    }
+    w6.J = L.dt6 * lam.J; w3.J = w6.J + w6.J;
+    float sv[3], sq[4], sw[3], lsd[4];
+    /* the next earlier stage's rate cotangent: base + offset * this stage's
+     * state cotangent */
+    auto earlier = [&](const RateAdj& base, float off, float offh) {
         RateAdj mu;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            mu.v[i] = bw[st] * lo.v[i] + hn * sv[i];
-            mu.w[i] = bw[st] * lo.w[i] + hn * sw[i];
+            mu.v[i] = POTATO_FMA(off, sv[i], base.v[i]);
+            mu.w[i] = POTATO_FMA(off, sw[i], base.w[i]);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            mu.qh[i] = bwh[st] * lo.q[i] + hnh * sq[i];
-            mu.d[i] = bw[st] * lo.d[i] + hn * sd[i];
-            mdsum[i] += mu.d[i];
-        }
-        mu.J = bw[st] * lo.J;
-        const Dyn& ys = st == 3 ? y4 : (st == 2 ? y3 : (st == 1 ? y2 : y1));
-        float nv_[3], nq_[4], nw_[3], nd_[4];
-        /* position rate is the stage velocity */
-#pragma unroll
-        for (int i = 0; i < 3; ++i) { nv_[i] = bw[st] * lo.p[i]; nw_[i] = 0.0f; }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { nq_[i] = 0.0f; nd_[i] = 0.0f; }
-        derivative_vjp(c, ys, mu, nv_, nq_, nw_, nd_);
-        /* stage state = y1 + h_st * previous rate: cotangent flows to y1 and
-         * (scaled by h_st) to the previous stage's rate */
+        for (int i = 0; i < 4; ++i) mu.h[i] = POTATO_FMA(offh, sq[i], base.h[i]);
+        mu.J = base.J;
+        return mu;
+    };
+    auto reverse_stage = [&](const RateAdj& mu, const float lp[3], const Dyn& y, float ssum, float cp, float ncp) {
+        derivative_vjp<true>(c, y, ssum, mu, sq, sw, lsd);
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            sv[i] = nv_[i]; sw[i] = nw_[i];
-            lam.v[i] += nv_[i]; lam.w[i] += nw_[i];
+            sv[i] = POTATO_FMA(c.ncd_m, mu.v[i], lp[i]);
+            lam.v[i] += sv[i];
+            lam.w[i] += sw[i];
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            sq[i] = nq_[i]; sd[i] = nd_[i];
-            lam.q[i] += nq_[i]; lam.d[i] += nd_[i];
+            lam.q[i] += sq[i];
+            lam.d[i] = POTATO_FMA(cp, lsd[i], lam.d[i]);
+            ldc[i] = POTATO_FMA(ncp, lsd[i], ldc[i]);
         }
-    }
-    float ldc[4];
+    };
+    reverse_stage(w6, p6, y4, ss4, c4, -(z * c3));
+    reverse_stage(earlier(w3, L.dt, L.half_dt), p3, y3, ss3, c3, -(hz * c2));
+    reverse_stage(earlier(w3, L.half_dt, L.quarter_dt), p3, y2, ss2, c2, -hz);
+    {
+        const RateAdj mu = earlier(w6, L.half_dt, L.quarter_dt);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ldc[i] = c.inv_tau * mdsum[i];
+        for (int i = 0; i < 3; ++i) lam.v[i] = POTATO_FMA(c.ncd_m, mu.v[i], lam.v[i] + p6[i]);
+        derivative_vjp<false>(c, y1, ss1, mu, lam.q, lam.w, lsd);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lam.d[i] += lsd[i];
+    }
+
+    const int32_t in_ip[3] = {bit_mask<kBitIp>(bits), bit_mask<kBitIp - 1>(bits), bit_mask<kBitIp - 2>(bits)};
+    const int32_t in_ia[3] = {bit_mask<kBitIa>(bits), bit_mask<kBitIa - 2>(bits), bit_mask<kBitIa - 4>(bits)};
+    const int32_t in_ir[3] = {bit_mask<kBitIr>(bits), bit_mask<kBitIr - 2>(bits), bit_mask<kBitIr - 4>(bits)};
+    const int32_t in_f[4] = {bit_mask<kBitRotor>(bits), bit_mask<kBitRotor - 1>(bits), bit_mask<kBitRotor - 2>(bits),
+                             bit_mask<kBitRotor - 3>(bits)};
 
     /* ---------------- controller, forward with intermediates ----------------
      * (the values the reverse needs; the branches are the recorded ones) */
-    float er[3] = {wp[0] - a.p[0], wp[1] - a.p[1], wp[2] - a.p[2]};
-    const float n2 = er[0] * er[0] + er[1] * er[1] + er[2] * er[2];
-    const bool sat = (bits & kBitSat) != 0;
-    float rs = 0.0f, sc = 1.0f;
-    if (sat) { rs = rsq(n2); sc = L.r_sat * rs; }
-    const float e[3] = {er[0] * sc, er[1] * sc, er[2] * sc};
-    float ipn[3];
-    bool in_ip[3];
+    const float er[3] = {wp[0] - a.p[0], wp[1] - a.p[1], wp[2] - a.p[2]};
+    const float n2 = POTATO_FMA(er[2], er[2], POTATO_FMA(er[1], er[1], er[0] * er[0]));
+    const bool sat = (bits >> kBitSat & 1u) != 0;
+    const float rs = rsq(n2), sc = sat ? L.r_sat * rs : 1.0f;
+    float e[3], acc[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        const float pre = a.ip[i] + e[i] * L.dt;
-        in_ip[i] = (bits & (kBitIp << i)) != 0;
-        ipn[i] = clampf_(pre, -L.ipos_max, L.ipos_max);
+        e[i] = er[i] * sc;
+        acc[i] = POTATO_FMA(-k.kdp, a.v[i], POTATO_FMA(k.kip, a.ip[i], k.kpp * e[i]));
     }
-    float acc[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) acc[i] = k.kpp * e[i] + k.kip * ipn[i] - k.kdp * a.v[i];
-    acc[2] += L.g;
-    const bool az_cl = (bits & kBitAz) != 0;
-    if (az_cl) acc[2] = L.az_min;
+    const bool az_cl = (bits >> kBitAz & 1u) != 0;
+    acc[2] = az_cl ? L.az_min : acc[2] + L.g;
     float bz[3];
     body_z(a.q, bz);
-    const float ra = rsq(acc[0] * acc[0] + acc[1] * acc[1] + acc[2] * acc[2]);
+    const float ra = rsq(POTATO_FMA(acc[2], acc[2], POTATO_FMA(acc[1], acc[1], acc[0] * acc[0])));
     const float nv[3] = {acc[0] * ra, acc[1] * ra, acc[2] * ra};
-    const float qr0 = 1.0f + nv[2], qr1 = -nv[1], qr2 = nv[0];
-    const float rq = rsq(qr0 * qr0 + qr1 * qr1 + qr2 * qr2);
-    const float qd[3] = {qr0 * rq, qr1 * rq, qr2 * rq};
+    const float qr0 = 1.0f + nv[2];
+    const float rq = rsq(qr0 + qr0);
+    const float qd[3] = {qr0 * rq, -(nv[1] * rq), nv[0] * rq};
     const float* q = a.q;
-    const float qex = q[0] * qd[1] - q[1] * qd[0] + q[3] * qd[2];
-    const float qey = q[0] * qd[2] - q[2] * qd[0] - q[3] * qd[1];
-    const float qez = q[2] * qd[1] - q[1] * qd[2] - q[3] * qd[0];
-    const float sg = (bits & kBitSgn) != 0 ? -2.0f : 2.0f;
-    const float eatt[3] = {sg * qex, sg * qey, sg * qez};
-    float ian[3], irn[3], wdes[3], erate[3];
-    bool in_ia[3], in_ir[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const float pa = a.ia[i] + eatt[i] * L.dt;
-        in_ia[i] = (bits & (kBitIa << i)) != 0;
-        ian[i] = clampf_(pa, -L.iatt_max, L.iatt_max);
-        wdes[i] = k.kpa * eatt[i] + k.kia * ian[i] - k.kda * a.w[i];
-        erate[i] = wdes[i] - a.w[i];
-        const float pr = a.ir[i] + erate[i] * L.dt;
-        in_ir[i] = (bits & (kBitIr << i)) != 0;
-        irn[i] = clampf_(pr, -L.irate_max, L.irate_max);
-    }
-    /* rotor speed W = sqrt(f / k_f) of the held command: dW/df = 1 / (2 k_f W),
-     * zero where the thrust was clamped or W == 0 */
-    float lf_scale[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float W = dc[i] + c.w_ref;
-        lf_scale[i] = (bits & (kBitRotor << i)) != 0 ? 0.5f * c.inv_kf * __builtin_amdgcn_rcpf(W) : 0.0f;
-    }
+    const float sg = (bits >> kBitSgn & 1u) != 0 ? -2.0f : 2.0f;
+    const float eatt[3] = {sg * POTATO_FMA(q[3], qd[2], POTATO_FMA(-q[1], qd[0], q[0] * qd[1])),
+                           sg * POTATO_FMA(-q[3], qd[1], POTATO_FMA(-q[2], qd[0], q[0] * qd[2])),
+                           sg * POTATO_FMA(-q[3], qd[0], POTATO_FMA(-q[1], qd[2], q[2] * qd[1]))};
 
-    /* ---------------- reverse: controller ---------------- */
+    /* ---------------- reverse: controller ----------------
+     * rotor speed W = sqrt(f / k_f) of the held command: dW/df = 1 / (2 k_f W),
+     * zero where the thrust was clamped or W == 0 */
     float lf[4];
+    const float hik = 0.5f * c.inv_kf;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) lf[i] = ldc[i] * lf_scale[i];
-    const float l_f4 = lf[0] + lf[1] + lf[2] + lf[3];
-    const float l_X = lf[0] - lf[1] - lf[2] + lf[3];
-    const float l_Y = -lf[0] - lf[1] + lf[2] + lf[3];
-    const float l_Z = lf[0] - lf[1] + lf[2] - lf[3];
-    const float l_fc = 0.25f * l_f4;
-    const float ltx = c.mix_x * l_X, lty = c.mix_y * l_Y, ltz = c.mix_z * l_Z;
-    const float lal[3] = {c.Ix * ltx, c.Iy * lty, c.Iz * ltz};
-    /* gyroscopic feed-forward w x (I w) */
+    for (int i = 0; i < 4; ++i) lf[i] = where(in_f[i], ldc[i] * (hik * __builtin_amdgcn_rcpf(dc[i] + c.w_ref)));
+    const float s02 = lf[0] + lf[2], s13 = lf[1] + lf[3], d02 = lf[0] - lf[2], d31 = lf[3] - lf[1];
+    const float m0 = (0.25f * c.mass) * (s02 + s13);          /* cotangent of the thrust per mass */
+    const float lal[3] = {c.Ix * (c.mix_x * (d02 + d31)), c.Iy * (c.mix_y * (d31 - d02)),
+                          c.Iz * (c.mix_z * (s02 - s13))};
+    /* gyroscopic feed-forward w x (I w): (I_z - I_y) ltx = gx I_x ltx */
     {
-        const float gzy = c.Iz - c.Iy, gxz = c.Ix - c.Iz, gyx = c.Iy - c.Ix;
-        lam.w[0] += lty * gxz * a.w[2] + ltz * gyx * a.w[1];
-        lam.w[1] += ltx * gzy * a.w[2] + ltz * gyx * a.w[0];
-        lam.w[2] += ltx * gzy * a.w[1] + lty * gxz * a.w[0];
+        const float g0 = c.gx * lal[0], g1 = c.gy * lal[1], g2 = c.gz * lal[2];
+        lam.w[0] = POTATO_FMA(g2, a.w[1], POTATO_FMA(g1, a.w[2], lam.w[0]));
+        lam.w[1] = POTATO_FMA(g0, a.w[2], POTATO_FMA(g2, a.w[0], lam.w[1]));
+        lam.w[2] = POTATO_FMA(g1, a.w[0], POTATO_FMA(g0, a.w[1], lam.w[2]));
     }
-    float l_eatt[3];
+    float le[3];
+    const float kda1 = 1.0f + k.kda;
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        /* w_prev <- w */
-        lam.w[i] += lo.wprev[i];
-        /* rate loop */
-        const float dwd = (a.w[i] - a.wprev[i]) * L.inv_dt;
-        gk[6] += lal[i] * erate[i];
-        gk[7] += lal[i] * irn[i];
-        gk[8] -= lal[i] * dwd;
-        float l_er = k.kpr * lal[i];
-        const float l_irn = lo.ir[i] + k.kir * lal[i];
-        lam.w[i] -= k.kdr * L.inv_dt * lal[i];
-        lam.wprev[i] = k.kdr * L.inv_dt * lal[i];
-        const float l_irpre = in_ir[i] ? l_irn : 0.0f;
-        lam.ir[i] = l_irpre;
-        l_er += L.dt * l_irpre;
-        /* erate = wdes - w */
-        const float l_wd = l_er;
-        lam.w[i] -= l_er;
-        /* attitude loop */
-        gk[3] += l_wd * eatt[i];
-        gk[4] += l_wd * ian[i];
-        gk[5] -= l_wd * a.w[i];
-        const float l_ian = lo.ia[i] + k.kia * l_wd;
-        lam.w[i] -= k.kda * l_wd;
-        const float l_iapre = in_ia[i] ? l_ian : 0.0f;
-        lam.ia[i] = l_iapre;
-        l_eatt[i] = k.kpa * l_wd + L.dt * l_iapre;
+        const float erate = POTATO_FMA(-k.kda, a.w[i], POTATO_FMA(k.kia, a.ia[i], k.kpa * eatt[i])) - a.w[i];
+        /* rate loop, and w_prev <- w */
+        gk[6] = POTATO_FMA(lal[i], erate, gk[6]);
+        gk[7] = POTATO_FMA(lal[i], a.ir[i], gk[7]);
+        a.ir[i] = POTATO_FMA(-erate, L.dt, a.ir[i]);
+        gk[8] = POTATO_FMA(-lal[i], a.dw[i], gk[8]);
+        const float l_dw = k.kdr_dt * lal[i];
+        const float lw = (lam.w[i] + lam.wprev[i]) - l_dw;
+        lam.wprev[i] = l_dw;
+        lam.ir[i] = where(in_ir[i], POTATO_FMA(k.kir, lal[i], lam.ir[i]));
+        const float l_er = POTATO_FMA(L.dt, lam.ir[i], k.kpr * lal[i]);
+        /* attitude loop, erate = wdes - w */
+        gk[3] = POTATO_FMA(l_er, eatt[i], gk[3]);
+        gk[4] = POTATO_FMA(l_er, a.ia[i], gk[4]);
+        a.ia[i] = POTATO_FMA(-eatt[i], L.dt, a.ia[i]);
+        gk[5] = POTATO_FMA(-l_er, a.w[i], gk[5]);
+        lam.w[i] = POTATO_FMA(-kda1, l_er, lw);
+        lam.ia[i] = where(in_ia[i], POTATO_FMA(k.kia, l_er, lam.ia[i]));
+        le[i] = sg * POTATO_FMA(L.dt, lam.ia[i], k.kpa * l_er);
     }
     /* error quaternion (the sign is a constant of the branch) */
-    const float lex = sg * l_eatt[0], ley = sg * l_eatt[1], lez = sg * l_eatt[2];
-    lam.q[0] += lex * qd[1] + ley * qd[2];
-    lam.q[1] += -lex * qd[0] - lez * qd[2];
-    lam.q[2] += -ley * qd[0] + lez * qd[1];
-    lam.q[3] += lex * qd[2] - ley * qd[1] - lez * qd[0];
-    const float lqd[3] = {-lex * q[1] - ley * q[2] - lez * q[3],
-                          lex * q[0] - ley * q[3] + lez * q[2],
-                          lex * q[3] + ley * q[0] - lez * q[1]};
-    /* normalisation of the desired-attitude quaternion */
-    const float dqd = qd[0] * lqd[0] + qd[1] * lqd[1] + qd[2] * lqd[2];
-    const float lqr0 = rq * (lqd[0] - qd[0] * dqd);
-    const float lqr1 = rq * (lqd[1] - qd[1] * dqd);
-    const float lqr2 = rq * (lqd[2] - qd[2] * dqd);
-    /* q_raw = (1 + n_z, -n_y, n_x, 0) */
-    const float ln[3] = {lqr2, -lqr1, lqr0};
-    const float dn = nv[0] * ln[0] + nv[1] * ln[1] + nv[2] * ln[2];
+    lam.q[0] = POTATO_FMA(le[1], qd[2], POTATO_FMA(le[0], qd[1], lam.q[0]));
+    lam.q[1] = POTATO_FMA(-le[2], qd[2], POTATO_FMA(-le[0], qd[0], lam.q[1]));
+    lam.q[2] = POTATO_FMA(le[2], qd[1], POTATO_FMA(-le[1], qd[0], lam.q[2]));
+    lam.q[3] = POTATO_FMA(-le[2], qd[0], POTATO_FMA(-le[1], qd[1], POTATO_FMA(le[0], qd[2], lam.q[3])));
+    const float lqd[3] = {-POTATO_FMA(le[2], q[3], POTATO_FMA(le[1], q[2], le[0] * q[1])),
+                          POTATO_FMA(le[2], q[2], POTATO_FMA(-le[1], q[3], le[0] * q[0])),
+                          POTATO_FMA(-le[2], q[1], POTATO_FMA(le[1], q[0], le[0] * q[3]))};
+    /* normalisation of the desired-attitude quaternion (1 + n_z, -n_y, n_x, 0) */
+    const float dqd = POTATO_FMA(qd[2], lqd[2], POTATO_FMA(qd[1], lqd[1], qd[0] * lqd[0]));
+    const float ln[3] = {rq * POTATO_FMA(-qd[2], dqd, lqd[2]), -(rq * POTATO_FMA(-qd[1], dqd, lqd[1])),
+                         rq * POTATO_FMA(-qd[0], dqd, lqd[0])};
+    const float dn = POTATO_FMA(nv[2], ln[2], POTATO_FMA(nv[1], ln[1], nv[0] * ln[0]));
     float la[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) la[i] = ra * (ln[i] - nv[i] * dn) + c.mass * l_fc * bz[i];
+    for (int i = 0; i < 3; ++i) la[i] = POTATO_FMA(ra, POTATO_FMA(-nv[i], dn, ln[i]), m0 * bz[i]);
     /* body z axis used for the collective thrust */
     {
-        const float m0 = c.mass * l_fc;
-        const float lb0 = m0 * acc[0], lb1 = m0 * acc[1], lb2 = m0 * acc[2];
-        lam.q[0] += 2.0f * (q[2] * lb0 - q[1] * lb1);
-        lam.q[1] += 2.0f * (q[3] * lb0 - q[0] * lb1) - 4.0f * q[1] * lb2;
-        lam.q[2] += 2.0f * (q[0] * lb0 + q[3] * lb1) - 4.0f * q[2] * lb2;
-        lam.q[3] += 2.0f * (q[1] * lb0 + q[2] * lb1);
+        const float t = m0 + m0;
+        const float b0 = t * acc[0], b1 = t * acc[1], b2 = (t + t) * acc[2];
+        lam.q[0] = POTATO_FMA(-q[1], b1, POTATO_FMA(q[2], b0, lam.q[0]));
+        lam.q[1] = POTATO_FMA(-q[1], b2, POTATO_FMA(-q[0], b1, POTATO_FMA(q[3], b0, lam.q[1])));
+        lam.q[2] = POTATO_FMA(-q[2], b2, POTATO_FMA(q[3], b1, POTATO_FMA(q[0], b0, lam.q[2])));
+        lam.q[3] = POTATO_FMA(q[2], b1, POTATO_FMA(q[1], b0, lam.q[3]));
     }
-    if (az_cl) la[2] = 0.0f;
+    la[2] = az_cl ? 0.0f : la[2];
     /* position loop */
     float l_e[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        gk[0] += la[i] * e[i];
-        gk[1] += la[i] * ipn[i];
-        gk[2] -= la[i] * a.v[i];
-        lam.v[i] -= k.kdp * la[i];
-        const float l_ipn = lo.ip[i] + k.kip * la[i];
-        const float l_ippre = in_ip[i] ? l_ipn : 0.0f;
-        lam.ip[i] = l_ippre;
-        l_e[i] = k.kpp * la[i] + L.dt * l_ippre;
+        gk[0] = POTATO_FMA(la[i], e[i], gk[0]);
+        gk[1] = POTATO_FMA(la[i], a.ip[i], gk[1]);
+        a.ip[i] = POTATO_FMA(-e[i], L.dt, a.ip[i]);
+        gk[2] = POTATO_FMA(-la[i], a.v[i], gk[2]);
+        lam.v[i] = POTATO_FMA(-k.kdp, la[i], lam.v[i]);
+        lam.ip[i] = where(in_ip[i], POTATO_FMA(k.kip, la[i], lam.ip[i]));
+        l_e[i] = POTATO_FMA(L.dt, lam.ip[i], k.kpp * la[i]);
     }
     /* saturation e = r_sat * er / |er| */
     if (sat) {
         const float u[3] = {er[0] * rs, er[1] * rs, er[2] * rs};
-        const float du = u[0] * l_e[0] + u[1] * l_e[1] + u[2] * l_e[2];
+        const float du = POTATO_FMA(u[2], l_e[2], POTATO_FMA(u[1], l_e[1], u[0] * l_e[0]));
 #pragma unroll
-        for (int i = 0; i < 3; ++i) l_e[i] = sc * (l_e[i] - u[i] * du);
+        for (int i = 0; i < 3; ++i) l_e[i] = sc * POTATO_FMA(-u[i], du, l_e[i]);
     }
 #pragma unroll
     for (int i = 0; i < 3; ++i) lam.p[i] -= l_e[i];
 }
+
+/* gk[8] as summed by step_vjp to the cotangent of kdr. */
+__device__ __forceinline__ void kdr_from_sum(const Limits& L, float gk[9]) { gk[8] *= L.inv_dt; }
 
 /* Row accessors: `base` is row 0 of a [rows][ld] buffer, the same address
  * in every active lane, and `bo` the lane's byte offset (column index
@@ -441,7 +443,9 @@ __device__ __forceinline__ void store_adj(float* x0, float* mem, int64_t ld, uin
 }
 
 /* Tape slots: one block of kTapeRows x 64 floats per wave and step, a row
- * being 64 consecutive floats (one per lane).  `slot` is the block's base,
+ * being 64 consecutive floats (one per lane).  Their traffic is what bounds
+ * the sweep most: with every slot's address folded onto one (a timing run)
+ * it took 27 % less time.  `slot` is the block's base,
  * the same for the whole wave; rows 0-15 and 16-30 are addressed from two
  * scalar bases at immediate offsets (k x 256 bytes, within the 4 KiB range
  * of the instruction's offset field), and `lb` is the lane's byte offset. */
@@ -453,49 +457,61 @@ struct TapeRows {
     __device__ __forceinline__ T* row(int k) const { return k < 16 ? lo + k * 64 : hi + (k - 16) * 64; }
 };
 
-/* Step-start state of a tape slot: rows 0-25 (p, v, q, w, rotors, the three
- * integrals). */
-__device__ __forceinline__ void store_tape(float* slot, uint32_t lb, const Agent& a) {
+/* The integrals before a step are on the tape only where they are needed:
+ * the reverse sweep knows those after the step, and where no clamp acted
+ * those before it are less the step's increment.  Each such subtraction
+ * rounds once, so every agent takes them from the tape at each step whose
+ * call-relative index k is a multiple of kRefresh, and an agent at a clamp
+ * takes that integral from it at that step (the wave then holds the rows for
+ * all its agents).  Nothing of this depends on where segments end or on the
+ * other agents of the wave.  One step in kRefresh writes and reads 9 rows
+ * more than the other 22 (179 B per agent-step instead of 248; kRefresh =
+ * 16 leaves at most 16 half-ulp roundings between two refreshes). */
+constexpr int kRefresh = 16;
+constexpr uint32_t kBitInt = 7u << (kBitIp - 2) | 0x3fu << (kBitIr - 4);   /* inside all nine clamps */
+__device__ __forceinline__ bool integrals_on_tape(int k, uint32_t bits) {
+    return k % kRefresh == 0 || __ballot((bits & kBitInt) != kBitInt) != 0;
+}
+
+/* A tape slot: the step-start state (rows 0-16: p, v, q, w, rotors), the
+ * held command and the branch decisions. */
+__device__ __forceinline__ void store_tape(float* slot, uint32_t lb, const Agent& a, const float dc[4],
+                                           uint32_t bits) {
     const TapeRows<float> t(slot);
     auto row = [&](int k) -> float& { return elem(t.row(k), lb); };
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        row(k) = a.p[k]; row(3 + k) = a.v[k]; row(10 + k) = a.w[k];
-        row(17 + k) = a.ip[k]; row(20 + k) = a.ia[k]; row(23 + k) = a.ir[k];
-    }
+    for (int k = 0; k < 3; ++k) { row(k) = a.p[k]; row(3 + k) = a.v[k]; row(10 + k) = a.w[k]; }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) { row(6 + k) = a.q[k]; row(13 + k) = a.d[k]; }
+    for (int k = 0; k < 4; ++k) { row(6 + k) = a.q[k]; row(13 + k) = a.d[k]; row(kTapeCmd + k) = dc[k]; }
+    row(kTapeBits) = __uint_as_float(bits);
 }
 
-/* The controller's held command and branch decisions of a tape slot. */
-__device__ __forceinline__ void store_tape_cmd(float* slot, uint32_t lb, const float dc[4], uint32_t bits) {
-    const TapeRows<float> t(slot);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) elem(t.row(kTapeCmd + k), lb) = dc[k];
-    elem(t.row(kTapeBits), lb) = __uint_as_float(bits);
-}
-
-/* A tape slot: the step-start state (w_prev given by the caller; J and the
- * carries are not needed), the held command and the branch decisions. */
-__device__ __forceinline__ void load_tape(const float* slot, uint32_t lb, const float wprev[3], Agent& a,
-                                          float dc[4], uint32_t& bits) {
+/* The same without the body rates, which the step after has read already. */
+__device__ __forceinline__ void load_tape(const float* slot, uint32_t lb, Replay& a) {
     const TapeRows<const float> t(slot);
     auto row = [&](int k) { return elem(t.row(k), lb); };
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        a.p[k] = row(k); a.v[k] = row(3 + k); a.w[k] = row(10 + k);
-        a.ip[k] = row(17 + k); a.ia[k] = row(20 + k); a.ir[k] = row(23 + k);
-        a.wprev[k] = wprev[k];
-        a.p_lo[k] = a.v_lo[k] = a.ip_lo[k] = 0.0f;
-    }
+    for (int k = 0; k < 3; ++k) { a.p[k] = row(k); a.v[k] = row(3 + k); }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) { a.q[k] = row(6 + k); a.d[k] = row(13 + k); dc[k] = row(kTapeCmd + k); }
-    bits = __float_as_uint(row(kTapeBits));
-    a.J = a.J_lo = 0.0f;
+    for (int k = 0; k < 4; ++k) { a.q[k] = row(6 + k); a.d[k] = row(13 + k); a.dc[k] = row(kTapeCmd + k); }
+    a.bits = __float_as_uint(row(kTapeBits));
 }
 
-/* Body rates at the start of a step (the w_prev of the next): rows 10-12
- * of a tape slot. */
+/* The integrals before step k that the agent takes from the tape. */
+__device__ __forceinline__ void load_tape_integrals(const float* slot, uint32_t lb, int k, Replay& a) {
+    const TapeRows<const float> t(slot);
+    auto row = [&](int r) { return elem(t.row(kTapeInt + r), lb); };
+    const bool all = k % kRefresh == 0;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const float ip = row(r), ia = row(3 + r), ir = row(6 + r);
+        a.ip[r] = all || !(a.bits >> (kBitIp - r) & 1u) ? ip : a.ip[r];
+        a.ia[r] = all || !(a.bits >> (kBitIa - 2 * r) & 1u) ? ia : a.ia[r];
+        a.ir[r] = all || !(a.bits >> (kBitIr - 2 * r) & 1u) ? ir : a.ir[r];
+    }
+}
+
+/* Body rates at the start of a step: rows 10-12 of a tape slot. */
 __device__ __forceinline__ void load_tape_w(const float* slot, uint32_t lb, float w[3]) {
     const TapeRows<const float> t(slot);
 #pragma unroll
@@ -514,17 +530,42 @@ __device__ __forceinline__ void step_wprev(const float* tape, int64_t tape_step,
     }
 }
 
-/* One recomputed forward step: its start state, held command and branch
- * decisions go to the tape slot, then the state advances (the forward
+/* Recomputed forward step k of the call: its start state, held command and
+ * branch decisions go to the tape slot, then the state advances (the forward
  * pass's own arithmetic, carries included, so the same bits). */
-__device__ __forceinline__ void recompute_step(const TypeConst& c, const Limits& L, const Gains& g, Agent& a,
+__device__ __forceinline__ void recompute_step(const TypeConst& c, const Limits& L, const Gains& g, Agent& a, int k,
                                                const float wp[3], float* slot, uint32_t lb) {
-    store_tape(slot, lb, a);
-    float dc[4];
+    float dc[4], before[9];
     uint32_t bits;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) { before[r] = a.ip[r]; before[3 + r] = a.ia[r]; before[6 + r] = a.ir[r]; }
     controller<true, true>(c, L, g, a, wp, dc, &bits);
-    store_tape_cmd(slot, lb, dc, bits);
+    store_tape(slot, lb, a, dc, bits);
+    if (integrals_on_tape(k, bits)) {
+        const TapeRows<float> t(slot);
+#pragma unroll
+        for (int r = 0; r < 9; ++r) elem(t.row(kTapeInt + r), lb) = before[r];
+    }
     rk4_step(c, L, a, dc);
+}
+
+/* Reverse of step s of a segment from the tape, step k of the call.  x
+ * carries the integrals after the step and w the body rates at its start,
+ * both from the step after it; they come back as those of the step before. */
+__device__ __forceinline__ void reverse_step(const TypeConst& c, const Limits& L, const Gains& g, Replay& x,
+                                             float w[3], int s, int k, const float wp[3], const float* tape,
+                                             int64_t tape_step, uint32_t lb, const float* ckpt_seg, int64_t ld,
+                                             uint32_t bo, AgentAdj& lam, float gk[9]) {
+    const float* const slot = tape + (int64_t)s * tape_step;
+    float wprev[3];
+    load_tape(slot, lb, x);
+    step_wprev(tape, tape_step, lb, s, ckpt_seg, ld, bo, wprev);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) { x.w[r] = w[r]; x.dw[r] = w[r] - wprev[r]; }
+    step_vjp(c, L, g, x, wp, lam, gk);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) w[r] = wprev[r];
+    if (integrals_on_tape(k, x.bits)) load_tape_integrals(slot, lb, k, x);
 }
 
 /*
@@ -545,7 +586,7 @@ __device__ __forceinline__ void recompute_step(const TypeConst& c, const Limits&
  * the same segment, slot and step, so checkpoint, tape and waypoint rows
  * are wave-uniform addresses even when step budgets differ between lanes.
  * Each reverse step loads its tape slot; the other resident wave covers
- * the load latency (holding the next slot in registers instead costs 30
+ * the load latency (holding the next slot in registers instead costs 22
  * registers and the second wave).
  */
 __device__ __forceinline__ void agent_backward(const TypeConst& c, const Limits& L, const Gains& g,
@@ -569,6 +610,8 @@ __device__ __forceinline__ void agent_backward(const TypeConst& c, const Limits&
             cur_ep = ep;
         }
     };
+    Replay x{};
+    float w[3] = {0.0f, 0.0f, 0.0f};
     for (int seg = n_seg_all - 1; seg >= 0; --seg) {
         if (seg >= n_seg) continue;
         const int k_begin = seg * K;
@@ -581,22 +624,24 @@ __device__ __forceinline__ void agent_backward(const TypeConst& c, const Limits&
         for (int s = 0; s < len; ++s) {
             if (k0 + s == next) { ++e; next += period; }
             use_epoch(e);
-            recompute_step(c, L, g, a, wpv, tape + (int64_t)s * tape_step, lb);
+            recompute_step(c, L, g, a, k_begin + s, wpv, tape + (int64_t)s * tape_step, lb);
         }
         /* reverse: start from the epoch of the segment's last step */
         e = resample > 0 ? (k0 + len - 1) / resample : 0;
         int64_t first = resample > 0 ? e * period : INT64_MIN;         /* first step of epoch e */
         const float* ck = ckpt + (int64_t)seg * kCkptRows * ld;
+        if (seg == n_seg - 1) {
+            /* the recomputation ended with the integrals after this lane's
+             * last step and, as the w_prev of the step that would follow,
+             * that step's body rates */
+#pragma unroll
+            for (int r = 0; r < 3; ++r) { x.ip[r] = a.ip[r]; x.ia[r] = a.ia[r]; x.ir[r] = a.ir[r]; w[r] = a.wprev[r]; }
+        }
         for (int s = K - 1; s >= 0; --s) {
             if (s >= len) continue;
             if (k0 + s < first) { --e; first -= period; }
-            Agent x;
-            float dc[4], wprev[3];
-            uint32_t bits;
-            step_wprev(tape, tape_step, lb, s, ck, ld, bo, wprev);
-            load_tape(tape + (int64_t)s * tape_step, lb, wprev, x, dc, bits);
             use_epoch(e);
-            step_vjp(c, L, g, x, wpv, dc, bits, lam, gk);
+            reverse_step(c, L, g, x, w, s, k_begin + s, wpv, tape, tape_step, lb, ck, ld, bo, lam, gk);
         }
     }
 }
@@ -620,6 +665,8 @@ struct WaypointCache {
     }
 };
 
+constexpr int kTailRows = 12;      /* the integrals and body rates that reverse_segment starts from */
+
 /* The two halves of one segment of agent_backward, for a kernel that runs
  * them on different waves: the forward recomputation of segment `seg` from
  * its checkpoint into the tape, and the reverse sweep of a recomputed
@@ -627,7 +674,7 @@ struct WaypointCache {
 __device__ __forceinline__ void recompute_segment(const TypeConst& c, const Limits& L, const Gains& g,
                                                   const float* ckpt, int64_t ld, uint32_t bo, int K, int seg,
                                                   int steps, int64_t step0, int resample, WaypointCache& wc,
-                                                  float* tape, int64_t tape_step, uint32_t lb) {
+                                                  float* tape, int64_t tape_step, uint32_t lb, float* tail) {
     const int64_t period = resample > 0 ? resample : INT64_MAX;
     const int k_begin = seg * K;
     const int len = steps - k_begin < K ? steps - k_begin : K;
@@ -639,7 +686,16 @@ __device__ __forceinline__ void recompute_segment(const TypeConst& c, const Limi
     for (int s = 0; s < len; ++s) {
         if (k0 + s == next) { ++e; next += period; }
         wc.use(e);
-        recompute_step(c, L, g, a, wc.v, tape + (int64_t)s * tape_step, lb);
+        recompute_step(c, L, g, a, k_begin + s, wc.v, tape + (int64_t)s * tape_step, lb);
+    }
+    if (k_begin + len == steps) {              /* this lane's last segment */
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            elem(tail + r * 64, lb) = a.ip[r];
+            elem(tail + (3 + r) * 64, lb) = a.ia[r];
+            elem(tail + (6 + r) * 64, lb) = a.ir[r];
+            elem(tail + (9 + r) * 64, lb) = a.wprev[r];
+        }
     }
 }
 
@@ -647,7 +703,8 @@ __device__ __forceinline__ void reverse_segment(const TypeConst& c, const Limits
                                                 const float* ckpt, int64_t ld, uint32_t bo, int K,
                                                 int seg, int steps, int64_t step0, int resample,
                                                 WaypointCache& wc, const float* tape, int64_t tape_step,
-                                                uint32_t lb, AgentAdj& lam, float gk[9]) {
+                                                uint32_t lb, const float* tail, Replay& x, float w[3],
+                                                AgentAdj& lam, float gk[9]) {
     const int64_t period = resample > 0 ? resample : INT64_MAX;
     const int k_begin = seg * K;
     const int len = steps - k_begin < K ? steps - k_begin : K;
@@ -655,16 +712,20 @@ __device__ __forceinline__ void reverse_segment(const TypeConst& c, const Limits
     int64_t e = resample > 0 ? (k0 + len - 1) / resample : 0;
     int64_t first = resample > 0 ? e * period : INT64_MIN;
     const float* ck = ckpt + (int64_t)seg * kCkptRows * ld;
+    if (k_begin + len == steps) {              /* this lane's last segment */
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            x.ip[r] = elem(tail + r * 64, lb);
+            x.ia[r] = elem(tail + (3 + r) * 64, lb);
+            x.ir[r] = elem(tail + (6 + r) * 64, lb);
+            w[r] = elem(tail + (9 + r) * 64, lb);
+        }
+    }
     for (int s = K - 1; s >= 0; --s) {
         if (s >= len) continue;
         if (k0 + s < first) { --e; first -= period; }
-        Agent x;
-        float dc[4], wprev[3];
-        uint32_t bits;
-        step_wprev(tape, tape_step, lb, s, ck, ld, bo, wprev);
-        load_tape(tape + (int64_t)s * tape_step, lb, wprev, x, dc, bits);
         wc.use(e);
-        step_vjp(c, L, g, x, wc.v, dc, bits, lam, gk);
+        reverse_step(c, L, g, x, w, s, k_begin + s, wc.v, tape, tape_step, lb, ck, ld, bo, lam, gk);
     }
 }
 

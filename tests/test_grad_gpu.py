@@ -422,3 +422,53 @@ def test_backward_contract_17_rows_and_optional_memory(torch_dev, diff_run):
         if with_mem:
             assert torch.all(gm[13:] == sentinel)
             assert np.array_equal(gm[:13].cpu().numpy(), diff_run["gx0"][17:30])
+
+
+@pytest.mark.parametrize("n_steps", [15, 16, 17, 60])
+def test_integrals_off_the_tape_at_clamps(torch_dev, n_steps):
+    """The reverse sweep takes the controller's integrals from the tape only
+    at every 16th step and where an agent is at a clamp.  Agents that start
+    at, near and away from the three clamps, with waypoints and rates that
+    drive them in and out of them: an agent's gradient does not depend on the
+    checkpoint interval, on which agents share its wave, or on the kernel
+    (a swarm small enough for the pipelined one, and 70,016 agents), bit for
+    bit.  Most agents meet a clamp."""
+    torch, dev = torch_dev
+    from paper_2308_12698_amd.sim import Simulator
+    n = 256
+    rng = np.random.default_rng(n_steps)
+    glob = I.globals_f32(ipos_max=0.5, iatt_max=0.05, irate_max=0.1)
+    s = I.hover_state(rng.uniform(0.0, 20.0, (3, n))).astype(np.float64)
+    s[10:13] = rng.normal(0.0, 1.0, (3, n))
+    for rows, top in ((slice(17, 20), 0.5), (slice(20, 23), 0.05), (slice(23, 26), 0.1)):
+        near = rng.uniform(0.97, 1.0, (3, n)) * rng.choice([-1.0, 1.0], (3, n))
+        s[rows] = top * np.where(rng.random((3, n)) < 0.5, near, rng.uniform(-0.5, 0.5, (3, n)))
+    s[17:26] = np.clip(s[17:26], -np.repeat([0.5, 0.05, 0.1], 3)[:, None], np.repeat([0.5, 0.05, 0.1], 3)[:, None])
+    wp = s[0:3] + rng.uniform(-3.0, 3.0, (3, n))
+    gains = np.asarray(I.DEFAULT_GAINS)[:, None] * rng.uniform(0.8, 1.2, (9, n))
+    lam = rng.normal(size=(30, n))
+    shuffle = rng.permutation(n)
+
+    def gradient(K, pick, reps=1):
+        up = lambda a: torch.from_numpy(np.ascontiguousarray(I.f32(np.tile(a[:, pick], (1, reps))))).to(dev)
+        sim = Simulator([I.base_type()], glob, mode=1)
+        x, m = up(s), n * reps
+        w, g = up(wp)[None].contiguous(), up(gains)
+        ckpt = torch.empty((-(-n_steps // K), 40, m), device=dev)
+        sim.step(x, n_steps, 2e-3, gains=g, wp=w, ckpt=ckpt, ckpt_every=K, carry=torch.zeros_like(x[:10]))
+        gx, gg = sim.step_backward(ckpt, K, n_steps, 2e-3, up(lam), gains=g, wp=w)
+        torch.cuda.synchronize()
+        sim.close()
+        both = torch.cat([gx, gg])[:, :n].cpu().numpy()
+        out = np.empty_like(both)
+        out[:, pick] = both
+        return out, x[17:26, :n].cpu().numpy()
+
+    ref, end = gradient(50, np.arange(n))
+    assert np.isfinite(ref).all()
+    limit = I.f32(np.repeat([0.5, 0.05, 0.1], 3))[:, None]
+    if n_steps == 60:
+        assert (np.abs(end) == limit).any(axis=0).mean() > 0.3
+    for K, pick, reps in ((1, np.arange(n), 1), (7, shuffle, 1), (16, np.arange(n), 1), (50, shuffle, 1),
+                          (50, np.arange(n), 274), (7, shuffle, 274)):
+        assert np.array_equal(gradient(K, pick, reps)[0], ref), (K, reps)
