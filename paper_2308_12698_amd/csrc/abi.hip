@@ -281,6 +281,33 @@ potato_status validate_step(const potato_ctx* ctx, const potato_state* st, const
     return POTATO_OK;
 }
 
+/* Launch shape of the fused form where the caller and the autotuner leave it
+ * open.
+ * Steps: a launch loads and stores 80 rows per agent around its steps, which
+ * at 100 steps costs 3 % of a rollout at 5,000 agents (0.984 us per step
+ * against 0.956 with 1,000) and at 1,048,576 (10.13 against 9.83), so a
+ * launch takes up to 1,000; swarms beyond 2^24 agents keep 100, so that no
+ * launch runs much longer than a sixth of a second.
+ * Block: 256 threads.  A launch that groups its agents per block fills more
+ * of its groups with wider blocks, but a block of 1,024 puts 16 waves on one
+ * compute unit, so the widest block is taken that still gives every compute
+ * unit one: mixed kinds, us per step with 256 / 512 / 1,024: 2.22 / 2.47 /
+ * 3.30 at 65,536 agents, 3.01 / 2.59 / 3.45 at 131,072, 4.69 / 3.78 / 3.49 at
+ * 251,904, 12.8 / 11.5 / 10.4 at 1,048,576.  With one kind (budgets only)
+ * the groups' gaps cost less: 1.12 / 1.57 / 2.75 at 65,536, 1.66 / 1.65 /
+ * 2.73 at 131,072, 2.76 / 2.81 / 2.81 at 251,904, 5.50 / 5.33 / 5.33 at
+ * 524,288. */
+Tuned default_shape(const Variant& v, const StepArgs& a, bool kinds) {
+    Tuned t{256, a.n <= (int64_t(1) << 24) ? 1000 : 100, 0};
+    if (rollout_grouped(v, a)) {
+        if (kinds)
+            t.block = a.n <= 65536 ? 256 : a.n <= 131072 ? 512 : 1024;
+        else
+            t.block = a.n <= 262144 ? 256 : 1024;
+    }
+    return t;
+}
+
 Plan make_plan(potato_ctx* ctx, const potato_state* st, const potato_params* pp, const potato_cmds* cm,
                float dt, int64_t n, float* ckpt, int32_t ckpt_every) {
     Plan P{};
@@ -309,11 +336,7 @@ Plan make_plan(potato_ctx* ctx, const potato_state* st, const potato_params* pp,
     a.n_groups = P.v.het && !P.v.perm ? ctx->n_groups : 0;
 
     const potato_options& o = ctx->opts;
-    /* agents grouped per block: the widest blocks measured best (mixed
-     * kinds at 1M agents, 512 threads: 9.3e10 agent-steps/s against 8.2e10
-     * with 256 and 7.0e10 with 128): more agents per block fill the groups
-     * of rare classes, and more waves share out the groups more evenly */
-    Tuned t{rollout_grouped(P.v, P.a) ? 1024 : 256, 100, 0};
+    Tuned t = default_shape(P.v, P.a, ctx->kinds);
     auto it = ctx->tuned.find(TuneKey{P.v.mode, P.v.het, P.v.gains, P.v.perm, P.v.ckpt});
     if (it != ctx->tuned.end()) t = it->second;
     if (o.form == POTATO_FORM_PLAIN) {
