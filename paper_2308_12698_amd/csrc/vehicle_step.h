@@ -33,13 +33,23 @@
  * trigonometric functions of the angles are evaluated once per step, at
  * the step-start state, and carried to each RK4 stage's angles by the
  * angle-sum formulas with short series for the stage's small offset
- * (sincos_shift, tan_shift); divisions by
+ * (veh_trig_near, veh_trig_far); the course error is the angle of one product of complex numbers
+ * (one arctangent instead of two or three); divisions by
  * the time constants, the wheelbase and g rho are multiplications by
  * reciprocals precomputed per type; the car's steering feed-forward is a
  * per-type constant.  Every integrated row keeps a rounding carry
  * (Fast2Sum), as the quadrotor's position and velocity do.  Contraction is
  * off and fused multiply-adds are placed explicitly, so the plain and the
  * fused launches give the same bits.
+ *
+ * Bound by instruction issue, like the quadrotor's step.  The library's
+ * sine, tangent, arctangent and division (large-argument branches, full
+ * special-case sequences) made a step of several hundred instructions more
+ * than the functions written here, which keep the library's as the rare
+ * branch: a car's step is now about 325 vector instructions and an
+ * aircraft's 430, in straight lines (a quadrotor's 525).  Mixed kinds in
+ * the type order, us per step before and after: 2.53 and 1.71 at 3,000
+ * agents, 6.11 and 5.70 at 524,288, 10.25 and 9.28 at 1,048,576.
  */
 #pragma once
 
@@ -47,12 +57,71 @@
 
 namespace potato {
 
+constexpr float kPi = 3.14159265358979323846f;
 constexpr float kTwoPi = 6.28318530717958647692f;
 constexpr float kInvTwoPi = 0.159154943091895335769f;
 
 /* Angle a moved into [-pi, pi] by whole turns. */
 __device__ __forceinline__ float wrap_pi(float a) {
     return POTATO_FMA(-kTwoPi, rintf(a * kInvTwoPi), a);
+}
+
+/* n / d: reciprocal, quotient and one correction by its exact residual;
+ * v_div_fixup gives zeros, infinities and NaN the results of the division.
+ * Five instructions where the full sequence takes eleven. */
+__device__ __forceinline__ float quotient(float n, float d) {
+#pragma clang fp contract(off)
+    const float r = __builtin_amdgcn_rcpf(d);
+    const float q = n * r;
+    return __builtin_amdgcn_div_fixupf(POTATO_FMA(POTATO_FMA(-d, q, n), r, q), d, n);
+}
+
+/* sin and cos of a, |a| <= kTrigMax: a - k pi/2 for the nearest k with pi/2
+ * in three parts (Cody and Waite, Software Manual for the Elementary
+ * Functions, 1980; each step a fused multiply-add, the first one exact),
+ * then the Taylor polynomials of the remainder, at most pi/4 and a little
+ * (through r^9 and r^10: truncation below 3e-9 and 2e-9). */
+constexpr float kTrigMax = 1e5f;
+__device__ __forceinline__ void sincos_near(float a, float& s, float& c) {
+#pragma clang fp contract(off)
+    const float k = rintf(a * 0.6366197466850281f);
+    float r = POTATO_FMA(-k, 1.5707963705062866f, a);
+    r = POTATO_FMA(-k, -4.371138828673793e-08f, r);
+    r = POTATO_FMA(-k, -1.7151245100058819e-15f, r);
+    const float r2 = r * r;
+    const float ps = POTATO_FMA(r2, POTATO_FMA(r2, POTATO_FMA(r2, 1.0f / 362880.0f, -1.0f / 5040.0f), 1.0f / 120.0f), -1.0f / 6.0f);
+    const float pc = POTATO_FMA(r2, POTATO_FMA(r2, POTATO_FMA(r2, POTATO_FMA(r2, -1.0f / 3628800.0f, 1.0f / 40320.0f), -1.0f / 720.0f), 1.0f / 24.0f), -0.5f);
+    const float sr = POTATO_FMA(r * r2, ps, r), cr = POTATO_FMA(r2, pc, 1.0f);
+    const uint32_t q = (uint32_t)(int32_t)k;
+    const bool odd = (q & 1u) != 0;
+    const uint32_t ss = (q & 2u) << 30, cs = ((q + 1u) & 2u) << 30;
+    s = __uint_as_float(__float_as_uint(odd ? cr : sr) ^ ss);
+    c = __uint_as_float(__float_as_uint(odd ? sr : cr) ^ cs);
+}
+
+/* Angle of the vector (x, y), as atan2(y, x), for a vector other than
+ * (0, 0): the smaller coordinate over the larger, moved by pi/4 where it
+ * exceeds tan(pi/8) (both within one division), and the arctangent's series
+ * through r^17 (truncation below 3e-9 for |r| <= tan(pi/8)). */
+__device__ __forceinline__ float vector_angle(float y, float x) {
+#pragma clang fp contract(off)
+    const float ax = fabsf(x), ay = fabsf(y);
+    const float mx = fmaxf(ax, ay), mn = fminf(ax, ay);
+    const bool big = mn > 0.41421356f * mx;
+    const float r = quotient(big ? mn - mx : mn, big ? mn + mx : mx);
+    const float r2 = r * r;
+    float p = POTATO_FMA(r2, 1.0f / 17.0f, -1.0f / 15.0f);
+    p = POTATO_FMA(r2, p, 1.0f / 13.0f);
+    p = POTATO_FMA(r2, p, -1.0f / 11.0f);
+    p = POTATO_FMA(r2, p, 1.0f / 9.0f);
+    p = POTATO_FMA(r2, p, -1.0f / 7.0f);
+    p = POTATO_FMA(r2, p, 1.0f / 5.0f);
+    p = POTATO_FMA(r2, p, -1.0f / 3.0f);
+    const float a0 = POTATO_FMA(r * r2, p, r);
+    const float a1 = big ? a0 + 0.25f * kPi : a0;
+    const float a2 = ay > ax ? 0.5f * kPi - a1 : a1;
+    const float a3 = x < 0.0f ? kPi - a2 : a2;
+    return copysignf(a3, y);
 }
 
 /* Rows a kind integrates (the car has no altitude or flight-path dynamics). */
@@ -67,53 +136,78 @@ struct VehTrig {
     float sh, ch, ta, sg, cg;
 };
 
+/* Angles beyond kTrigMax (and NaN) take the library's functions, which
+ * reduce any argument. */
 template <int KIND>
 __device__ __forceinline__ void veh_trig(const float x[7], VehTrig& T) {
-    sincosf(x[4], &T.sh, &T.ch);
-    T.ta = tanf(x[5]);
-    if (KIND == KIND_WING) sincosf(x[6], &T.sg, &T.cg);
-}
-
-/* sin and cos of a0 + d from those of a0, for a stage's small angle offset
- * d: the angle-sum formulas with sin d and cos d from their Taylor series
- * (through d^7 and d^8: remainders below 6e-11 for |d| <= 0.3, past FP32
- * rounding);
- * larger offsets (very long time steps) call sincosf. */
-__device__ __forceinline__ void sincos_shift(float a0, float s0, float c0, float d, float& s, float& c) {
-#pragma clang fp contract(off)
-    if (fabsf(d) <= 0.3f) {
-        const float d2 = d * d;
-        const float sd = d * POTATO_FMA(-d2 * (1.0f / 6.0f), POTATO_FMA(-d2, 1.0f / 20.0f * POTATO_FMA(-d2, 1.0f / 42.0f, 1.0f), 1.0f), 1.0f);
-        const float cm = d2 * 0.5f * POTATO_FMA(-d2, 1.0f / 12.0f * POTATO_FMA(-d2, 1.0f / 30.0f * POTATO_FMA(-d2, 1.0f / 56.0f, 1.0f), 1.0f), 1.0f);
-        /* cos d = 1 - cm */
-        s = POTATO_FMA(c0, sd, POTATO_FMA(-s0, cm, s0));
-        c = POTATO_FMA(-s0, sd, POTATO_FMA(-c0, cm, c0));
+    const float far = KIND == KIND_WING ? fmaxf(fmaxf(fabsf(x[4]), fabsf(x[5])), fabsf(x[6]))
+                                        : fmaxf(fabsf(x[4]), fabsf(x[5]));
+    const bool nan = !(x[4] == x[4]) || !(x[5] == x[5]) || (KIND == KIND_WING && !(x[6] == x[6]));
+    if (far <= kTrigMax && !nan) {
+        float sa, ca;
+        sincos_near(x[4], T.sh, T.ch);
+        sincos_near(x[5], sa, ca);
+        T.ta = quotient(sa, ca);
+        if (KIND == KIND_WING) sincos_near(x[6], T.sg, T.cg);
     } else {
-        sincosf(a0 + d, &s, &c);
+        sincosf(x[4], &T.sh, &T.ch);
+        T.ta = tanf(x[5]);
+        if (KIND == KIND_WING) sincosf(x[6], &T.sg, &T.cg);
     }
 }
 
-/* tan(a0 + d) from t0 = tan(a0): (t0 + tan d) / (1 - t0 tan d), tan d from
- * its series through d^7 (the remainder is below 3e-10 of tan d for
- * |d| <= 0.1); larger offsets, or a denominator that would cancel, call
- * tanf. */
-__device__ __forceinline__ float tan_shift(float a0, float t0, float d) {
+/* The angles' functions at a stage state x0 + offsets d (h k of the previous
+ * stage's rates) from those at x0: sin and cos by the angle-sum formulas,
+ * tan(a0 + d) as (t0 + tan d) / (1 - t0 tan d), with sin d, cos d - 1 and
+ * tan d from their Taylor series.  NEAR: offsets of at most 0.02 rad, as
+ * every ordinary time step gives, and series through d^3, d^4 and d^5
+ * (truncation below 2e-9 of sin d and tan d, 1e-13 of cos d); false when an
+ * offset is larger or NaN. */
+template <int KIND>
+__device__ __forceinline__ bool veh_trig_near(const VehTrig& T0, float d4, float d5, float d6, VehTrig& T) {
 #pragma clang fp contract(off)
-    const float d2 = d * d;
-    const float td = d * POTATO_FMA(d2 * (1.0f / 3.0f), POTATO_FMA(d2, 0.4f * POTATO_FMA(d2, 17.0f / 42.0f, 1.0f), 1.0f), 1.0f);
-    const float den = POTATO_FMA(-t0, td, 1.0f);
-    if (fabsf(d) <= 0.1f && den >= 0.5f) return (t0 + td) / den;
-    return tanf(a0 + d);
+    auto shift = [](float s0, float c0, float d, float& s, float& c) {
+        const float d2 = d * d;
+        const float sd = POTATO_FMA(d * d2, -1.0f / 6.0f, d);
+        const float cm = d2 * POTATO_FMA(d2, 1.0f / 24.0f, -0.5f);
+        s = POTATO_FMA(c0, sd, POTATO_FMA(s0, cm, s0));
+        c = POTATO_FMA(-s0, sd, POTATO_FMA(c0, cm, c0));
+    };
+    shift(T0.sh, T0.ch, d4, T.sh, T.ch);
+    if (KIND == KIND_WING) shift(T0.sg, T0.cg, d6, T.sg, T.cg);
+    const float q2 = d5 * d5;
+    const float td = d5 * POTATO_FMA(q2, POTATO_FMA(q2, 2.0f / 15.0f, 1.0f / 3.0f), 1.0f);
+    const float den = POTATO_FMA(-T0.ta, td, 1.0f);
+    T.ta = quotient(T0.ta + td, den);
+    const float far = KIND == KIND_WING ? fabsf(d4) + fabsf(d6) : fabsf(d4);
+    return far + fabsf(d5) <= 0.02f && den >= 0.5f;
 }
 
-/* The angles' functions at a stage state x0 + offsets (h k of the previous
- * stage's rates) from those at x0. */
+/* The same for any offset: longer series up to 0.3 rad (0.1 of the tangent),
+ * the library's functions of the new angles beyond (very long time steps). */
 template <int KIND>
-__device__ __forceinline__ void veh_trig_shift(const float x0[7], const VehTrig& T0, float h, const float k[7],
-                                               VehTrig& T) {
-    sincos_shift(x0[4], T0.sh, T0.ch, h * k[4], T.sh, T.ch);
-    T.ta = tan_shift(x0[5], T0.ta, h * k[5]);
-    if (KIND == KIND_WING) sincos_shift(x0[6], T0.sg, T0.cg, h * k[6], T.sg, T.cg);
+__device__ __forceinline__ void veh_trig_far(const float x0[7], const VehTrig& T0, float d4, float d5, float d6,
+                                             VehTrig& T) {
+#pragma clang fp contract(off)
+    auto shift = [](float s0, float c0, float d, float& s, float& c) {
+        const float d2 = d * d;
+        const float sd = POTATO_FMA(d * d2, POTATO_FMA(d2, POTATO_FMA(d2, -1.0f / 5040.0f, 1.0f / 120.0f), -1.0f / 6.0f), d);
+        const float cm = d2 * POTATO_FMA(d2, POTATO_FMA(d2, POTATO_FMA(d2, 1.0f / 40320.0f, -1.0f / 720.0f), 1.0f / 24.0f), -0.5f);
+        s = POTATO_FMA(c0, sd, POTATO_FMA(s0, cm, s0));
+        c = POTATO_FMA(-s0, sd, POTATO_FMA(c0, cm, c0));
+    };
+    const float q2 = d5 * d5;
+    const float td = d5 * POTATO_FMA(q2, POTATO_FMA(q2, POTATO_FMA(q2, 17.0f / 315.0f, 2.0f / 15.0f), 1.0f / 3.0f), 1.0f);
+    const float den = POTATO_FMA(-T0.ta, td, 1.0f);
+    if (fabsf(d4) <= 0.3f && fabsf(d5) <= 0.1f && den >= 0.5f && (KIND != KIND_WING || fabsf(d6) <= 0.3f)) {
+        shift(T0.sh, T0.ch, d4, T.sh, T.ch);
+        T.ta = quotient(T0.ta + td, den);
+        if (KIND == KIND_WING) shift(T0.sg, T0.cg, d6, T.sg, T.cg);
+    } else {
+        sincosf(x0[4] + d4, &T.sh, &T.ch);
+        T.ta = tanf(x0[5] + d5);
+        if (KIND == KIND_WING) sincosf(x0[6] + d6, &T.sg, &T.cg);
+    }
 }
 
 /* Rates of rows 0-6 at state x (its angles' functions in T) with inputs u
@@ -142,7 +236,7 @@ __device__ __forceinline__ void veh_rates(const VehConst& c, const float x[7], c
         dx[1] = vh * T.sh;
         dx[2] = x[3] * T.sg;
         dx[3] = (u[0] - x[3]) * c.inv_tau[0];
-        dx[4] = (c.g * T.ta) / x[3];
+        dx[4] = quotient(c.g * T.ta, x[3]);
         dx[5] = (u[1] - x[5]) * c.inv_tau[1];
         dx[6] = (u[2] - x[6]) * c.inv_tau[2];
     }
@@ -155,19 +249,40 @@ __device__ __forceinline__ void veh_guidance(const VehConst& c, const float x[7]
                                              float u[3]) {
 #pragma clang fp contract(off)
     const float ex = x[0] - wp[0], ey = x[1] - wp[1];
-    const float d = sqrtf(POTATO_FMA(ey, ey, ex * ex));
-    const float chi_d = POTATO_FMA(c.lam, atanf(c.k_orb_rho * (d - c.rho)), atan2f(ey, ex) + c.lam_half_pi);
+    const float u0 = c.k_orb_rho * (sqrt_fast(POTATO_FMA(ey, ey, ex * ex)) - c.rho);
+    /* course error: course command minus the car's course (its yaw plus the
+     * side-slip angle) or the aircraft's, in [-pi, pi]: the angle of the
+     * product of the complex numbers whose angles add up to it, ex + i ey,
+     * i lam, 1 + i lam u0, cos - i sin of the heading and 1 - i tan(beta) */
+    const float lu = c.lam * u0;
+    const float ar = -c.lam * ey, ai = c.lam * ex;
+    const float br = POTATO_FMA(-ai, lu, ar), bi = POTATO_FMA(ar, lu, ai);
+    float cr = POTATO_FMA(bi, T.sh, br * T.ch), ci = POTATO_FMA(-br, T.sh, bi * T.ch);
     if (KIND == KIND_CAR) {
-        /* the car's course is its yaw plus the side-slip angle */
-        const float beta = atanf(c.lr_L * T.ta);
-        const float e = wrap_pi(chi_d - (x[4] + beta));
+        const float tb = c.lr_L * T.ta;
+        const float dr = POTATO_FMA(ci, tb, cr), di = POTATO_FMA(-cr, tb, ci);
+        cr = dr;
+        ci = di;
+    }
+    const float size = fabsf(cr) + fabsf(ci);
+    float e;
+    if (fabsf(c.lam) == 1.0f && size >= 1e-30f && size <= 3e38f) {
+        e = vector_angle(ci, cr);
+    } else {
+        /* another lambda, the orbit's centre, infinities: angle by angle
+         * (the heading without its whole turns, whose rounding would be that
+         * of the difference) */
+        const float chi_d = POTATO_FMA(c.lam, atanf(u0), atan2f(ey, ex) + c.lam_half_pi);
+        const float course = atan2f(T.sh, T.ch);
+        e = wrap_pi(chi_d - (KIND == KIND_CAR ? course + atanf(c.lr_L * T.ta) : course));
+    }
+    if (KIND == KIND_CAR) {
         u[0] = clampf_(POTATO_FMA(c.k_hold, c.cruise - x[3], c.cd_m * x[3]), -c.lim[0], c.lim[0]);
         u[1] = clampf_(POTATO_FMA(c.k_head, e, c.ff), -c.lim[1], c.lim[1]);
         u[2] = 0.0f;
     } else {
         /* bank that holds the circle: tan(phi) = V^2 / (g rho) */
-        const float e = wrap_pi(chi_d - x[4]);
-        const float ff = c.lam * atanf((x[3] * x[3]) * c.inv_g_rho);
+        const float ff = c.lam * vector_angle((x[3] * x[3]) * c.inv_g_rho, 1.0f);
         u[0] = c.cruise;
         u[1] = clampf_(POTATO_FMA(c.k_head, e, ff), -c.lim[1], c.lim[1]);
         u[2] = clampf_(c.k_hold * (wp[2] - x[2]), -c.lim[2], c.lim[2]);
@@ -183,34 +298,47 @@ template <int KIND, bool CARRY>
 __device__ __forceinline__ void veh_rk4(const VehConst& c, const Limits& L, float x[7], const VehTrig& T, float lo[7],
                                         const float u[3]) {
 #pragma clang fp contract(off)
-    float k[7], acc[7], xs[7];
+    float k1[7], k[7], acc[7], xs[7];
     VehTrig Ts;
-    veh_rates<KIND>(c, x, T, u, k);
+    veh_rates<KIND>(c, x, T, u, k1);
+    auto start = [&]() {
 #pragma unroll
-    for (int i = 0; i < 7; ++i) {
-        acc[i] = k[i];
-        xs[i] = veh_row<KIND>(i) ? POTATO_FMA(L.half_dt, k[i], x[i]) : x[i];
-    }
-    veh_trig_shift<KIND>(x, T, L.half_dt, k, Ts);
-    veh_rates<KIND>(c, xs, Ts, u, k);
+        for (int i = 0; i < 7; ++i) acc[i] = k[i] = k1[i];
+    };
+    auto advance = [&](float h) {
 #pragma unroll
-    for (int i = 0; i < 7; ++i) {
-        acc[i] = POTATO_FMA(2.0f, k[i], acc[i]);
-        xs[i] = veh_row<KIND>(i) ? POTATO_FMA(L.half_dt, k[i], x[i]) : x[i];
-    }
-    veh_trig_shift<KIND>(x, T, L.half_dt, k, Ts);
-    veh_rates<KIND>(c, xs, Ts, u, k);
+        for (int i = 0; i < 7; ++i) xs[i] = veh_row<KIND>(i) ? POTATO_FMA(h, k[i], x[i]) : x[i];
+    };
+    auto add = [&](float weight) {
+        veh_rates<KIND>(c, xs, Ts, u, k);
 #pragma unroll
-    for (int i = 0; i < 7; ++i) {
-        acc[i] = POTATO_FMA(2.0f, k[i], acc[i]);
-        xs[i] = veh_row<KIND>(i) ? POTATO_FMA(L.dt, k[i], x[i]) : x[i];
+        for (int i = 0; i < 7; ++i) acc[i] = POTATO_FMA(weight, k[i], acc[i]);
+    };
+    /* stages 2-4 straight through; an agent with an offset too large for
+     * them takes the three again, one copy of their code */
+    bool near = true;
+    start();
+#pragma unroll
+    for (int st = 0; st < 3; ++st) {
+        const float h = st < 2 ? L.half_dt : L.dt;
+        advance(h);
+        near = veh_trig_near<KIND>(T, h * k[4], h * k[5], h * k[6], Ts) && near;
+        add(st < 2 ? 2.0f : 1.0f);
     }
-    veh_trig_shift<KIND>(x, T, L.dt, k, Ts);
-    veh_rates<KIND>(c, xs, Ts, u, k);
+    if (!near) {
+        start();
+#pragma unroll 1
+        for (int st = 0; st < 3; ++st) {
+            const float h = st < 2 ? L.half_dt : L.dt;
+            advance(h);
+            veh_trig_far<KIND>(x, T, h * k[4], h * k[5], h * k[6], Ts);
+            add(st < 2 ? 2.0f : 1.0f);
+        }
+    }
 #pragma unroll
     for (int i = 0; i < 7; ++i) {
         if (!veh_row<KIND>(i)) continue;
-        add_carry<CARRY>(x[i], lo[i], L.dt6 * (acc[i] + k[i]));
+        add_carry<CARRY>(x[i], lo[i], L.dt6 * acc[i]);
     }
 }
 

@@ -280,3 +280,38 @@ def test_collision_radius_of_vehicle_types(oracle, torch_dev):
     ref, ref_died = oracle.detect_collisions(state, [t["radius"] for t in sw.types], np.ones(sw.n, np.uint8),
                                              type_idx=sw.type_idx)
     assert np.array_equal(got, ref) and int(died.item()) == ref_died > 0
+
+
+@pytest.mark.parametrize("dt,steps,turns", [(1e-3, 50, 0.0), (0.05, 40, 0.0), (0.1, 40, 0.0), (0.25, 20, 0.0),
+                                            (1e-3, 1, 1e5), (1e-3, 1, 1e6)])
+def test_vehicle_angle_ranges(oracle, torch_dev, dt, steps, turns):
+    """The ranges of the vehicles' trigonometry: stage offsets within the
+    short series (dt = 1 ms), the longer ones and beyond (dt up to 0.25 s,
+    steering far from its command), headings up to and past the reduction's
+    range (one step, so that the heading's own rounding does not enter),
+    orbit directions other than +-1, agents at the very centre of their
+    orbit and on its axes."""
+    r = np.random.default_rng(int(steps + 1000 * dt))
+    types = [I.car_type(lam=1.0), I.car_type(lam=-1.0), I.car_type(lam=0.5), I.wing_type(lam=1.0),
+             I.wing_type(lam=-1.0), I.wing_type(lam=-0.75)]
+    n = 1200
+    labels = r.integers(0, len(types), n).astype(np.uint8)
+    s = np.zeros((30, n))
+    wp = np.zeros((1, 3, n))
+    for t, ty in enumerate(types):
+        idx = np.where(labels == t)[0]
+        centre = np.stack([r.uniform(0, 100, idx.size), r.uniform(0, 100, idx.size),
+                           np.zeros(idx.size) if ty["kind"] == 1 else r.uniform(40, 60, idx.size)])
+        s[0:7, idx] = I.orbit_starts(r, ty, centre)
+        s[5, idx] = r.uniform(-0.5, 0.5, idx.size)
+        wp[0][:, idx] = centre
+    special = np.arange(0, n, 10)
+    s[0:2, special] = np.round(s[0:2, special])
+    wp[0, 0:2, special] = s[0:2, special].T                 # at the centre
+    wp[0, 0, special[::3]] += 30.0                           # on an axis, behind and ahead
+    wp[0, 1, special[1::3]] -= 30.0
+    s[4] += r.choice([-1.0, 1.0], n) * r.uniform(0.5, 1.0, n) * turns
+    sw = I.Swarm("angles", 1, dt, steps, I.f32(s), types, I.globals_f32(), type_idx=labels, wp=I.f32(wp))
+    got = gpu_run(torch_dev, sw, steps)
+    assert_kinds_parity(got, oracle_run(oracle, sw, steps), sw)
+    assert np.array_equal(got, gpu_run(torch_dev, sw, steps, form="plain"))
