@@ -124,6 +124,20 @@ const void* rollout_kernel(const Variant& v, const StepArgs& a);
 constexpr int64_t kLaneAgents = POTATO_LANE_AGENTS;
 bool rollout_lanes(const Variant& v, const StepArgs& a);
 
+/* Closed-loop swarms of more than kSpacedAgents (more than two waves per
+ * SIMD) of one quadrotor type, or with cars or aircraft, take the spaced
+ * rsq and sqrt of quad_step.h: per step 9.87 -> 9.25 us at 1,048,576
+ * quadrotors, 5.16 -> 4.91 at 524,288, 2.75 -> 2.69 at 262,144, 2.33 -> 2.28
+ * at 140,000 (but 1.53 -> 1.58 at 131,072); mixed kinds 2.53 -> 2.37 ms per
+ * call at 500,000, equal at 1M and at 262,144.  Quadrotors of several types
+ * lose by it (2.63 -> 2.85 ms per call at 250,000: their kernel's registers
+ * spill) and keep the plain instructions. */
+#ifndef POTATO_SPACED_AGENTS
+#define POTATO_SPACED_AGENTS 131072
+#endif
+constexpr int64_t kSpacedAgents = POTATO_SPACED_AGENTS;
+bool rollout_spaced(const Variant& v, const StepArgs& a);
+
 /* Adjoint: kernel pointer (occupancy queries) and launch of grid_blocks
  * blocks.  One agent per thread, kAdjBlock threads per block, tape
  * [K][grid threads / 64][kTapeRows][64]; or, with `pipe`, kAdjPipeBlock

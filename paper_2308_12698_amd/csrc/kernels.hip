@@ -23,7 +23,8 @@
  *         in the caller's carry rows (without: uncompensated updates);
  *   KINDS the type table also holds cars and fixed-wing aircraft: a lane
  *         whose type is one of those runs its own step (vehicle_step.h)
- *         over rows 0-6 instead of the quadrotor's.
+ *         over rows 0-6 instead of the quadrotor's;
+ *   SPACED rsq and sqrt between s_nop (closed loop of many agents).
  * k_rollout_lanes: the same for small swarms of quadrotors, four lanes per
  * agent.
  * k_adjoint: reverse sweep of a checkpointed rollout, one agent per lane,
@@ -288,7 +289,7 @@ __device__ __forceinline__ void group_agents(const StepArgs& A, const TypeConst*
      * thread reaches once it is done with this call's */
 }
 
-template <int MODE, bool HET, bool GAINS, bool CKPT, bool PERM, bool CARRY, bool KINDS>
+template <int MODE, bool HET, bool GAINS, bool CKPT, bool PERM, bool CARRY, bool KINDS, bool SPACED>
 __global__ void __launch_bounds__(1024) POTATO_ROLLOUT_ATTR k_rollout(const StepArgs A) {
     static_assert(!(KINDS && CKPT), "checkpoints (the adjoint) cover quadrotors only");
     static_assert(CARRY || !CKPT, "checkpoints hold the carries");
@@ -441,9 +442,9 @@ __global__ void __launch_bounds__(1024) POTATO_ROLLOUT_ATTR k_rollout(const Step
                         wp[k] = elem(uniform(A.wp + ((int64_t)epoch * 3 + k) * A.cmd_ld), bo);
                     next_epoch_step = epoch < A.n_epochs - 1 ? next_epoch_step + A.resample : INT64_MAX;
                 }
-                controller<CARRY>(c, lim, g, a, wp, dc);
+                controller<CARRY, false, SPACED>(c, lim, g, a, wp, dc);
             }
-            rk4_step<CARRY>(c, lim, a, dc);
+            rk4_step<CARRY, SPACED>(c, lim, a, dc);
         }
 
 #pragma unroll
@@ -866,17 +867,26 @@ __global__ void __launch_bounds__(256) k_count_nonfinite(const float* rows, int6
         atomicAdd(count, (unsigned long long)__popcll(mask));
 }
 
-template <int MODE, bool HET, bool GAINS, bool CKPT, bool PERM, bool CARRY, bool KINDS>
+template <int MODE, bool HET, bool GAINS, bool CKPT, bool PERM, bool CARRY, bool KINDS, bool SPACED = false>
 const void* kfn() {
-    return reinterpret_cast<const void*>(&k_rollout<MODE, HET, GAINS, CKPT, PERM, CARRY, KINDS>);
+    return reinterpret_cast<const void*>(&k_rollout<MODE, HET, GAINS, CKPT, PERM, CARRY, KINDS, SPACED>);
 }
 
 /* Checkpoints are only written with carries and only for quadrotor tables
  * (the host refuses the other combinations), so a variant with ckpt maps to
  * the checkpointing kernel, which reads and writes the carries. */
 template <int MODE, bool HET, bool GAINS, bool PERM>
-const void* kfn_carry(const Variant& v) {
+const void* kfn_carry(const Variant& v, const StepArgs& a) {
     if (MODE == 1 && v.ckpt) return kfn<MODE, HET, GAINS, MODE == 1, PERM, true, false>();
+    if (rollout_spaced(v, a)) {
+        constexpr bool S = MODE == 1;   /* open loop never is */
+        if (v.kinds)
+            return v.carry ? kfn<MODE, HET, GAINS, false, PERM, true, true, S>()
+                           : kfn<MODE, HET, GAINS, false, PERM, false, true, S>();
+        constexpr bool H = S && !HET;   /* nor are quadrotors of several types */
+        return v.carry ? kfn<MODE, HET, GAINS, false, PERM, true, false, H>()
+                       : kfn<MODE, HET, GAINS, false, PERM, false, false, H>();
+    }
     if (v.kinds)
         return v.carry ? kfn<MODE, HET, GAINS, false, PERM, true, true>()
                        : kfn<MODE, HET, GAINS, false, PERM, false, true>();
@@ -887,6 +897,11 @@ const void* kfn_carry(const Variant& v) {
 }  // namespace
 
 bool rollout_lanes(const Variant& v, const StepArgs& a) { return !v.kinds && a.n <= kLaneAgents; }
+
+bool rollout_spaced(const Variant& v, const StepArgs& a) {
+    return v.mode == 1 && !v.ckpt && (v.kinds || !v.het) && a.n > kSpacedAgents;
+}
+
 
 const void* rollout_kernel(const Variant& v, const StepArgs& a) {
     if (rollout_lanes(v, a)) {
@@ -899,10 +914,10 @@ const void* rollout_kernel(const Variant& v, const StepArgs& a) {
     }
     /* open loop: gains and checkpoints do not apply */
     if (v.mode == 0) {
-        if (!v.het) return kfn_carry<0, false, false, false>(v);
-        return v.perm ? kfn_carry<0, true, false, true>(v) : kfn_carry<0, true, false, false>(v);
+        if (!v.het) return kfn_carry<0, false, false, false>(v, a);
+        return v.perm ? kfn_carry<0, true, false, true>(v, a) : kfn_carry<0, true, false, false>(v, a);
     }
-#define POTATO_PICK(H, P) return v.gains ? kfn_carry<1, H, true, P>(v) : kfn_carry<1, H, false, P>(v);
+#define POTATO_PICK(H, P) return v.gains ? kfn_carry<1, H, true, P>(v, a) : kfn_carry<1, H, false, P>(v, a);
     if (!v.het) { POTATO_PICK(false, false) }
     if (v.perm) { POTATO_PICK(true, true) }
     POTATO_PICK(true, false)

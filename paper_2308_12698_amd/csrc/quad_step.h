@@ -205,8 +205,28 @@ __device__ __forceinline__ float clampf_(float x, float lo, float hi) {
     return __builtin_amdgcn_fmed3f(x, lo, hi);
 }
 
-__device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ float sqrt_fast(float x) { return __builtin_amdgcn_sqrtf(x); }
+/* v_rsq_f32 and v_sqrt_f32.  SPACED: with an s_nop before and after, the
+ * same instruction and bits.  A wave's transcendental instruction costs the
+ * other waves of its SIMD their turns for some 100 clocks: a stream with one
+ * rsq in 64 instructions issues one per 3.8 clocks instead of one per 2.1,
+ * and with the two s_nop one per 2.5.  The step has 8 of them in 520.  Worth
+ * it from three waves per SIMD on (rollout_spaced); the waits of one or two
+ * waves are not filled by others (0.94 -> 1.07 us per step at 65,536
+ * agents). */
+template <bool SPACED = false>
+__device__ __forceinline__ float rsq(float x) {
+    if (!SPACED) return __builtin_amdgcn_rsqf(x);
+    float r;
+    asm("s_nop 1\n\tv_rsq_f32 %0, %1\n\ts_nop 1" : "=v"(r) : "v"(x));
+    return r;
+}
+template <bool SPACED = false>
+__device__ __forceinline__ float sqrt_fast(float x) {
+    if (!SPACED) return __builtin_amdgcn_sqrtf(x);
+    float r;
+    asm("s_nop 1\n\tv_sqrt_f32 %0, %1\n\ts_nop 1" : "=v"(r) : "v"(x));
+    return r;
+}
 
 /* Body z axis in the inertial frame: third column of R(q), unit-norm form
  * (eq. qd2 with thrust along body z). */
@@ -273,7 +293,7 @@ __device__ __forceinline__ void derivative(const TypeConst& c, const float v[3],
  * integral keeps its rounding carry in a.ip_lo.  BITS: the branch
  * decisions go to *bits (kBit*; comparisons only, the arithmetic is the
  * same). */
-template <bool CARRY = true, bool BITS = false>
+template <bool CARRY = true, bool BITS = false, bool SPACED = false>
 __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, const Gains& k,
                                            Agent& a, const float wp[3], float dc[4],
                                            uint32_t* bits = nullptr) {
@@ -281,7 +301,7 @@ __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, 
     /* position loop: error saturated to radius r_sat */
     float e[3] = {wp[0] - a.p[0], wp[1] - a.p[1], wp[2] - a.p[2]};
     const float n2 = POTATO_FMA(e[2], e[2], POTATO_FMA(e[1], e[1], e[0] * e[0]));
-    const float sc = n2 > L.r_sat2 ? L.r_sat * rsq(n2) : 1.0f;
+    const float sc = n2 > L.r_sat2 ? L.r_sat * rsq<SPACED>(n2) : 1.0f;
     uint32_t b = 0u;
     if (BITS) push_bit(b, n2 > L.r_sat2);
     float acc[3];
@@ -310,10 +330,10 @@ __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, 
 
     /* desired attitude: shortest rotation of z onto the thrust direction,
      * q_des ~ (1 + n_z, -n_y, n_x, 0), whose squared norm is 2 (1 + n_z) */
-    const float ra = rsq(POTATO_FMA(acc[2], acc[2], POTATO_FMA(acc[1], acc[1], acc[0] * acc[0])));
+    const float ra = rsq<SPACED>(POTATO_FMA(acc[2], acc[2], POTATO_FMA(acc[1], acc[1], acc[0] * acc[0])));
     const float nx = acc[0] * ra, ny = acc[1] * ra, nz = acc[2] * ra;
     const float qr0 = 1.0f + nz;
-    const float rq = rsq(qr0 + qr0);
+    const float rq = rsq<SPACED>(qr0 + qr0);
     const float qd0 = qr0 * rq, qd1 = -(ny * rq), qd2 = nx * rq;
 
     /* attitude loop on conj(q) o q_des (short arc) */
@@ -355,14 +375,14 @@ __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, 
     for (int i = 0; i < 4; ++i) {
         const float fi = clampf_(f[i], 0.0f, c.f_max);
         if (BITS) push_bit(b, f[i] > 0.0f && f[i] <= c.f_max);
-        dc[i] = sqrt_fast(fi * c.inv_kf) - c.w_ref;
+        dc[i] = sqrt_fast<SPACED>(fi * c.inv_kf) - c.w_ref;
     }
     if (BITS) *bits = b;
 }
 
 /* Classical RK4 with the command held, then quaternion renormalisation.
  * CARRY: p, v and J keep their rounding carries in a.p_lo, a.v_lo, a.J_lo. */
-template <bool CARRY = true>
+template <bool CARRY = true, bool SPACED = false>
 __device__ __forceinline__ void rk4_step(const TypeConst& c, const Limits& L, Agent& a,
                                          const float dc[4]) {
 #pragma clang fp contract(off)
@@ -451,7 +471,7 @@ __device__ __forceinline__ void rk4_step(const TypeConst& c, const Limits& L, Ag
     }
     add_carry<CARRY>(a.J, a.J_lo, POTATO_FMA(L.dt6, ass, L.dt * c.four_w2));
 
-    const float r = rsq(POTATO_FMA(a.q[3], a.q[3],
+    const float r = rsq<SPACED>(POTATO_FMA(a.q[3], a.q[3],
                         POTATO_FMA(a.q[2], a.q[2], POTATO_FMA(a.q[1], a.q[1], a.q[0] * a.q[0]))));
 #pragma unroll
     for (int i = 0; i < 4; ++i) a.q[i] *= r;

@@ -770,3 +770,52 @@ def test_four_lanes_per_agent_give_the_bits_of_one(torch_dev, n, kind):
         a, b = one[k], four[k]
         same = (a.view(np.int32) == b.view(np.int32)) | (np.isnan(a) & np.isnan(b))
         assert same.all(), (k, np.argwhere(~same)[:5])
+
+
+@pytest.mark.parametrize("kind", ["closed", "uncompensated", "gains", "kinds", "kinds_order"])
+def test_rollouts_of_many_agents_keep_their_bits(torch_dev, kind):
+    """Closed-loop swarms of more than 131,072 agents take the spaced rsq and
+    sqrt: the first 131,072 agents of one more must come out bit for bit as
+    in a swarm of their own (far way-points, thrust at its bounds, NaN and
+    infinite states, zero and unnormalised attitudes)."""
+    torch, dev = torch_dev
+    from paper_2308_12698_amd.sim import Simulator
+    n = 131072
+    rng = np.random.default_rng(78)
+    N = n + 1
+    s = np.zeros((30, N))
+    s[0:3] = rng.uniform(0.0, 50.0, (3, N))
+    s[3:6] = rng.normal(0.0, 2.0, (3, N))
+    s[6:10] = rng.normal(0.0, 1.0, (4, N)) + np.array([[2.0], [0.0], [0.0], [0.0]])
+    s[6:10, ::2] /= np.linalg.norm(s[6:10, ::2], axis=0)
+    s[6:10, 5::1000] = 0.0
+    s[10:13] = rng.normal(0.0, 2.0, (3, N))
+    s[13:17] = rng.normal(0.0, 80.0, (4, N))
+    s[17:29] = rng.uniform(-1.0, 1.0, (12, N))
+    bad = np.arange(3, N, 997)
+    for k, i in enumerate(bad):
+        s[k % 30, i] = (np.nan, np.inf, -np.inf)[k % 3]
+    state = I.f32(s)
+    wp = I.f32(rng.uniform(-50.0, 100.0, (2, 3, N)))
+    wp[:, :, ::4] = state[0:3, ::4]
+    carry = None if kind == "uncompensated" else I.f32(rng.normal(0.0, 1e-7, (10, N)))
+    gains = I.f32(np.asarray(I.DEFAULT_GAINS)[:, None] * rng.uniform(0.5, 3.0, (9, N)))
+    types, ti = [I.base_type()], None
+    if kind.startswith("kinds"):
+        types = [I.base_type(), I.car_type(lam=1.0), I.wing_type(lam=-1.0), I.base_type(), I.car_type(lam=-1.0)]
+        ti = rng.integers(0, 5, N).astype(np.uint8)
+    out = []
+    for m in (n, N):
+        sim = Simulator(types, I.globals_f32(), mode=1, form="fused")
+        st = _dev(torch, dev, state[:, :m])
+        ct = None if carry is None else _dev(torch, dev, carry[:, :m])
+        tt = None if ti is None else _dev(torch, dev, ti[:m])
+        sim.step(st, 23, 1e-3, type_idx=tt, carry=ct, perm=sim.order_by_type(tt) if kind == "kinds_order" else None,
+                 gains=_dev(torch, dev, gains[:, :m]) if kind == "gains" else None,
+                 wp=_dev(torch, dev, wp[:, :, :m]), resample_every=11)
+        torch.cuda.synchronize()
+        out.append([st.cpu().numpy()[:, :n]] + ([] if ct is None else [ct.cpu().numpy()[:, :n]]))
+        sim.close()
+    for a, b in zip(*out):
+        same = (a.view(np.int32) == b.view(np.int32)) | (np.isnan(a) & np.isnan(b))
+        assert same.all(), np.argwhere(~same)[:5]
