@@ -9,27 +9,35 @@
  * for bit wherever it is taken.  All decisions of one call use the alive set
  * on entry (simultaneous events).
  *
- * Grid: cell edge h = 2.02 r_max (r_max the largest radius), so any colliding
- * pair sits in the same or an adjacent cell.  Cells map to buckets by their
+ * Grid: with h = 2.02 r_max (r_max the largest radius), colliding agents are
+ * less than h apart along every axis.  A cell is h x 2h x 2h: an agent's
+ * partners sit in the 3 cells around it along x, and along y and z in its
+ * own cell or in the one on the side of the half that it is in, 12 cells in
+ * 4 (y, z) rows.  (Cells of h x h x h have 27 neighbours in 9 rows: the
+ * query took 48 us against 31 at 1M agents; where the grid is wrapped, 12
+ * buckets also hold fewer candidates than 27.)  Cells map to buckets by their
  * indices wrapped to 2^bx x 2^by x 2^bz, where the bits split the budget
  * 2^k >= 2N by the extent of the alive agents' bounding box (so a flat
  * swarm does not leave the buckets of an unused depth empty); buckets are
  * linear with x fastest, and each x row holds two extra ghost columns (a
  * copy of the last column before the first and of the first after the
  * last), so the three x neighbours of any cell are three consecutive
- * buckets and a cell's 27 neighbours are 9 contiguous bucket ranges.
+ * buckets and an agent's 12 cells are 4 contiguous bucket ranges.
  * Passes: bounding box (block partials, reduced again by every block of
- * the next kernel); a two-level sort of (x, y, z, radius) and the agent id
- * into bucket order (per-tile counts of bucket partitions, their scan, the
- * tiles' items written partition by partition, then each window of a
- * partition sorted in LDS, which also writes the bucket starts); query, one
- * thread per sorted slot, over the candidates of its 9 ranges in batches of
- * loads in flight; one block adding up the dead.  Cells that share a bucket
+ * the next kernel, which plans the wrap and stores it); a two-level sort of
+ * the items (position and radius or id) into bucket order (per-tile counts
+ * of bucket partitions, their scan, the tiles' items written partition by
+ * partition, then each window of a partition sorted in LDS, which also
+ * writes the bucket starts); query, one thread per sorted slot, over the
+ * candidates of its 4 ranges in batches of loads in flight; one block adding
+ * up the dead.  At 1M agents (5 per cubic metre) they take 7, 8.5, 6, 12,
+ * 16.5, 31 and 3 us, at 20,000 their latencies.  Cells that share a bucket
  * are far apart and fail the distance test; the decision is always the
  * distance test.  Small swarms test every pair instead (k_coll_pairs).  The 1 % margin in h keeps
  * the neighbour property exact for |coordinates| < 2^16 h (about 22 km for
  * 0.17 m radii).
  */
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -60,6 +68,11 @@ __device__ __forceinline__ int32_t cell_index(float x, float inv_h) {
     return (int32_t)floorf(c);
 }
 
+/* The cells are two edges wide in y and z: an agent's neighbours along such
+ * an axis are its own cell and the one on the side of the half it is in. */
+__device__ __forceinline__ int32_t wide_cell(int32_t c) { return c >> 1; }
+__device__ __forceinline__ uint32_t near_side(int32_t c) { return (uint32_t)((c & 1) * 2 - 1); }
+
 /* Wrap of the grid: 2^bx x 2^by x 2^bz cells, x rows of 2^bx + 2 buckets. */
 struct Wrap {
     int bx, by, bz;
@@ -67,17 +80,23 @@ struct Wrap {
     uint32_t row;            /* 2^bx + 2 */
 };
 
-__device__ __forceinline__ int ceil_log2(int64_t e) {
-    int b = 0;
-    while (b < 40 && (int64_t(1) << b) < e) ++b;
-    return b;
+/* e >= 1 */
+__device__ __forceinline__ int ceil_log2(int64_t e) { return e > 1 ? 64 - __clzll(e - 1) : 0; }
+
+__device__ __forceinline__ Wrap wrap_of(const int32_t* b) {
+    Wrap w;
+    w.bx = b[0]; w.by = b[1]; w.bz = b[2];
+    w.mx = (1u << b[0]) - 1u; w.my = (1u << b[1]) - 1u; w.mz = (1u << b[2]) - 1u;
+    w.row = (1u << b[0]) + 2u;
+    return w;
 }
 
 /* Bits per axis for bucket budget 2^k from the bounding box (min x, y, z,
  * max x, y, z, in cells): start from the bits that cover each extent, then
  * take bits away, each time from the axis whose extent is the smallest
  * multiple of its halved wrap (it gains the fewest wraps), x not below
- * kMinXBits.  Wave-uniform: every kernel of a pass computes the same wrap. */
+ * kMinXBits.  Every block of k_coll_hist computes the same wrap and one
+ * stores its bits for the later kernels of the pass. */
 __device__ __forceinline__ Wrap plan_wrap(const int32_t* box, int k) {
     int64_t e[3];
     for (int a = 0; a < 3; ++a) {
@@ -95,11 +114,7 @@ __device__ __forceinline__ Wrap plan_wrap(const int32_t* box, int k) {
         }
         --b[best];
     }
-    Wrap w;
-    w.bx = b[0]; w.by = b[1]; w.bz = b[2];
-    w.mx = (1u << b[0]) - 1u; w.my = (1u << b[1]) - 1u; w.mz = (1u << b[2]) - 1u;
-    w.row = (1u << b[0]) + 2u;
-    return w;
+    return wrap_of(b);
 }
 
 /* Bucket of wrapped cell (column col = wrapped x + 1, wrapped y, wrapped z). */
@@ -112,7 +127,11 @@ __device__ __forceinline__ uint32_t bucket_of(const Wrap& w, uint32_t col, uint3
  * bounds, then every block of the next kernel reduces the partials itself
  * (one atomic per block on six shared words serialised the first form of
  * this pass: 96 us at 1M agents). */
-constexpr int kBoxBlocks = 1024;
+constexpr int kBoxBlocks = 512;
+constexpr int64_t kBoxWords = 6 * 1024;      /* of the workspace, for 6 * kBoxBlocks */
+static_assert(6 * kBoxBlocks <= kBoxWords, "partial bounds fit");
+constexpr int kBoxThreads = 512;
+constexpr int kBoxUnroll = 4;
 constexpr int kMaxWaves = 16;
 
 __device__ __forceinline__ int32_t bound_op(int a, int32_t x, int32_t y) { return a < 3 ? min(x, y) : max(x, y); }
@@ -136,20 +155,36 @@ __device__ __forceinline__ void block_bounds(int32_t v[6], int32_t (*red)[kMaxWa
     }
 }
 
-__global__ void __launch_bounds__(256) k_coll_bounds(const float* rows, int64_t ld, int64_t n, const uint8_t* alive,
-                                                     float inv_h, int32_t* partial) {
+__global__ void __launch_bounds__(kBoxThreads) k_coll_bounds(const float* rows, int64_t ld, int64_t n,
+                                                             const uint8_t* alive, float inv_h, int32_t* partial) {
     __shared__ int32_t red[6][kMaxWaves];
     int32_t v[6] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, INT32_MIN};
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        if (!alive[i]) continue;
-        for (int a = 0; a < 3; ++a) {
-            const int32_t c = cell_index(rows[a * ld + i], inv_h);
-            v[a] = min(v[a], c);
-            v[3 + a] = max(v[3 + a], c);
+    const int64_t stride = (int64_t)gridDim.x * kBoxThreads;
+    for (int64_t i0 = (int64_t)blockIdx.x * kBoxThreads + threadIdx.x; i0 < n; i0 += kBoxUnroll * stride) {
+        /* all loads of a round in flight together */
+        float x[kBoxUnroll][3];
+        bool on[kBoxUnroll];
+#pragma unroll
+        for (int u = 0; u < kBoxUnroll; ++u) {
+            const int64_t i = i0 + u * stride;
+            on[u] = i < n;
+            if (on[u]) {
+                on[u] = alive[i] != 0;
+                for (int a = 0; a < 3; ++a) x[u][a] = rows[a * ld + i];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kBoxUnroll; ++u) {
+            if (!on[u]) continue;
+            for (int a = 0; a < 3; ++a) {
+                const int32_t f = cell_index(x[u][a], inv_h), c = a ? wide_cell(f) : f;
+                v[a] = min(v[a], c);
+                v[3 + a] = max(v[3 + a], c);
+            }
         }
     }
     block_bounds(v, red);
-    if (threadIdx.x < 6) partial[blockIdx.x * 6 + threadIdx.x] = red[threadIdx.x][0];
+    if (threadIdx.x < 6) partial[threadIdx.x * gridDim.x + blockIdx.x] = red[threadIdx.x][0];
 }
 
 /* The bounding box from the partials of k_coll_bounds, in every thread of
@@ -158,7 +193,7 @@ __device__ __forceinline__ void reduce_box(const int32_t* partial, int n_partial
                                            int32_t* box_lds) {
     int32_t v[6] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, INT32_MIN};
     for (int b = threadIdx.x; b < n_partial; b += blockDim.x)
-        for (int a = 0; a < 6; ++a) v[a] = bound_op(a, v[a], partial[b * 6 + a]);
+        for (int a = 0; a < 6; ++a) v[a] = bound_op(a, v[a], partial[a * n_partial + b]);
     block_bounds(v, red);
     if (threadIdx.x < 6) box_lds[threadIdx.x] = red[threadIdx.x][0];
     __syncthreads();
@@ -180,8 +215,8 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t n_blocks) {
 __device__ __forceinline__ void wrapped_cell(const Wrap& w, float x, float y, float z, float inv_h, uint32_t& wx,
                                              uint32_t& wy, uint32_t& wz) {
     wx = (uint32_t)cell_index(x, inv_h) & w.mx;
-    wy = (uint32_t)cell_index(y, inv_h) & w.my;
-    wz = (uint32_t)cell_index(z, inv_h) & w.mz;
+    wy = (uint32_t)wide_cell(cell_index(y, inv_h)) & w.my;
+    wz = (uint32_t)wide_cell(cell_index(z, inv_h)) & w.mz;
 }
 
 /* An agent in the first wrapped column also sits in the ghost column after
@@ -198,6 +233,16 @@ __device__ __forceinline__ uint32_t item_bucket(const Wrap& w, const float4& q, 
     wrapped_cell(w, q.x, q.y, q.z, inv_h, wx, wy, wz);
     const uint32_t b = bucket_of(w, wx + 1, wy, wz);
     return id < 0 ? (uint32_t)((int32_t)b + ghost_offset(w, wx)) : b;
+}
+
+/* An item is (x, y, z, radius) with its id in an array beside it; where all
+ * agents have one radius the id takes the radius's place: one scattered
+ * store and one gathered load less per item (1M agents: the tiles' pass 19
+ * -> 12 us and the windows' 23 -> 16.5, with the wrap kept and the scan by
+ * shuffles). */
+template <bool ONE_RADIUS>
+__device__ __forceinline__ int32_t item_id(const float4& q, const int32_t* ids, int32_t j) {
+    return ONE_RADIUS ? __float_as_int(q.w) : ids[j];
 }
 
 /* Sort of the items into bucket order.  An item is an alive agent, or the
@@ -231,11 +276,10 @@ __device__ __forceinline__ int32_t cell_offset(const int32_t* off, const int32_t
     return c < cells ? off[c] + totals[c / kScanBlock] : off[cells];
 }
 
-/* Also reduces the bounding box: block 0 stores it for the later kernels
- * of the pass. */
+/* Also reduces the bounding box and plans the wrap. */
 __global__ void __launch_bounds__(kTileBlock) k_coll_hist(const float* rows, int64_t ld, int64_t n,
                                                           const uint8_t* alive, float inv_h, const int32_t* partial,
-                                                          int n_partial, int32_t* box, int k,
+                                                          int n_partial, int32_t* wrap, int k,
                                                           int s, int32_t parts, int64_t tile, int32_t* hist) {
     extern __shared__ int32_t cnt[];
     __shared__ int32_t red[6][kMaxWaves];
@@ -261,8 +305,12 @@ __global__ void __launch_bounds__(kTileBlock) k_coll_hist(const float* rows, int
      * its reduction */
     load(a0);
     reduce_box(partial, n_partial, red, box_lds);
-    if (blockIdx.x == 0 && threadIdx.x < 6) box[threadIdx.x] = box_lds[threadIdx.x];
     const Wrap w = plan_wrap(box_lds, k);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        wrap[0] = w.bx;
+        wrap[1] = w.by;
+        wrap[2] = w.bz;
+    }
     for (int32_t p = threadIdx.x; p < parts; p += kTileBlock) cnt[p] = 0;
     __syncthreads();
     for (int64_t base = a0; base < a1; base += kTileAgents) {
@@ -282,10 +330,11 @@ __global__ void __launch_bounds__(kTileBlock) k_coll_hist(const float* rows, int
     for (int32_t p = threadIdx.x; p < parts; p += kTileBlock) hist[(int64_t)p * gridDim.x + t] = cnt[p];
 }
 
+template <bool ONE_RADIUS>
 __global__ void __launch_bounds__(kTileBlock) k_coll_part(const float* rows, int64_t ld, int64_t n,
                                                           const uint8_t* alive, const uint8_t* type, int n_types,
-                                                          const float* radius, float inv_h, const int32_t* box,
-                                                          int k, int s, int32_t parts, int64_t tile,
+                                                          const float* radius, float inv_h, const int32_t* wrap,
+                                                          int s, int32_t parts, int64_t tile,
                                                           const int32_t* off, const int32_t* totals, float4* tpos,
                                                           int32_t* tid) {
     extern __shared__ int32_t cur[];
@@ -304,12 +353,13 @@ __global__ void __launch_bounds__(kTileBlock) k_coll_part(const float* rows, int
             if (on[r]) {
                 on[r] = alive[i] != 0;
                 q[r] = make_float4(rows[i], rows[ld + i], rows[2 * ld + i],
-                                   radius[type ? type_entry(type, (uint32_t)i, n_types) : 0]);
+                                   ONE_RADIUS ? __int_as_float((int32_t)i)
+                                              : radius[type_entry(type, (uint32_t)i, n_types)]);
             }
         }
     };
     load(a0);
-    const Wrap w = plan_wrap(box, k);
+    const Wrap w = wrap_of(wrap);
     for (int32_t p = threadIdx.x; p < parts; p += kTileBlock) {
         const int64_t c = (int64_t)p * gridDim.x + t;
         cur[p] = off[c] + totals[c / kScanBlock];
@@ -326,12 +376,14 @@ __global__ void __launch_bounds__(kTileBlock) k_coll_part(const float* rows, int
             const uint32_t b = bucket_of(w, wx + 1, wy, wz);
             const int32_t slot = atomicAdd(&cur[b >> s], 1);
             tpos[slot] = q[r];
-            tid[slot] = i;
+            if (!ONE_RADIUS) tid[slot] = i;
             const int32_t g = ghost_offset(w, wx);
             if (g != 0) {
                 const int32_t gslot = atomicAdd(&cur[(uint32_t)((int32_t)b + g) >> s], 1);
+                const int32_t gi = (int32_t)((uint32_t)i | 0x80000000u);
+                if (ONE_RADIUS) q[r].w = __int_as_float(gi);
                 tpos[gslot] = q[r];
-                tid[gslot] = (int32_t)((uint32_t)i | 0x80000000u);
+                if (!ONE_RADIUS) tid[gslot] = gi;
             }
         }
     }
@@ -348,17 +400,20 @@ __global__ void __launch_bounds__(kTileBlock) k_coll_part(const float* rows, int
 constexpr int kSortBlock = 512;
 constexpr int kSortItems = 8;
 constexpr int kSortStage = kSortBlock * kSortItems;
-static_assert(kWindow % kSortBlock == 0, "whole rounds of the scan");
+constexpr int kScanItems = kWindow / kSortBlock;
+static_assert(kScanItems * kSortBlock == kWindow && kScanItems % 4 == 0, "the scan's share of a thread");
 static_assert(kSortStage <= 65536, "staged indices are 16-bit");
 
+template <bool ONE_RADIUS>
 __global__ void __launch_bounds__(kSortBlock) k_coll_sort(const float4* tpos, const int32_t* tid,
                                                           const int32_t* off, const int32_t* totals, int64_t tiles,
-                                                          int64_t cells, float inv_h, const int32_t* box, int k,
+                                                          int64_t cells, float inv_h, const int32_t* wrap,
                                                           int s, int32_t* start, float4* spos, int32_t* ids) {
-    __shared__ int32_t cnt[kWindow];
+    __shared__ int4 cnt4[kWindow / 4];
+    int32_t* const cnt = reinterpret_cast<int32_t*>(cnt4);
     __shared__ uint16_t order[kSortStage];
     __shared__ int32_t wsum[kSortBlock / 64];
-    const Wrap w = plan_wrap(box, k);
+    const Wrap w = wrap_of(wrap);
     const int64_t b0 = (int64_t)blockIdx.x << kWindowBits;
     const int64_t p = (int64_t)blockIdx.x >> (s - kWindowBits);
     const int32_t lo = cell_offset(off, totals, p * tiles, cells);
@@ -377,7 +432,8 @@ __global__ void __launch_bounds__(kSortBlock) k_coll_sort(const float4* tpos, co
             const int32_t j = lo + (int32_t)threadIdx.x + u * kSortBlock;
             rr[u] = kWindow;
             if (j >= hi) continue;
-            const int64_t r = (int64_t)item_bucket(w, tpos[j], tid[j], inv_h) - b0;
+            const float4 q = tpos[j];
+            const int64_t r = (int64_t)item_bucket(w, q, item_id<ONE_RADIUS>(q, tid, j), inv_h) - b0;
             if (r < 0)
                 ++below;
             else if (r < kWindow) {
@@ -387,7 +443,8 @@ __global__ void __launch_bounds__(kSortBlock) k_coll_sort(const float4* tpos, co
         }
     } else {
         for (int32_t j = lo + (int32_t)threadIdx.x; j < hi; j += kSortBlock) {
-            const int64_t r = (int64_t)item_bucket(w, tpos[j], tid[j], inv_h) - b0;
+            const float4 q = tpos[j];
+            const int64_t r = (int64_t)item_bucket(w, q, item_id<ONE_RADIUS>(q, tid, j), inv_h) - b0;
             if (r < 0)
                 ++below;
             else if (r < kWindow)
@@ -401,26 +458,40 @@ __global__ void __launch_bounds__(kSortBlock) k_coll_sort(const float4* tpos, co
     for (int u = 0; u < kSortBlock / 64; ++u) carry += wsum[u];
     const int32_t first = carry;                    /* the window's first slot */
     __syncthreads();
-    /* exclusive scan of the window's counts, kSortBlock at a time: the
-     * bucket starts, and the cursors of the placement below */
-    for (int c = 0; c < kWindow; c += kSortBlock) {
-        const int32_t v = cnt[c + threadIdx.x];
-        int32_t x = v;
+    /* exclusive scan of the window's counts, kScanItems consecutive ones per
+     * thread: the bucket starts, and the cursors of the placement below */
+    {
+        int4 v[kScanItems / 4];
+        int32_t sum = 0;
+#pragma unroll
+        for (int u = 0; u < kScanItems / 4; ++u) {
+            v[u] = cnt4[threadIdx.x * (kScanItems / 4) + u];
+            sum += v[u].x + v[u].y + v[u].z + v[u].w;
+        }
+        int32_t x = sum;
         for (int d = 1; d < 64; d <<= 1) {
             const int32_t y = __shfl_up(x, d);
             if (lane >= d) x += y;
         }
         if (lane == 63) wsum[wave] = x;
         __syncthreads();
-        int32_t pre = carry, all = 0;
+        int32_t e = carry + x - sum;
         for (int u = 0; u < kSortBlock / 64; ++u) {
-            pre += u < wave ? wsum[u] : 0;
-            all += wsum[u];
+            e += u < wave ? wsum[u] : 0;
+            carry += wsum[u];
         }
-        const int32_t e = pre + x - v;
-        cnt[c + threadIdx.x] = e;
-        start[b0 + c + threadIdx.x] = e;
-        carry += all;
+        int4* const out = reinterpret_cast<int4*>(start + b0);
+#pragma unroll
+        for (int u = 0; u < kScanItems / 4; ++u) {
+            int4 o;
+            o.x = e;
+            o.y = o.x + v[u].x;
+            o.z = o.y + v[u].y;
+            o.w = o.z + v[u].z;
+            e = o.w + v[u].w;
+            cnt4[threadIdx.x * (kScanItems / 4) + u] = o;
+            out[threadIdx.x * (kScanItems / 4) + u] = o;
+        }
         __syncthreads();
     }
     if (staged) {
@@ -434,17 +505,17 @@ __global__ void __launch_bounds__(kSortBlock) k_coll_sort(const float4* tpos, co
         for (int32_t j = threadIdx.x; j < carry - first; j += kSortBlock) {
             const int32_t from = lo + order[j];
             spos[first + j] = tpos[from];
-            ids[first + j] = tid[from];
+            if (!ONE_RADIUS) ids[first + j] = tid[from];
         }
     } else {
         for (int32_t j = lo + (int32_t)threadIdx.x; j < hi; j += kSortBlock) {
             const float4 qj = tpos[j];
-            const int32_t ij = tid[j];
+            const int32_t ij = item_id<ONE_RADIUS>(qj, tid, j);
             const int64_t r = (int64_t)item_bucket(w, qj, ij, inv_h) - b0;
             if (r >= 0 && r < kWindow) {
                 const int32_t slot = atomicAdd(&cnt[r], 1);
                 spos[slot] = qj;
-                ids[slot] = ij;
+                if (!ONE_RADIUS) ids[slot] = ij;
             }
         }
     }
@@ -453,20 +524,24 @@ __global__ void __launch_bounds__(kSortBlock) k_coll_sort(const float4* tpos, co
 /* One thread per sorted real slot (grid-stride; ghost slots are skipped):
  * consecutive lanes hold agents of the same or nearby cells, so the bucket
  * ranges and candidates they read are shared through the caches, and each
- * XCD takes a contiguous range of slots (xcd_tile).  The 9
+ * XCD takes a contiguous range of slots (xcd_tile).  The 4
  * candidate ranges are walked as one sequence, POTATO_QUERY_BATCH loads at
  * a time (indices past a lane's end read its own slot and are masked), and
  * a lane stops once it has found a collision.  (Copying each block's
  * candidate rows to LDS first, with consecutive loads, measured 1.25 times
  * slower at 1M agents: fewer waves per SIMD, a barrier per round, and the
  * L1 already serves most candidate reads.) */
+constexpr int kRanges = 4;
+
+template <bool ONE_RADIUS>
 __global__ void __launch_bounds__(256) k_coll_query(const float4* spos, const int32_t* ids, const int32_t* start,
-                                                    const int32_t* total, float inv_h, const int32_t* box, int k_bits,
-                                                    uint8_t* alive, int32_t* died_part) {
+                                                    const int32_t* total, const float* radius, float inv_h,
+                                                    const int32_t* wrap, uint8_t* alive, int32_t* died_part) {
 #pragma clang fp contract(off)
     __shared__ int32_t wave_died[256 / 64];
     int32_t my_died = 0;
-    const Wrap w = plan_wrap(box, k_bits);
+    const Wrap w = wrap_of(wrap);
+    const float rs1 = radius[0] + radius[0];
     const int64_t slots = *total;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -475,28 +550,33 @@ __global__ void __launch_bounds__(256) k_coll_query(const float4* spos, const in
          * sees every lane; slot indices stay below 2^31 (at most two slots
          * per agent, fewer than 2^30 agents) */
         const int32_t k = (int32_t)(k0 + threadIdx.x);
-        const int32_t id = k < slots ? ids[k] : -1;
+        float4 pk = make_float4(0.0f, 0.0f, 0.0f, __int_as_float(-1));
+        if (ONE_RADIUS && k < slots) pk = spos[k];
+        const int32_t id = k < slots ? item_id<ONE_RADIUS>(pk, ids, k) : -1;
         bool hit = false;
         if (id >= 0) {
-            const float4 pk = spos[k];
+            if (!ONE_RADIUS) pk = spos[k];
             uint32_t wx, wy, wz;
             wrapped_cell(w, pk.x, pk.y, pk.z, inv_h, wx, wy, wz);
-            /* the 9 (y, z) rows: bucket range of columns wx .. wx + 2 (ghost-padded) */
-            int32_t lo[9], hi[9];
+            /* the 4 (y, z) rows: bucket range of columns wx .. wx + 2 (ghost-padded);
+             * an axis wrapped to a single cell has no other row */
+            const uint32_t ny = (wy + near_side(cell_index(pk.y, inv_h))) & w.my;
+            const uint32_t nz = (wz + near_side(cell_index(pk.z, inv_h))) & w.mz;
+            int32_t lo[kRanges], hi[kRanges];
 #pragma unroll
-            for (int r = 0; r < 9; ++r) {
-                const uint32_t ry = (wy + (uint32_t)(r % 3) - 1u) & w.my;
-                const uint32_t rz = (wz + (uint32_t)(r / 3) - 1u) & w.mz;
-                const uint32_t b0 = bucket_of(w, wx, ry, rz);
+            for (int r = 0; r < kRanges; ++r) {
+                const uint32_t b0 = bucket_of(w, wx, r & 1 ? ny : wy, r & 2 ? nz : wz);
                 lo[r] = start[b0];
                 hi[r] = start[b0 + 3];
             }
+            if (w.my == 0) hi[1] = lo[1], hi[3] = lo[3];
+            if (w.mz == 0) hi[2] = lo[2], hi[3] = lo[3];
             /* candidate t of the sequence is slot t + d[r] for the last range r
              * whose first candidate number cum[r] is <= t */
-            int32_t cum[9], d[9];
+            int32_t cum[kRanges], d[kRanges];
             int32_t T = 0;
 #pragma unroll
-            for (int r = 0; r < 9; ++r) {
+            for (int r = 0; r < kRanges; ++r) {
                 cum[r] = T;
                 d[r] = lo[r] - T;
                 T += hi[r] - lo[r];
@@ -504,7 +584,7 @@ __global__ void __launch_bounds__(256) k_coll_query(const float4* spos, const in
             auto collides = [&](const float4& pj) {
                 const float ex = pk.x - pj.x, ey = pk.y - pj.y, ez = pk.z - pj.z;
                 const float d2 = (ex * ex + ey * ey) + ez * ez;
-                const float rs = pk.w + pj.w;
+                const float rs = ONE_RADIUS ? rs1 : pk.w + pj.w;
                 return d2 < rs * rs;
             };
             constexpr int B = POTATO_QUERY_BATCH;
@@ -516,7 +596,7 @@ __global__ void __launch_bounds__(256) k_coll_query(const float4* spos, const in
                     const int32_t t = t0 + u;
                     int32_t j = t + d[0];
 #pragma unroll
-                    for (int r = 1; r < 9; ++r) j = t >= cum[r] ? t + d[r] : j;
+                    for (int r = 1; r < kRanges; ++r) j = t >= cum[r] ? t + d[r] : j;
                     use[u] = t < T && j != k;
                     pc[u] = spos[t < T ? j : k];
                 }
@@ -547,24 +627,27 @@ __global__ void __launch_bounds__(256) k_coll_query(const float4* spos, const in
     }
 }
 
+constexpr int kDiedBlock = 1024;
+
 /* *died += the sum of the per-block counts of the query. */
-__global__ void __launch_bounds__(256) k_coll_died(const int32_t* died_part, int n_part, unsigned long long* died) {
-    __shared__ unsigned long long red[256 / 64];
+__global__ void __launch_bounds__(kDiedBlock) k_coll_died(const int32_t* died_part, int n_part, unsigned long long* died) {
+    __shared__ unsigned long long red[kDiedBlock / 64];
     unsigned long long x = 0;
-    for (int b = threadIdx.x; b < n_part; b += blockDim.x) x += (unsigned long long)died_part[b];
+#pragma unroll 4
+    for (int b = threadIdx.x; b < n_part; b += kDiedBlock) x += (unsigned long long)died_part[b];
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64] = x;
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long sum = 0;
-        for (int w = 0; w < (int)(blockDim.x / 64); ++w) sum += red[w];
+        for (int w = 0; w < kDiedBlock / 64; ++w) sum += red[w];
         *died += sum;
     }
 }
 
 /* Small swarms: every pair of agents, no grid.  The eight launches of the
- * grid pass cost their latencies, whatever the number of agents (44-49 us
- * from 1,000 to 20,000 agents); all n^2 / 2 pairs of 5,000 agents are 2 us of
+ * grid pass cost their latencies, whatever the number of agents (31-33 us
+ * from 2,000 to 20,000 agents); all n^2 / 2 pairs of 5,000 agents are 2 us of
  * FP32 work.  A wave holds the agents i of TILES tiles of 64, one per lane
  * and tile, and tests them against a tile of 64 agents j that its block
  * keeps in LDS and every lane reads at the same address.  The blocks cover
@@ -582,12 +665,13 @@ __global__ void __launch_bounds__(256) k_coll_died(const int32_t* died_part, int
  * 10.4 / 14.4 / 17.9 / 23.8 / 44 us with one, 13.5 / 16.0 / 21.0 / 21.3 / 36
  * with two): two from kPairsOneTile agents on.
  * kPairsMaxAgents: where the pairs' n^2 meets the grid pass's latencies
- * (16,000 agents: 36-38 us against 47-51; 20,000: 50-52 against 44-48). */
+ * (12,000 agents: 26-28 us against 32; 13,000: 29-32 against 32-33; 14,000:
+ * 31-33 against 32-33; 16,000: 36-39 against 32-33). */
 constexpr int kPairBlock = 256;
 constexpr int kPairWaves = kPairBlock / 64;
 constexpr int64_t kPairsOneTile = 9216;
 #ifndef POTATO_PAIRS_MAX
-#define POTATO_PAIRS_MAX 16384
+#define POTATO_PAIRS_MAX 13312
 #endif
 constexpr int64_t kPairsMaxAgents = POTATO_PAIRS_MAX;
 
@@ -728,10 +812,10 @@ constexpr int64_t workspace_for(int64_t n) {
     /* items (x, y, z, r) in partition order and in bucket order [2n] each
      * first (16-byte aligned: agents and ghosts); their ids [2n] each;
      * bucket starts [parts << s]; partition-tile offsets [parts * tiles + 1];
-     * chunk totals of their scan [chunks]; bounding box [6]; its per-block
-     * partials [kBoxBlocks][6]; the query's per-block counts of dead agents */
+     * chunk totals of their scan [chunks]; bits of the wrap [3 of 6]; the
+     * bounding box's per-block partials [kBoxWords]; the query's per-block counts of dead agents */
     const int64_t blocks = (n + 255) / 256;
-    return 16 * 4 * n + 4 * (4 * n + (q.parts << q.s) + cells + 1 + chunks + 6 + 6 * kBoxBlocks + blocks) + 256;
+    return 16 * 4 * n + 4 * (4 * n + (q.parts << q.s) + cells + 1 + chunks + 6 + kBoxWords + blocks) + 256;
 }
 
 /* Workspace of the allocation-free entry point: a file-scope device array
@@ -797,26 +881,28 @@ hipError_t launch_detect_collisions(const float* rows, int64_t ld, int64_t n, co
     int32_t* start = ids + 2 * n;
     int32_t* off = start + (q.parts << q.s);
     int32_t* totals = off + cells + 1;
-    int32_t* box = totals + scan_chunks((uint32_t)cells);
-    int32_t* partial = box + 6;
-    int32_t* died_part = partial + 6 * kBoxBlocks;
+    int32_t* wrap = totals + scan_chunks((uint32_t)cells);
+    int32_t* partial = wrap + 6;
+    int32_t* died_part = partial + kBoxWords;
     const float inv_h = 1.0f / (2.02f * r_max);
     const unsigned nb = (unsigned)((n + 255) / 256);
-    const unsigned nbox = nb < (unsigned)kBoxBlocks ? nb : (unsigned)kBoxBlocks;
+    const unsigned nbox = std::min<unsigned>((unsigned)((n + kBoxThreads - 1) / kBoxThreads), kBoxBlocks);
     const size_t lds = (size_t)q.parts * sizeof(int32_t);
-    hipLaunchKernelGGL(k_coll_bounds, dim3(nbox), dim3(256), 0, s, rows, ld, n, alive, inv_h, partial);
+    hipLaunchKernelGGL(k_coll_bounds, dim3(nbox), dim3(kBoxThreads), 0, s, rows, ld, n, alive, inv_h, partial);
     hipLaunchKernelGGL(k_coll_hist, dim3((unsigned)q.tiles), dim3(kTileBlock), lds, s, rows, ld, n, alive, inv_h,
-                       partial, (int)nbox, box, q.k, q.s, (int32_t)q.parts, q.tile, off);
+                       partial, (int)nbox, wrap, q.k, q.s, (int32_t)q.parts, q.tile, off);
     /* in place, chunk by chunk (the consumers add the chunk totals); the
      * slot count goes to off[cells] */
     launch_exclusive_scan_chunks(off, off, totals, off + cells, (uint32_t)cells, s);
-    hipLaunchKernelGGL(k_coll_part, dim3((unsigned)q.tiles), dim3(kTileBlock), lds, s, rows, ld, n, alive, type,
-                       n_types, radius_dev, inv_h, box, q.k, q.s, (int32_t)q.parts, q.tile, off, totals, tpos, tid);
-    hipLaunchKernelGGL(k_coll_sort, dim3((unsigned)((q.parts << q.s) >> kWindowBits)), dim3(kSortBlock), 0, s, tpos,
-                       tid, off, totals, q.tiles, cells, inv_h, box, q.k, q.s, start, spos, ids);
-    hipLaunchKernelGGL(k_coll_query, dim3(nb), dim3(256), 0, s, spos, ids, start, off + cells, inv_h, box, q.k, alive,
-                       died ? died_part : nullptr);
-    if (died) hipLaunchKernelGGL(k_coll_died, dim3(1), dim3(256), 0, s, died_part, (int)nb, died);
+    hipLaunchKernelGGL((type ? k_coll_part<false> : k_coll_part<true>), dim3((unsigned)q.tiles), dim3(kTileBlock), lds,
+                       s, rows, ld, n, alive, type, n_types, radius_dev, inv_h, wrap, q.s, (int32_t)q.parts, q.tile,
+                       off, totals, tpos, tid);
+    hipLaunchKernelGGL((type ? k_coll_sort<false> : k_coll_sort<true>), dim3((unsigned)((q.parts << q.s) >> kWindowBits)),
+                       dim3(kSortBlock), 0, s, tpos, tid, off, totals, q.tiles, cells, inv_h, wrap, q.s, start, spos,
+                       ids);
+    hipLaunchKernelGGL((type ? k_coll_query<false> : k_coll_query<true>), dim3(nb), dim3(256), 0, s, spos, ids, start,
+                       off + cells, radius_dev, inv_h, wrap, alive, died ? died_part : nullptr);
+    if (died) hipLaunchKernelGGL(k_coll_died, dim3(1), dim3(kDiedBlock), 0, s, died_part, (int)nb, died);
     return hipGetLastError();
 }
 

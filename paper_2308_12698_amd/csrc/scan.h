@@ -16,44 +16,57 @@ namespace {
 
 constexpr int kScanBlock = 1024;
 
+/* Inclusive scan of v over a block of kScanBlock threads; *all receives the
+ * sum.  Shuffles within the waves, then every thread adds up the waves
+ * before its own: one barrier instead of the twenty of a scan through LDS
+ * (the two launches below are all latency: 6.5 -> 5 us together).  part may
+ * be used again after another barrier. */
+__device__ __forceinline__ int32_t block_scan(int32_t v, int32_t* part, int32_t* all) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t x = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t y = __shfl_up(x, d);
+        if (lane >= d) x += y;
+    }
+    if (lane == 63) part[wave] = x;
+    __syncthreads();
+    int32_t sum = 0;
+#pragma unroll
+    for (int u = 0; u < kScanBlock / 64; ++u) {
+        const int32_t t = part[u];
+        x += u < wave ? t : 0;
+        sum += t;
+    }
+    *all = sum;
+    return x;
+}
+
 /* Exclusive scan in chunks of kScanBlock: per-chunk scan + chunk totals. */
 __global__ void __launch_bounds__(kScanBlock) k_scan_chunks(const int32_t* in, int32_t* out, int32_t* totals,
                                                             uint32_t m) {
-    __shared__ int32_t buf[kScanBlock];
+    __shared__ int32_t part[kScanBlock / 64];
     const uint32_t g = blockIdx.x * kScanBlock + threadIdx.x;
     const int32_t v = g < m ? in[g] : 0;
-    buf[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 1; off < kScanBlock; off <<= 1) {
-        const int32_t add = (int)threadIdx.x >= off ? buf[threadIdx.x - off] : 0;
-        __syncthreads();
-        buf[threadIdx.x] += add;
-        __syncthreads();
-    }
-    if (g < m) out[g] = buf[threadIdx.x] - v;
-    if (threadIdx.x == kScanBlock - 1) totals[blockIdx.x] = buf[threadIdx.x];
+    int32_t all;
+    const int32_t x = block_scan(v, part, &all);
+    if (g < m) out[g] = x - v;
+    if (threadIdx.x == 0) totals[blockIdx.x] = all;
 }
 
 /* One block: exclusive scan of the chunk totals (any count), in place;
  * the grand total goes to *grand. */
 __global__ void __launch_bounds__(kScanBlock) k_scan_totals(int32_t* totals, uint32_t n_chunks, int32_t* grand) {
-    __shared__ int32_t buf[kScanBlock];
+    __shared__ int32_t part[kScanBlock / 64];
     int32_t carry = 0;
     for (uint32_t c0 = 0; c0 < n_chunks; c0 += kScanBlock) {
         const uint32_t c = c0 + threadIdx.x;
         const int32_t v = c < n_chunks ? totals[c] : 0;
-        buf[threadIdx.x] = v;
+        int32_t all;
+        const int32_t x = block_scan(v, part, &all);
+        if (c < n_chunks) totals[c] = carry + x - v;
+        carry += all;
         __syncthreads();
-        for (int off = 1; off < kScanBlock; off <<= 1) {
-            const int32_t add = (int)threadIdx.x >= off ? buf[threadIdx.x - off] : 0;
-            __syncthreads();
-            buf[threadIdx.x] += add;
-            __syncthreads();
-        }
-        if (c < n_chunks) totals[c] = carry + buf[threadIdx.x] - v;
-        const int32_t chunk = buf[kScanBlock - 1];
-        __syncthreads();
-        carry += chunk;
     }
     if (threadIdx.x == 0) *grand = carry;
 }

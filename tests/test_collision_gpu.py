@@ -308,3 +308,38 @@ def test_detection_around_the_pairs_limits(oracle, torch_dev, n, typed):
     assert np.array_equal(got, ref) and died == ref_died
     again, more = gpu_detect(torch_dev, state, types, got, ti)
     assert np.array_equal(again, got) and more == 0
+
+
+@pytest.mark.parametrize("shape", ["lattice", "plane", "line", "cluster", "far"])
+@pytest.mark.parametrize("typed", [False, True])
+def test_detection_on_the_grid_at_cell_edges(oracle, torch_dev, shape, typed):
+    """The grid pass just above the all-pairs limit.  Jittered lattices with
+    a pitch of one contact distance put partners on every side of every half
+    cell (a volume around the origin, one layer, one row; the last two along
+    an edge of the cells, so that pairs straddle it); a coincident cluster
+    larger than the sort's staging; far clamped, infinite and NaN positions.
+    Decisions and counts as the brute-force reference, bit for bit."""
+    rng = np.random.default_rng(len(shape) + 10 * typed)
+    n = 13313
+    types = [I.base_type()] + ([I.base_type(arm=0.4), I.base_type(arm=0.05)] if typed else [])
+    ti = rng.integers(0, 5, n).astype(np.uint8) if typed else None      # 3 and 4 read as the last type
+    r = max(t["radius"] for t in types)
+    k = np.arange(n)
+    side = {"plane": (116, 116, 1), "line": (n, 1, 1)}.get(shape, (24, 24, 24))
+    cell = np.stack([k % side[0], k // side[0] % side[1], k // (side[0] * side[1])]).astype(np.float64)
+    pos = (cell - np.asarray(side)[:, None] // 2) * (2.0 * r) + rng.normal(0.0, 0.2 * r, (3, n))
+    if shape == "cluster":
+        pos[:, 2000:8000] = np.array([[3.3], [-2.2], [1.1]])
+    if shape == "far":
+        pos[:, 0:400:2] = rng.uniform(-6e6, 6e6, (3, 200))
+        pos[:, 1:400:2] = pos[:, 0:400:2]
+        pos[0, 400:420] = np.nan
+        pos[1, 420:440] = np.inf
+        pos[2, 440:460] = -np.inf
+    state = I.hover_state(pos.astype(np.float32).astype(np.float64))
+    alive = (rng.random(n) > 0.1).astype(np.uint8)
+    got, died = gpu_detect(torch_dev, state, types, alive, ti)
+    ref, ref_died = oracle.detect_collisions(state, [t["radius"] for t in types], alive,
+                                             None if ti is None else np.minimum(ti, 2))
+    assert np.array_equal(got, ref) and died == ref_died
+    assert 0 < died < int(alive.sum())
