@@ -144,10 +144,23 @@ bool rollout_spaced(const Variant& v, const StepArgs& a);
  * threads per block serving 64 agents with one recomputing and one
  * reversing wave, tape [grid][2][K][kTapeRows][64].  Either way the tape
  * takes K x kTapeRows x grid x block floats. */
-const void* adjoint_kernel(bool het, bool gains, bool perm, bool pipe);
+const void* adjoint_kernel(bool het, bool gains, bool perm, bool pipe, bool stream = false);
 hipError_t launch_adjoint(bool het, bool gains, bool perm, bool pipe, const AdjArgs& a, int grid_blocks,
                           hipStream_t stream);
 size_t adjoint_lds_bytes(bool het, int n_types, bool pipe);
+
+/* Launches whose tape (the 22 rows that every step writes and reads) does
+ * not fit the 256 MB Infinity Cache with room to spare read it with loads
+ * that leave the cache to the slots still to come: per step 3.36 -> 3.33 us
+ * at 65,536 agents with 50 steps per segment, 3.28 -> 2.97 with 20 (231 MB),
+ * 3.25 -> 3.11 at 49,152 with 50.  Smaller tapes stay in the caches, and the
+ * plain loads are the better ones (8,192 agents, 20 steps per segment: 2.44
+ * against 2.54).  One agent per thread: only where the waves come back to
+ * their slots for further agents (14.65 -> 13.9 at 300,007 agents, 51.5 ->
+ * 49.9 at 1,048,576; a single round at 131,072 is no faster, 5.97 against
+ * 6.07). */
+constexpr int64_t kStreamTapeBytes = int64_t(192) << 20;
+bool adjoint_streams(bool pipe, const AdjArgs& a);
 constexpr int kAdjBlock = 256;
 constexpr int kAdjPipeBlock = 128;
 /* Use the pipelined adjoint for small swarms (1) or never (0). */

@@ -670,7 +670,7 @@ __global__ void __launch_bounds__(1024) k_rollout_lanes(const StepArgs A) {
 #define POTATO_ADJOINT_LIMITS_FROM_LDS 0
 #endif
 
-template <bool HET, bool GAINS, bool PERM>
+template <bool HET, bool GAINS, bool PERM, bool STREAM>
 __global__ void __launch_bounds__(kAdjBlock)
     __attribute__((amdgpu_waves_per_eu(POTATO_ADJOINT_WAVES, POTATO_ADJOINT_WAVES))) k_adjoint(const AdjArgs A) {
     extern __shared__ float4 lds_raw[];
@@ -717,7 +717,7 @@ __global__ void __launch_bounds__(kAdjBlock)
         load_adj(A.grad_final, ld, bo, lam);
         float gk[9] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         if (steps > 0)
-            agent_backward(c, lim, g, A.ckpt, ld, bo, A.K, n_seg_all, steps, A.step0, A.wp, A.cmd_ld,
+            agent_backward<STREAM>(c, lim, g, A.ckpt, ld, bo, A.K, n_seg_all, steps, A.step0, A.wp, A.cmd_ld,
                            A.n_epochs, A.resample, tape, tape_step, lb, lam, gk);
         store_adj(A.grad_x0, A.grad_mem, ld, bo, lam);
         if (A.grad_gains) {
@@ -740,7 +740,7 @@ __global__ void __launch_bounds__(kAdjBlock)
  * group, the group loop bounds being the same for the whole block).
  * Tape: per block, 2 buffers x K slots x kTapeRows x 64 floats.
  */
-template <bool HET, bool GAINS, bool PERM>
+template <bool HET, bool GAINS, bool PERM, bool STREAM>
 __global__ void __launch_bounds__(kAdjPipeBlock)
     __attribute__((amdgpu_waves_per_eu(POTATO_ADJOINT_WAVES, POTATO_ADJOINT_WAVES))) k_adjoint_pipe(const AdjArgs A) {
     extern __shared__ float4 lds_raw[];
@@ -803,7 +803,7 @@ __global__ void __launch_bounds__(kAdjPipeBlock)
             } else {
                 const int seg = n_seg_all - t;
                 if (t > 0 && seg < n_seg)
-                    reverse_segment(c, lim, g, A.ckpt, ld, bo, A.K, seg, steps, A.step0, A.resample, wc,
+                    reverse_segment<STREAM>(c, lim, g, A.ckpt, ld, bo, A.K, seg, steps, A.step0, A.resample, wc,
                                     tape + (seg & 1) * buf_stride, tape_step, lb,
                                     tails + (seg & 1) * kTailRows * 64, x, w, lam, gk);
             }
@@ -925,12 +925,12 @@ const void* rollout_kernel(const Variant& v, const StepArgs& a) {
 }
 
 template <bool H, bool G, bool P>
-const void* afn() {
-    return reinterpret_cast<const void*>(&k_adjoint<H, G, P>);
-}
-template <bool H, bool G, bool P>
-const void* apfn() {
-    return reinterpret_cast<const void*>(&k_adjoint_pipe<H, G, P>);
+const void* afn(bool pipe, bool stream) {
+    if (pipe)
+        return stream ? reinterpret_cast<const void*>(&k_adjoint_pipe<H, G, P, true>)
+                      : reinterpret_cast<const void*>(&k_adjoint_pipe<H, G, P, false>);
+    return stream ? reinterpret_cast<const void*>(&k_adjoint<H, G, P, true>)
+                  : reinterpret_cast<const void*>(&k_adjoint<H, G, P, false>);
 }
 
 size_t adjoint_lds_bytes(bool het, int n_types, bool pipe) {
@@ -938,22 +938,22 @@ size_t adjoint_lds_bytes(bool het, int n_types, bool pipe) {
            (pipe ? 2 * (size_t)kTailRows * 64 * sizeof(float) : 0);
 }
 
-const void* adjoint_kernel(bool het, bool gains, bool perm, bool pipe) {
-    if (pipe) {
-        if (!het) return gains ? apfn<false, true, false>() : apfn<false, false, false>();
-        if (perm) return gains ? apfn<true, true, true>() : apfn<true, false, true>();
-        return gains ? apfn<true, true, false>() : apfn<true, false, false>();
-    }
-    if (!het) return gains ? afn<false, true, false>() : afn<false, false, false>();
-    if (perm) return gains ? afn<true, true, true>() : afn<true, false, true>();
-    return gains ? afn<true, true, false>() : afn<true, false, false>();
+const void* adjoint_kernel(bool het, bool gains, bool perm, bool pipe, bool stream) {
+    if (!het) return gains ? afn<false, true, false>(pipe, stream) : afn<false, false, false>(pipe, stream);
+    if (perm) return gains ? afn<true, true, true>(pipe, stream) : afn<true, false, true>(pipe, stream);
+    return gains ? afn<true, true, false>(pipe, stream) : afn<true, false, false>(pipe, stream);
+}
+
+bool adjoint_streams(bool pipe, const AdjArgs& a) {
+    const int64_t bytes = (int64_t)a.K * kTapeInt * (int64_t)sizeof(float) * a.tape_ld;
+    return bytes > kStreamTapeBytes && (pipe || a.n > a.tape_ld);
 }
 
 hipError_t launch_adjoint(bool het, bool gains, bool perm, bool pipe, const AdjArgs& a, int grid_blocks,
                           hipStream_t stream) {
     void* args[] = {const_cast<AdjArgs*>(&a)};
     const size_t lds = adjoint_lds_bytes(het, a.n_types, pipe);
-    return hipLaunchKernel(adjoint_kernel(het, gains, perm, pipe), dim3((unsigned)grid_blocks),
+    return hipLaunchKernel(adjoint_kernel(het, gains, perm, pipe, adjoint_streams(pipe, a)), dim3((unsigned)grid_blocks),
                            dim3((unsigned)(pipe ? kAdjPipeBlock : kAdjBlock)), args, lds, stream);
 }
 

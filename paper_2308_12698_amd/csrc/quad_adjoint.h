@@ -457,6 +457,14 @@ struct TapeRows {
     __device__ __forceinline__ T* row(int k) const { return k < 16 ? lo + k * 64 : hi + (k - 16) * 64; }
 };
 
+/* A tape value's load.  STREAM: marked as not read again, so that it leaves
+ * its cache line to the slots still to be written and read; for tapes that
+ * do not fit the Infinity Cache (adjoint_streams). */
+template <bool STREAM>
+__device__ __forceinline__ float tape_load(const float& x) {
+    return STREAM ? __builtin_nontemporal_load(&x) : x;
+}
+
 /* The integrals before a step are on the tape only where they are needed:
  * the reverse sweep knows those after the step, and where no clamp acted
  * those before it are less the step's increment.  Each such subtraction
@@ -487,9 +495,10 @@ __device__ __forceinline__ void store_tape(float* slot, uint32_t lb, const Agent
 }
 
 /* The same without the body rates, which the step after has read already. */
+template <bool STREAM>
 __device__ __forceinline__ void load_tape(const float* slot, uint32_t lb, Replay& a) {
     const TapeRows<const float> t(slot);
-    auto row = [&](int k) { return elem(t.row(k), lb); };
+    auto row = [&](int k) { return tape_load<STREAM>(elem(t.row(k), lb)); };
 #pragma unroll
     for (int k = 0; k < 3; ++k) { a.p[k] = row(k); a.v[k] = row(3 + k); }
 #pragma unroll
@@ -512,18 +521,20 @@ __device__ __forceinline__ void load_tape_integrals(const float* slot, uint32_t 
 }
 
 /* Body rates at the start of a step: rows 10-12 of a tape slot. */
+template <bool STREAM>
 __device__ __forceinline__ void load_tape_w(const float* slot, uint32_t lb, float w[3]) {
     const TapeRows<const float> t(slot);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) w[k] = elem(t.row(10 + k), lb);
+    for (int k = 0; k < 3; ++k) w[k] = tape_load<STREAM>(elem(t.row(10 + k), lb));
 }
 
 /* w_prev of step s of a segment: the body rates of step s - 1 on the tape,
  * or, for the segment's first step, the checkpoint's rows 26-28. */
+template <bool STREAM>
 __device__ __forceinline__ void step_wprev(const float* tape, int64_t tape_step, uint32_t lb, int s,
                                            const float* ckpt_seg, int64_t ld, uint32_t bo, float wprev[3]) {
     if (s > 0) {
-        load_tape_w(tape + (int64_t)(s - 1) * tape_step, lb, wprev);
+        load_tape_w<STREAM>(tape + (int64_t)(s - 1) * tape_step, lb, wprev);
     } else {
 #pragma unroll
         for (int k = 0; k < 3; ++k) wprev[k] = elem(row_ptr(ckpt_seg, ld, 26 + k), bo);
@@ -552,14 +563,15 @@ __device__ __forceinline__ void recompute_step(const TypeConst& c, const Limits&
 /* Reverse of step s of a segment from the tape, step k of the call.  x
  * carries the integrals after the step and w the body rates at its start,
  * both from the step after it; they come back as those of the step before. */
+template <bool STREAM>
 __device__ __forceinline__ void reverse_step(const TypeConst& c, const Limits& L, const Gains& g, Replay& x,
                                              float w[3], int s, int k, const float wp[3], const float* tape,
                                              int64_t tape_step, uint32_t lb, const float* ckpt_seg, int64_t ld,
                                              uint32_t bo, AgentAdj& lam, float gk[9]) {
     const float* const slot = tape + (int64_t)s * tape_step;
     float wprev[3];
-    load_tape(slot, lb, x);
-    step_wprev(tape, tape_step, lb, s, ckpt_seg, ld, bo, wprev);
+    load_tape<STREAM>(slot, lb, x);
+    step_wprev<STREAM>(tape, tape_step, lb, s, ckpt_seg, ld, bo, wprev);
 #pragma unroll
     for (int r = 0; r < 3; ++r) { x.w[r] = w[r]; x.dw[r] = w[r] - wprev[r]; }
     step_vjp(c, L, g, x, wp, lam, gk);
@@ -589,6 +601,7 @@ __device__ __forceinline__ void reverse_step(const TypeConst& c, const Limits& L
  * the load latency (holding the next slot in registers instead costs 22
  * registers and the second wave).
  */
+template <bool STREAM>
 __device__ __forceinline__ void agent_backward(const TypeConst& c, const Limits& L, const Gains& g,
                                                const float* ckpt, int64_t ld, uint32_t bo, int K,
                                                int n_seg_all, int steps, int64_t step0, const float* wp,
@@ -641,7 +654,7 @@ __device__ __forceinline__ void agent_backward(const TypeConst& c, const Limits&
             if (s >= len) continue;
             if (k0 + s < first) { --e; first -= period; }
             use_epoch(e);
-            reverse_step(c, L, g, x, w, s, k_begin + s, wpv, tape, tape_step, lb, ck, ld, bo, lam, gk);
+            reverse_step<STREAM>(c, L, g, x, w, s, k_begin + s, wpv, tape, tape_step, lb, ck, ld, bo, lam, gk);
         }
     }
 }
@@ -699,6 +712,7 @@ __device__ __forceinline__ void recompute_segment(const TypeConst& c, const Limi
     }
 }
 
+template <bool STREAM>
 __device__ __forceinline__ void reverse_segment(const TypeConst& c, const Limits& L, const Gains& g,
                                                 const float* ckpt, int64_t ld, uint32_t bo, int K,
                                                 int seg, int steps, int64_t step0, int resample,
@@ -725,7 +739,7 @@ __device__ __forceinline__ void reverse_segment(const TypeConst& c, const Limits
         if (s >= len) continue;
         if (k0 + s < first) { --e; first -= period; }
         wc.use(e);
-        reverse_step(c, L, g, x, w, s, k_begin + s, wc.v, tape, tape_step, lb, ck, ld, bo, lam, gk);
+        reverse_step<STREAM>(c, L, g, x, w, s, k_begin + s, wc.v, tape, tape_step, lb, ck, ld, bo, lam, gk);
     }
 }
 

@@ -472,3 +472,41 @@ def test_integrals_off_the_tape_at_clamps(torch_dev, n_steps):
     for K, pick, reps in ((1, np.arange(n), 1), (7, shuffle, 1), (16, np.arange(n), 1), (50, shuffle, 1),
                           (50, np.arange(n), 274), (7, shuffle, 274)):
         assert np.array_equal(gradient(K, pick, reps)[0], ref), (K, reps)
+
+
+@pytest.mark.parametrize("n", [49152, 65536, 131137])
+@pytest.mark.parametrize("types", [1, 8])
+def test_streamed_tape_gives_the_same_gradient(torch_dev, n, types):
+    """Tapes of more than 192 MiB are read with streaming loads: 50 steps
+    per segment, pipelined (49,152 and 65,536 agents) and one agent per
+    thread in more than one round (131,137 agents), against 7 steps per
+    segment, whose tapes are a seventh of that.  Gradients bit for bit, types
+    with different budgets, dead agents."""
+    torch, dev = torch_dev
+    from paper_2308_12698_amd.sim import Simulator
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n)
+    rand = lambda *shape: torch.rand(shape, device=dev, generator=gen)
+    table = [I.base_type()] if types == 1 else [dict(t, budget=b) for t, b in
+                                                zip(I.hetero_types(), (37, 50, 75, 120, 149, 53, 99, 1))]
+    ti = None if types == 1 else torch.randint(0, types, (n,), device=dev, generator=gen, dtype=torch.uint8)
+    gains = (torch.tensor(I.DEFAULT_GAINS, device=dev)[:, None] * (rand(9, n) * 0.4 + 0.8)).contiguous()
+    alive = (rand(n) > 0.1).to(torch.uint8)
+    start = torch.zeros((30, n), device=dev)
+    start[0:3] = rand(3, n) * 50.0
+    start[6] = 1.0
+    start[10:13] = rand(3, n) - 0.5
+    wp = (start[0:3] + rand(3, n) * 8.0 - 4.0)[None].contiguous()
+    seed = rand(30, n) - 0.5
+    sim = Simulator(table, I.globals_f32(), mode=1)
+    out = []
+    for K in (7, 50):
+        x = start.clone()
+        ckpt = torch.empty((-(-56 // K), 40, n), device=dev)
+        sim.step(x, 56, 1e-3, gains=gains, wp=wp, ckpt=ckpt, ckpt_every=K, type_idx=ti, alive=alive,
+                 carry=torch.zeros_like(x[:10]))
+        out.append(torch.cat(sim.step_backward(ckpt, K, 56, 1e-3, seed, gains=gains, wp=wp, type_idx=ti, alive=alive)))
+    torch.cuda.synchronize()
+    sim.close()
+    assert torch.isfinite(out[0]).all() and out[0][30:].abs().max() > 0
+    assert torch.equal(out[0], out[1])
