@@ -285,8 +285,12 @@ potato_status validate_step(const potato_ctx* ctx, const potato_state* st, const
  * open.
  * Steps: a launch loads and stores 80 rows per agent around its steps, which
  * at 100 steps costs 3 % of a rollout at 5,000 agents (0.984 us per step
- * against 0.956 with 1,000) and at 1,048,576 (10.13 against 9.83), so a
- * launch takes up to 1,000; swarms beyond 2^24 agents keep 100, so that no
+ * against 0.956 with 1,000), so a launch takes up to 1,000.  Launches of the
+ * spaced form of one type take 250: over more steps the waves of a SIMD
+ * drift apart and their last ones run alone (1,000 steps in launches of
+ * 1,000 / 500 / 250 / 100: 9.73 / 9.47 / 9.29 / 9.6 ms at 1,048,576 agents,
+ * 6.79 / 6.52 / 6.41 ms at 700,000, 3.20 / 3.12 / 3.13 at 300,000); open loop
+ * and several types gain nothing by it.  Swarms beyond 2^24 agents keep 100, so that no
  * launch runs much longer than a sixth of a second.
  * Block: 256 threads.  A launch that groups its agents per block fills more
  * of its groups with wider blocks, but a block of 1,024 puts 16 waves on one
@@ -299,6 +303,7 @@ potato_status validate_step(const potato_ctx* ctx, const potato_state* st, const
  * 524,288. */
 Tuned default_shape(const Variant& v, const StepArgs& a, bool kinds) {
     Tuned t{256, a.n <= (int64_t(1) << 24) ? 1000 : 100, 0};
+    if (rollout_spaced(v, a) && !kinds) t.steps = std::min(t.steps, 250);
     if (rollout_grouped(v, a)) {
         if (kinds)
             t.block = a.n <= 65536 ? 256 : a.n <= 131072 ? 512 : 1024;
