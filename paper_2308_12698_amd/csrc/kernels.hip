@@ -879,11 +879,10 @@ template <int MODE, bool HET, bool GAINS, bool PERM>
 const void* kfn_carry(const Variant& v, const StepArgs& a) {
     if (MODE == 1 && v.ckpt) return kfn<MODE, HET, GAINS, MODE == 1, PERM, true, false>();
     if (rollout_spaced(v, a)) {
-        constexpr bool S = MODE == 1;   /* open loop never is */
+        constexpr bool K = MODE == 1 && PERM, H = MODE == 1 && !HET;
         if (v.kinds)
-            return v.carry ? kfn<MODE, HET, GAINS, false, PERM, true, true, S>()
-                           : kfn<MODE, HET, GAINS, false, PERM, false, true, S>();
-        constexpr bool H = S && !HET;   /* nor are quadrotors of several types */
+            return v.carry ? kfn<MODE, HET, GAINS, false, PERM, true, true, K>()
+                           : kfn<MODE, HET, GAINS, false, PERM, false, true, K>();
         return v.carry ? kfn<MODE, HET, GAINS, false, PERM, true, false, H>()
                        : kfn<MODE, HET, GAINS, false, PERM, false, false, H>();
     }
@@ -899,7 +898,7 @@ const void* kfn_carry(const Variant& v, const StepArgs& a) {
 bool rollout_lanes(const Variant& v, const StepArgs& a) { return !v.kinds && a.n <= kLaneAgents; }
 
 bool rollout_spaced(const Variant& v, const StepArgs& a) {
-    return v.mode == 1 && !v.ckpt && (v.kinds || !v.het) && a.n > kSpacedAgents;
+    return v.mode == 1 && !v.ckpt && (v.kinds ? v.perm && !a.alive : !v.het) && a.n > kSpacedAgents;
 }
 
 
