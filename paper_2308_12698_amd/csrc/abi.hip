@@ -290,8 +290,8 @@ potato_status validate_step(const potato_ctx* ctx, const potato_state* st, const
  * drift apart and their last ones run alone (1,000 steps in launches of
  * 1,000 / 500 / 250 / 100: 9.73 / 9.47 / 9.29 / 9.6 ms at 1,048,576 agents,
  * 6.79 / 6.52 / 6.41 ms at 700,000, 3.20 / 3.12 / 3.13 at 300,000); open loop
- * and several types gain nothing by it.  Swarms beyond 2^24 agents keep 100, so that no
- * launch runs much longer than a sixth of a second.
+ * and several types gain nothing by it.  Swarms beyond 2^24 agents keep 100,
+ * so that no launch runs much longer than a sixth of a second.
  * Block: 256 threads.  A launch that groups its agents per block fills more
  * of its groups with wider blocks, but a block of 1,024 puts 16 waves on one
  * compute unit, so the widest block is taken that still gives every compute
