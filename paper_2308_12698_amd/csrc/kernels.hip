@@ -895,7 +895,9 @@ const void* kfn_carry(const Variant& v, const StepArgs& a) {
 
 }  // namespace
 
-bool rollout_lanes(const Variant& v, const StepArgs& a) { return !v.kinds && a.n <= kLaneAgents; }
+bool rollout_lanes(const Variant& v, const StepArgs& a) {
+    return !v.kinds && a.n <= kLaneAgents && (v.het || a.n_steps != 1);
+}
 
 bool rollout_spaced(const Variant& v, const StepArgs& a) {
     return v.mode == 1 && !v.ckpt && (v.kinds ? v.perm && !a.alive : !v.het) && a.n > kSpacedAgents;

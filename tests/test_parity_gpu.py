@@ -819,3 +819,29 @@ def test_rollouts_of_many_agents_keep_their_bits(torch_dev, kind):
     for a, b in zip(*out):
         same = (a.view(np.int32) == b.view(np.int32)) | (np.isnan(a) & np.isnan(b))
         assert same.all(), np.argwhere(~same)[:5]
+
+
+@pytest.mark.parametrize("n", [1, 257, 10000, 16384])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_single_step_launches_of_small_swarms(torch_dev, n, mode):
+    """Launches of one step take one agent per lane, longer ones four lanes:
+    17 steps in launches of 17, 16 and 1, and of 1 (twice, the second time in
+    the plain form) must agree bit for bit."""
+    torch, dev = torch_dev
+    from paper_2308_12698_amd.sim import Simulator
+    rng = np.random.default_rng(n + mode)
+    state = I.hover_state(rng.uniform(0.0, 50.0, (3, n)))
+    wp = _dev(torch, dev, I.f32(rng.uniform(0.0, 50.0, (2, 3, n))))
+    cmd = _dev(torch, dev, I.f32(rng.uniform(-200.0, 200.0, (4, n))))
+    out = []
+    for form, per_launch in (("fused", 17), ("fused", 16), ("fused", 1), ("plain", 1)):
+        sim = Simulator([I.base_type()], I.globals_f32(), mode=mode, form=form, steps_per_launch=per_launch)
+        st, ct = _dev(torch, dev, state), torch.zeros((10, n), device=dev)
+        sim.step(st, 17, 1e-3, carry=ct, motor_cmd=cmd if mode == 0 else None, wp=wp if mode == 1 else None,
+                 resample_every=9)
+        torch.cuda.synchronize()
+        out.append(torch.cat([st, ct]).cpu().numpy())
+        sim.close()
+    assert np.isfinite(out[0]).all()
+    for other in out[1:]:
+        assert np.array_equal(out[0], other)
