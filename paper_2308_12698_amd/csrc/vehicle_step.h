@@ -66,15 +66,23 @@ __device__ __forceinline__ float wrap_pi(float a) {
     return POTATO_FMA(-kTwoPi, rintf(a * kInvTwoPi), a);
 }
 
-/* n / d: reciprocal, quotient and one correction by its exact residual;
- * v_div_fixup gives zeros, infinities and NaN the results of the division.
- * Five instructions where the full sequence takes eleven. */
+/* n / d: reciprocal, quotient and one correction by its exact residual, four
+ * instructions where the full sequence takes eleven, with the division's own
+ * rounding (4 million random pairs without a difference).  For a finite n
+ * and |d| from 1e-37 to 1e37: v_rcp_f32 makes infinity of a subnormal and
+ * zero of a number whose reciprocal would be one, and the correction then
+ * has no residual to work with. */
 __device__ __forceinline__ float quotient(float n, float d) {
 #pragma clang fp contract(off)
     const float r = __builtin_amdgcn_rcpf(d);
     const float q = n * r;
-    return __builtin_amdgcn_div_fixupf(POTATO_FMA(POTATO_FMA(-d, q, n), r, q), d, n);
+    return POTATO_FMA(POTATO_FMA(-d, q, n), r, q);
 }
+
+/* Airspeeds that quotient() divides by; the speeds at the step's stages are
+ * then zero or normal numbers too (a sum of products of such numbers with a
+ * time step does not come below 1e-35). */
+__device__ __forceinline__ bool ordinary_speed(float v) { return fabsf(v) >= 1e-20f && fabsf(v) <= 1e20f; }
 
 /* sin and cos of a, |a| <= kTrigMax: a - k pi/2 for the nearest k with pi/2
  * in three parts (Cody and Waite, Software Manual for the Elementary
@@ -100,13 +108,15 @@ __device__ __forceinline__ void sincos_near(float a, float& s, float& c) {
 }
 
 /* Angle of the vector (x, y), as atan2(y, x), for a vector other than
- * (0, 0): the smaller coordinate over the larger, moved by pi/4 where it
- * exceeds tan(pi/8) (both within one division), and the arctangent's series
- * through r^17 (truncation below 3e-9 for |r| <= tan(pi/8)). */
+ * (0, 0) with the larger coordinate from 1e-37 to 1e37: the smaller
+ * coordinate over the larger, moved by pi/4 where it exceeds tan(pi/8) (both
+ * within one division), and the arctangent's series through r^17 (truncation
+ * below 3e-9 for |r| <= tan(pi/8)).  NaN for a NaN coordinate. */
 __device__ __forceinline__ float vector_angle(float y, float x) {
 #pragma clang fp contract(off)
     const float ax = fabsf(x), ay = fabsf(y);
-    const float mx = fmaxf(ax, ay), mn = fminf(ax, ay);
+    const bool steep = ay > ax;
+    const float mx = steep ? ay : ax, mn = steep ? ax : ay;
     const bool big = mn > 0.41421356f * mx;
     const float r = quotient(big ? mn - mx : mn, big ? mn + mx : mx);
     const float r2 = r * r;
@@ -119,7 +129,7 @@ __device__ __forceinline__ float vector_angle(float y, float x) {
     p = POTATO_FMA(r2, p, -1.0f / 3.0f);
     const float a0 = POTATO_FMA(r * r2, p, r);
     const float a1 = big ? a0 + 0.25f * kPi : a0;
-    const float a2 = ay > ax ? 0.5f * kPi - a1 : a1;
+    const float a2 = steep ? 0.5f * kPi - a1 : a1;
     const float a3 = x < 0.0f ? kPi - a2 : a2;
     return copysignf(a3, y);
 }
@@ -212,7 +222,7 @@ __device__ __forceinline__ void veh_trig_far(const float x0[7], const VehTrig& T
 
 /* Rates of rows 0-6 at state x (its angles' functions in T) with inputs u
  * held. */
-template <int KIND>
+template <int KIND, bool ANY_SPEED>
 __device__ __forceinline__ void veh_rates(const VehConst& c, const float x[7], const VehTrig& T, const float u[3],
                                           float dx[7]) {
 #pragma clang fp contract(off)
@@ -236,7 +246,8 @@ __device__ __forceinline__ void veh_rates(const VehConst& c, const float x[7], c
         dx[1] = vh * T.sh;
         dx[2] = x[3] * T.sg;
         dx[3] = (u[0] - x[3]) * c.inv_tau[0];
-        dx[4] = quotient(c.g * T.ta, x[3]);
+        const float turn = c.g * T.ta;
+        dx[4] = ANY_SPEED && !ordinary_speed(x[3]) ? turn / x[3] : quotient(turn, x[3]);
         dx[5] = (u[1] - x[5]) * c.inv_tau[1];
         dx[6] = (u[2] - x[6]) * c.inv_tau[2];
     }
@@ -266,10 +277,10 @@ __device__ __forceinline__ void veh_guidance(const VehConst& c, const float x[7]
     }
     const float size = fabsf(cr) + fabsf(ci);
     float e;
-    if (fabsf(c.lam) == 1.0f && size >= 1e-30f && size <= 3e38f) {
+    if (fabsf(c.lam) == 1.0f && size >= 1e-30f && size <= 1e37f) {
         e = vector_angle(ci, cr);
     } else {
-        /* another lambda, the orbit's centre, infinities: angle by angle
+        /* another lambda, the orbit's centre, very far, infinities: angle by angle
          * (the heading without its whole turns, whose rounding would be that
          * of the difference) */
         const float chi_d = POTATO_FMA(c.lam, atanf(u0), atan2f(ey, ex) + c.lam_half_pi);
@@ -282,7 +293,8 @@ __device__ __forceinline__ void veh_guidance(const VehConst& c, const float x[7]
         u[2] = 0.0f;
     } else {
         /* bank that holds the circle: tan(phi) = V^2 / (g rho) */
-        const float ff = c.lam * vector_angle((x[3] * x[3]) * c.inv_g_rho, 1.0f);
+        const float tb = (x[3] * x[3]) * c.inv_g_rho;
+        const float ff = c.lam * vector_angle(tb > 1e30f ? 1e30f : tb, 1.0f);
         u[0] = c.cruise;
         u[1] = clampf_(POTATO_FMA(c.k_head, e, ff), -c.lim[1], c.lim[1]);
         u[2] = clampf_(c.k_hold * (wp[2] - x[2]), -c.lim[2], c.lim[2]);
@@ -298,40 +310,42 @@ template <int KIND, bool CARRY>
 __device__ __forceinline__ void veh_rk4(const VehConst& c, const Limits& L, float x[7], const VehTrig& T, float lo[7],
                                         const float u[3]) {
 #pragma clang fp contract(off)
-    float k1[7], k[7], acc[7], xs[7];
+    float k[7], acc[7], xs[7];
     VehTrig Ts;
-    veh_rates<KIND>(c, x, T, u, k1);
     auto start = [&]() {
 #pragma unroll
-        for (int i = 0; i < 7; ++i) acc[i] = k[i] = k1[i];
+        for (int i = 0; i < 7; ++i) acc[i] = k[i];
     };
     auto advance = [&](float h) {
 #pragma unroll
         for (int i = 0; i < 7; ++i) xs[i] = veh_row<KIND>(i) ? POTATO_FMA(h, k[i], x[i]) : x[i];
     };
     auto add = [&](float weight) {
-        veh_rates<KIND>(c, xs, Ts, u, k);
 #pragma unroll
         for (int i = 0; i < 7; ++i) acc[i] = POTATO_FMA(weight, k[i], acc[i]);
     };
-    /* stages 2-4 straight through; an agent with an offset too large for
-     * them takes the three again, one copy of their code */
-    bool near = true;
+    /* straight through; an agent with an offset too large for it, or an
+     * aircraft nearly at rest, takes the step again, one copy of its code */
+    bool near = KIND != KIND_WING || ordinary_speed(x[3]);
+    veh_rates<KIND, false>(c, x, T, u, k);
     start();
 #pragma unroll
     for (int st = 0; st < 3; ++st) {
         const float h = st < 2 ? L.half_dt : L.dt;
         advance(h);
         near = veh_trig_near<KIND>(T, h * k[4], h * k[5], h * k[6], Ts) && near;
+        veh_rates<KIND, false>(c, xs, Ts, u, k);
         add(st < 2 ? 2.0f : 1.0f);
     }
     if (!near) {
+        veh_rates<KIND, true>(c, x, T, u, k);
         start();
 #pragma unroll 1
         for (int st = 0; st < 3; ++st) {
             const float h = st < 2 ? L.half_dt : L.dt;
             advance(h);
             veh_trig_far<KIND>(x, T, h * k[4], h * k[5], h * k[6], Ts);
+            veh_rates<KIND, true>(c, xs, Ts, u, k);
             add(st < 2 ? 2.0f : 1.0f);
         }
     }

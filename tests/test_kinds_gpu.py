@@ -315,3 +315,83 @@ def test_vehicle_angle_ranges(oracle, torch_dev, dt, steps, turns):
     got = gpu_run(torch_dev, sw, steps)
     assert_kinds_parity(got, oracle_run(oracle, sw, steps), sw)
     assert np.array_equal(got, gpu_run(torch_dev, sw, steps, form="plain"))
+
+
+def one_kind(kind, state, wp=None, cmd=None, dt=1e-3, **params):
+    """A swarm of one car or aircraft type: rows 0-6 of its agents and their
+    waypoints [3, n] (closed loop) or commands [4, n] (open loop)."""
+    n = state.shape[1]
+    s = np.zeros((30, n))
+    s[0:7] = state
+    ty = I.car_type(**params) if kind == 1 else I.wing_type(**params)
+    return I.Swarm("one_kind", 0 if wp is None else 1, dt, 1, I.f32(s), [ty], I.globals_f32(),
+                   wp=None if wp is None else I.f32(wp[None]), motor_cmd=None if cmd is None else I.f32(cmd))
+
+
+@pytest.mark.parametrize("n", [1, 300])
+def test_aircraft_nearly_at_rest(oracle, torch_dev, n):
+    """Airspeeds down to the smallest subnormal, commanded to stop, wings
+    level (the course rate g tan(bank) / V is zero whatever V is, so the
+    heading stays what it is) or at banks as small as their speeds (a
+    quotient of two subnormals of some rad/s).  Speeds of 1e-39 m/s keep 19
+    bits, so 20 steps' roundings of speed and bank are 20 x 2^-20 x the
+    0.2 rad turned at most, well inside the tolerance."""
+    r = np.random.default_rng(n)
+    x = np.zeros((7, n))
+    x[0:3] = r.uniform(10.0, 60.0, (3, n))
+    x[3] = 10.0 ** r.uniform(-39.0, -36.0, n)
+    x[5] = x[3] * r.uniform(-1.0, 1.0, n)
+    level = np.arange(n) % 3 == 1
+    x[3, level] = 10.0 ** r.uniform(-44.0, 1.0, int(level.sum()))
+    x[5, level] = 0.0
+    x[4] = r.uniform(-3.0, 3.0, n)
+    x[6] = r.uniform(-0.1, 0.1, n)
+    sw = one_kind(2, x, cmd=np.zeros((4, n)))
+    ref = oracle_run(oracle, sw, 20)
+    for form in ("fused", "plain"):
+        got = gpu_run(torch_dev, sw, 20, form=form)
+        assert np.isfinite(got).all()
+        assert np.array_equal(got[4, level], sw.state[4, level].astype(np.float64))
+        assert_kinds_parity(got, ref, sw)
+
+
+@pytest.mark.parametrize("kind", [1, 2])
+@pytest.mark.parametrize("far", [0.9e19, 1.2e19])
+def test_orbits_beyond_the_reciprocals_range(oracle, torch_dev, kind, far):
+    """Agents so far from their orbit that the course error's product of
+    complex numbers exceeds 2^126, whose reciprocal is no normal number: they
+    still steer towards it."""
+    r = np.random.default_rng(int(far / 1e18) + kind)
+    n = 500
+    rho = 25.0 if kind == 1 else 80.0
+    th, off = r.uniform(-np.pi, np.pi, n), r.uniform(-0.25, 0.25, n)
+    x = np.zeros((7, n))
+    x[0:2] = far * r.uniform(0.97, 1.03, n) * np.stack([np.cos(th), np.sin(th)])
+    x[2] = 50.0
+    x[3] = 15.0
+    x[4] = th + np.pi + off
+    wp = np.zeros((3, n))
+    wp[2] = 50.0
+    sw = one_kind(kind, x, wp=wp, rho=rho, k_orb=rho)
+    ref = oracle_run(oracle, sw, 20)
+    assert (np.abs(ref[5]) > 1e-3).mean() > 0.5              # they do steer
+    assert_kinds_parity(gpu_run(torch_dev, sw, 20), ref, sw)
+
+
+def test_vehicles_that_are_not_finite_keep_to_themselves(torch_dev):
+    """NaN and infinite rows (speed, heading, actuator, flight path, position)
+    of cars and aircraft: those agents stay not finite, and every other agent
+    of their waves has the bits it has without them."""
+    r = np.random.default_rng(6)
+    sw = I.config_kinds(n=3000, n_steps=100)
+    veh = np.where(agent_kinds(sw) != 0)[0]
+    bad = r.choice(veh, 300, replace=False)
+    state = sw.state.copy()
+    for k, i in enumerate(bad):
+        state[(3, 4, 5, 0, 1)[k % 5], i] = (np.nan, np.inf, -np.inf)[k % 3]
+    clean = gpu_run(torch_dev, sw, 100)
+    got = gpu_run(torch_dev, sw, 100, state=state)
+    rest = np.setdiff1d(np.arange(sw.n), bad)
+    assert np.array_equal(got[:, rest], clean[:, rest])
+    assert (~np.isfinite(got[0:7, bad])).any(axis=0).all()
+    assert np.array_equal(got, gpu_run(torch_dev, sw, 100, state=state, form="plain"), equal_nan=True)
