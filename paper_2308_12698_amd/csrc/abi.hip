@@ -171,6 +171,7 @@ Limits make_limits(const potato_limits& L, float dt) {
     r.dt = dt;
     r.half_dt = 0.5f * dt;
     r.dt6 = dt / 6.0f;
+    r.dt6_lo = (float)((double)dt / 6.0 - (double)r.dt6);
     r.quarter_dt = 0.5f * r.half_dt;
     r.dt12 = 0.5f * r.dt6;
     r.inv_dt = 1.0f / dt;

@@ -84,11 +84,23 @@ __device__ __forceinline__ float quotient(float n, float d) {
  * time step does not come below 1e-35). */
 __device__ __forceinline__ bool ordinary_speed(float v) { return fabsf(v) >= 1e-20f && fabsf(v) <= 1e20f; }
 
+/* Taylor polynomials of the sine and cosine of r, at most pi/4 and a little:
+ * sin r = r + r^3 ps, cos r = 1 + r^2 pc (through r^9 and r^10: truncation
+ * below 3e-9 and 2e-9).  Returns r^2. */
+__device__ __forceinline__ float sincos_series(float r, float& ps, float& pc) {
+#pragma clang fp contract(off)
+    const float r2 = r * r;
+    ps = POTATO_FMA(r2, POTATO_FMA(r2, POTATO_FMA(r2, 1.0f / 362880.0f, -1.0f / 5040.0f), 1.0f / 120.0f), -1.0f / 6.0f);
+    pc = POTATO_FMA(r2, POTATO_FMA(r2, POTATO_FMA(r2, POTATO_FMA(r2, -1.0f / 3628800.0f, 1.0f / 40320.0f), -1.0f / 720.0f), 1.0f / 24.0f), -0.5f);
+    return r2;
+}
+
 /* sin and cos of a, |a| <= kTrigMax: a - k pi/2 for the nearest k with pi/2
  * in three parts (Cody and Waite, Software Manual for the Elementary
  * Functions, 1980; each step a fused multiply-add, the first one exact),
- * then the Taylor polynomials of the remainder, at most pi/4 and a little
- * (through r^9 and r^10: truncation below 3e-9 and 2e-9). */
+ * then the series of the remainder.  Against 64 bits, 4 million angles
+ * within 6 rad: 1.42 ulp at most, 0.28 and 0.31 in the mean (the library's
+ * sincosf: 1.45 and 1.54, 0.29 and 0.32). */
 constexpr float kTrigMax = 1e5f;
 __device__ __forceinline__ void sincos_near(float a, float& s, float& c) {
 #pragma clang fp contract(off)
@@ -96,9 +108,8 @@ __device__ __forceinline__ void sincos_near(float a, float& s, float& c) {
     float r = POTATO_FMA(-k, 1.5707963705062866f, a);
     r = POTATO_FMA(-k, -4.371138828673793e-08f, r);
     r = POTATO_FMA(-k, -1.7151245100058819e-15f, r);
-    const float r2 = r * r;
-    const float ps = POTATO_FMA(r2, POTATO_FMA(r2, POTATO_FMA(r2, 1.0f / 362880.0f, -1.0f / 5040.0f), 1.0f / 120.0f), -1.0f / 6.0f);
-    const float pc = POTATO_FMA(r2, POTATO_FMA(r2, POTATO_FMA(r2, POTATO_FMA(r2, -1.0f / 3628800.0f, 1.0f / 40320.0f), -1.0f / 720.0f), 1.0f / 24.0f), -0.5f);
+    float ps, pc;
+    const float r2 = sincos_series(r, ps, pc);
     const float sr = POTATO_FMA(r * r2, ps, r), cr = POTATO_FMA(r2, pc, 1.0f);
     const uint32_t q = (uint32_t)(int32_t)k;
     const bool odd = (q & 1u) != 0;
@@ -107,11 +118,34 @@ __device__ __forceinline__ void sincos_near(float a, float& s, float& c) {
     c = __uint_as_float(__float_as_uint(odd ? sr : cr) ^ cs);
 }
 
+/* tan a, |a| <= kTrigMax, with one division, numerator and denominator being
+ * the sine and cosine of the remainder as sums of two numbers each: 1.32 ulp
+ * at most, 0.26 in the mean (tanf: 1.32 and 0.28; the quotient of the rounded
+ * sine and cosine: 2.2 and 0.42). */
+__device__ __forceinline__ float tan_near(float a) {
+#pragma clang fp contract(off)
+    const float k = rintf(a * 0.6366197466850281f);
+    const float t = POTATO_FMA(-k, 1.5707963705062866f, a);
+    const float r = POTATO_FMA(-k, -4.371138828673793e-08f, t);
+    const float lo = POTATO_FMA(-k, -1.7151245100058819e-15f, POTATO_FMA(-k, -4.371138828673793e-08f, t - r));
+    float ps, pc;
+    const float r2 = sincos_series(r, ps, pc);
+    const float ds = POTATO_FMA(r * r2, ps, lo), dc = POTATO_FMA(r2, pc, -(r * lo));
+    const float s = r + ds, c = 1.0f + dc;
+    const float s_lo = (r - s) + ds, c_lo = (1.0f - c) + dc;
+    const bool odd = ((uint32_t)(int32_t)k & 1u) != 0;
+    const float n = odd ? -c : s, n_lo = odd ? -c_lo : s_lo, d = odd ? s : c, d_lo = odd ? s_lo : c_lo;
+    const float rd = __builtin_amdgcn_rcpf(d);
+    const float q = n * rd;
+    return POTATO_FMA(POTATO_FMA(-q, d_lo, POTATO_FMA(-d, q, n) + n_lo), rd, q);
+}
+
 /* Angle of the vector (x, y), as atan2(y, x), for a vector other than
  * (0, 0) with the larger coordinate from 1e-37 to 1e37: the smaller
  * coordinate over the larger, moved by pi/4 where it exceeds tan(pi/8) (both
  * within one division), and the arctangent's series through r^17 (truncation
- * below 3e-9 for |r| <= tan(pi/8)).  NaN for a NaN coordinate. */
+ * below 3e-9 for |r| <= tan(pi/8)).  NaN for a NaN coordinate.  2.27 ulp at
+ * most, 0.38 in the mean (atan2f: 2.76 and 0.43). */
 __device__ __forceinline__ float vector_angle(float y, float x) {
 #pragma clang fp contract(off)
     const float ax = fabsf(x), ay = fabsf(y);
@@ -154,10 +188,8 @@ __device__ __forceinline__ void veh_trig(const float x[7], VehTrig& T) {
                                         : fmaxf(fabsf(x[4]), fabsf(x[5]));
     const bool nan = !(x[4] == x[4]) || !(x[5] == x[5]) || (KIND == KIND_WING && !(x[6] == x[6]));
     if (far <= kTrigMax && !nan) {
-        float sa, ca;
         sincos_near(x[4], T.sh, T.ch);
-        sincos_near(x[5], sa, ca);
-        T.ta = quotient(sa, ca);
+        T.ta = tan_near(x[5]);
         if (KIND == KIND_WING) sincos_near(x[6], T.sg, T.cg);
     } else {
         sincosf(x[4], &T.sh, &T.ch);
@@ -260,7 +292,12 @@ __device__ __forceinline__ void veh_guidance(const VehConst& c, const float x[7]
                                              float u[3]) {
 #pragma clang fp contract(off)
     const float ex = x[0] - wp[0], ey = x[1] - wp[1];
-    const float u0 = c.k_orb_rho * (sqrt_fast(POTATO_FMA(ey, ey, ex * ex)) - c.rho);
+    /* distance from the orbit's centre: the square root with one correction
+     * by its exact residual, the library's rounding (NaN at the centre and at
+     * infinity, which take the general form below) */
+    const float d2 = POTATO_FMA(ey, ey, ex * ex);
+    const float rd = rsq(d2), d0 = d2 * rd;
+    const float u0 = c.k_orb_rho * (POTATO_FMA(POTATO_FMA(-d0, d0, d2), 0.5f * rd, d0) - c.rho);
     /* course error: course command minus the car's course (its yaw plus the
      * side-slip angle) or the aircraft's, in [-pi, pi]: the angle of the
      * product of the complex numbers whose angles add up to it, ex + i ey,
@@ -283,7 +320,8 @@ __device__ __forceinline__ void veh_guidance(const VehConst& c, const float x[7]
         /* another lambda, the orbit's centre, very far, infinities: angle by angle
          * (the heading without its whole turns, whose rounding would be that
          * of the difference) */
-        const float chi_d = POTATO_FMA(c.lam, atanf(u0), atan2f(ey, ex) + c.lam_half_pi);
+        const float uf = c.k_orb_rho * (sqrtf(d2) - c.rho);
+        const float chi_d = POTATO_FMA(c.lam, atanf(uf), atan2f(ey, ex) + c.lam_half_pi);
         const float course = atan2f(T.sh, T.ch);
         e = wrap_pi(chi_d - (KIND == KIND_CAR ? course + atanf(c.lr_L * T.ta) : course));
     }
@@ -305,7 +343,12 @@ __device__ __forceinline__ void veh_guidance(const VehConst& c, const float x[7]
  * state x whose angles' functions are T; CARRY: every integrated row keeps
  * its rounding carry in lo (the heading matters most: it grows by nearly
  * equal increments every step, and a rounding bias of its updates would be
- * cancelled by a steady steering or bank offset). */
+ * cancelled by a steady steering or bank offset).  The increment dt/6 times
+ * the sum of the rates is not rounded before it meets the carry, and dt/6 is
+ * taken in two parts: its rounding alone moves an aircraft by half an ulp of
+ * the way flown.  Mean position error after 500 steps of 1 ms, against 64
+ * bits: aircraft 2.1e-7 -> 0.8e-7 m, cars 4.8e-8 -> 1.3e-8 (at the cost of
+ * the multiplication and addition that the two fused ones replace). */
 template <int KIND, bool CARRY>
 __device__ __forceinline__ void veh_rk4(const VehConst& c, const Limits& L, float x[7], const VehTrig& T, float lo[7],
                                         const float u[3]) {
@@ -352,7 +395,14 @@ __device__ __forceinline__ void veh_rk4(const VehConst& c, const Limits& L, floa
 #pragma unroll
     for (int i = 0; i < 7; ++i) {
         if (!veh_row<KIND>(i)) continue;
-        add_carry<CARRY>(x[i], lo[i], L.dt6 * acc[i]);
+        if (CARRY) {
+            const float y = POTATO_FMA(L.dt6, acc[i], POTATO_FMA(L.dt6_lo, acc[i], lo[i]));
+            const float s = x[i] + y;
+            lo[i] = y - (s - x[i]);
+            x[i] = s;
+        } else {
+            x[i] = POTATO_FMA(L.dt6, acc[i], x[i]);
+        }
     }
 }
 
