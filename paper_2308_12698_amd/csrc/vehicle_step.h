@@ -33,7 +33,7 @@
  * trigonometric functions of the angles are evaluated once per step, at
  * the step-start state, and carried to each RK4 stage's angles by the
  * angle-sum formulas with short series for the stage's small offset
- * (veh_trig_near, veh_trig_far); the course error is the angle of one product of complex numbers
+ * (veh_trig_near); the course error is the angle of one product of complex numbers
  * (one arctangent instead of two or three); divisions by
  * the time constants, the wheelbase and g rho are multiplications by
  * reciprocals precomputed per type; the car's steering feed-forward is a
@@ -46,10 +46,10 @@
  * sine, tangent, arctangent and division (large-argument branches, full
  * special-case sequences) made a step of several hundred instructions more
  * than the functions written here, which keep the library's as the rare
- * branch: a car's step is now about 325 vector instructions and an
- * aircraft's 430, in straight lines (a quadrotor's 525).  Mixed kinds in
- * the type order, us per step before and after: 2.53 and 1.71 at 3,000
- * agents, 6.11 and 5.70 at 524,288, 10.25 and 9.28 at 1,048,576.
+ * branch: a car's step is now 327 vector instructions and an aircraft's 439
+ * (262,144 agents each), in straight lines (a quadrotor's 525).  Mixed kinds
+ * in the type order, us per step before and after: 2.57 and 1.72 at 3,000
+ * agents, 6.03 and 5.37 at 524,288, 11.4 and 9.8 at 1,048,576.
  */
 #pragma once
 
@@ -201,55 +201,28 @@ __device__ __forceinline__ void veh_trig(const float x[7], VehTrig& T) {
 /* The angles' functions at a stage state x0 + offsets d (h k of the previous
  * stage's rates) from those at x0: sin and cos by the angle-sum formulas,
  * tan(a0 + d) as (t0 + tan d) / (1 - t0 tan d), with sin d, cos d - 1 and
- * tan d from their Taylor series.  NEAR: offsets of at most 0.02 rad, as
- * every ordinary time step gives, and series through d^3, d^4 and d^5
- * (truncation below 2e-9 of sin d and tan d, 1e-13 of cos d); false when an
- * offset is larger or NaN. */
+ * tan d from their Taylor series through d^5, d^6 and d^7: truncation below
+ * 2e-11, 3e-13 and 3e-11 at kNearOffset, past FP32 rounding.  False when an
+ * offset is larger. */
+constexpr float kNearOffset = 0.1f;
 template <int KIND>
 __device__ __forceinline__ bool veh_trig_near(const VehTrig& T0, float d4, float d5, float d6, VehTrig& T) {
 #pragma clang fp contract(off)
     auto shift = [](float s0, float c0, float d, float& s, float& c) {
         const float d2 = d * d;
-        const float sd = POTATO_FMA(d * d2, -1.0f / 6.0f, d);
-        const float cm = d2 * POTATO_FMA(d2, 1.0f / 24.0f, -0.5f);
+        const float sd = POTATO_FMA(d * d2, POTATO_FMA(d2, 1.0f / 120.0f, -1.0f / 6.0f), d);
+        const float cm = d2 * POTATO_FMA(d2, POTATO_FMA(d2, -1.0f / 720.0f, 1.0f / 24.0f), -0.5f);
         s = POTATO_FMA(c0, sd, POTATO_FMA(s0, cm, s0));
         c = POTATO_FMA(-s0, sd, POTATO_FMA(c0, cm, c0));
     };
     shift(T0.sh, T0.ch, d4, T.sh, T.ch);
     if (KIND == KIND_WING) shift(T0.sg, T0.cg, d6, T.sg, T.cg);
     const float q2 = d5 * d5;
-    const float td = d5 * POTATO_FMA(q2, POTATO_FMA(q2, 2.0f / 15.0f, 1.0f / 3.0f), 1.0f);
-    const float den = POTATO_FMA(-T0.ta, td, 1.0f);
-    T.ta = quotient(T0.ta + td, den);
-    const float far = KIND == KIND_WING ? fabsf(d4) + fabsf(d6) : fabsf(d4);
-    return far + fabsf(d5) <= 0.02f && den >= 0.5f;
-}
-
-/* The same for any offset: longer series up to 0.3 rad (0.1 of the tangent),
- * the library's functions of the new angles beyond (very long time steps). */
-template <int KIND>
-__device__ __forceinline__ void veh_trig_far(const float x0[7], const VehTrig& T0, float d4, float d5, float d6,
-                                             VehTrig& T) {
-#pragma clang fp contract(off)
-    auto shift = [](float s0, float c0, float d, float& s, float& c) {
-        const float d2 = d * d;
-        const float sd = POTATO_FMA(d * d2, POTATO_FMA(d2, POTATO_FMA(d2, -1.0f / 5040.0f, 1.0f / 120.0f), -1.0f / 6.0f), d);
-        const float cm = d2 * POTATO_FMA(d2, POTATO_FMA(d2, POTATO_FMA(d2, 1.0f / 40320.0f, -1.0f / 720.0f), 1.0f / 24.0f), -0.5f);
-        s = POTATO_FMA(c0, sd, POTATO_FMA(s0, cm, s0));
-        c = POTATO_FMA(-s0, sd, POTATO_FMA(c0, cm, c0));
-    };
-    const float q2 = d5 * d5;
     const float td = d5 * POTATO_FMA(q2, POTATO_FMA(q2, POTATO_FMA(q2, 17.0f / 315.0f, 2.0f / 15.0f), 1.0f / 3.0f), 1.0f);
     const float den = POTATO_FMA(-T0.ta, td, 1.0f);
-    if (fabsf(d4) <= 0.3f && fabsf(d5) <= 0.1f && den >= 0.5f && (KIND != KIND_WING || fabsf(d6) <= 0.3f)) {
-        shift(T0.sh, T0.ch, d4, T.sh, T.ch);
-        T.ta = quotient(T0.ta + td, den);
-        if (KIND == KIND_WING) shift(T0.sg, T0.cg, d6, T.sg, T.cg);
-    } else {
-        sincosf(x0[4] + d4, &T.sh, &T.ch);
-        T.ta = tanf(x0[5] + d5);
-        if (KIND == KIND_WING) sincosf(x0[6] + d6, &T.sg, &T.cg);
-    }
+    T.ta = quotient(T0.ta + td, den);
+    const float far = fmaxf(fmaxf(fabsf(d4), fabsf(d5)), KIND == KIND_WING ? fabsf(d6) : 0.0f);
+    return far <= kNearOffset && den >= 0.5f;
 }
 
 /* Rates of rows 0-6 at state x (its angles' functions in T) with inputs u
@@ -339,6 +312,8 @@ __device__ __forceinline__ void veh_guidance(const VehConst& c, const float x[7]
     }
 }
 
+constexpr float kNearStep = 0.06f;
+
 /* Classical RK4 over rows 0-6 with the inputs held, from the step-start
  * state x whose angles' functions are T; CARRY: every integrated row keeps
  * its rounding carry in lo (the heading matters most: it grows by nearly
@@ -367,18 +342,30 @@ __device__ __forceinline__ void veh_rk4(const VehConst& c, const Limits& L, floa
 #pragma unroll
         for (int i = 0; i < 7; ++i) acc[i] = POTATO_FMA(weight, k[i], acc[i]);
     };
-    /* straight through; an agent with an offset too large for it, or an
-     * aircraft nearly at rest, takes the step again, one copy of its code */
-    bool near = KIND != KIND_WING || ordinary_speed(x[3]);
-    veh_rates<KIND, false>(c, x, T, u, k);
-    start();
+    /* Straight through, the stages' functions from those of the step's start.
+     * An agent with an offset too large for that, or an aircraft nearly at
+     * rest, takes the step again, every stage's functions from its own angles
+     * (one copy of that code), and so do all agents at once where the time
+     * step makes such offsets common: a step of both forms takes 1.5 of
+     * either.  us per step of 500,000 cars and aircraft turning towards their
+     * orbits: 4.0 and 5.2 at steps of 1 to 20 ms, 4.1 and 5.9 at 50 ms, 5.6
+     * and 7.3 at 250 ms (with series for offsets of 0.02 rad at most, the
+     * three stages twice beyond: 3.9 and 5.1 at 1 ms, but 5.9 and 6.4 at 20
+     * ms and 7.0 and 9.9 at 250 ms; with the library's functions throughout
+     * 4.9 and 6.3, 5.8 and 7.5 at 250 ms). */
+    bool near = L.dt <= kNearStep;
+    if (near) {
+        veh_rates<KIND, false>(c, x, T, u, k);
+        start();
 #pragma unroll
-    for (int st = 0; st < 3; ++st) {
-        const float h = st < 2 ? L.half_dt : L.dt;
-        advance(h);
-        near = veh_trig_near<KIND>(T, h * k[4], h * k[5], h * k[6], Ts) && near;
-        veh_rates<KIND, false>(c, xs, Ts, u, k);
-        add(st < 2 ? 2.0f : 1.0f);
+        for (int st = 0; st < 3; ++st) {
+            const float h = st < 2 ? L.half_dt : L.dt;
+            advance(h);
+            near = veh_trig_near<KIND>(T, h * k[4], h * k[5], h * k[6], Ts) && near;
+            veh_rates<KIND, false>(c, xs, Ts, u, k);
+            add(st < 2 ? 2.0f : 1.0f);
+        }
+        if (KIND == KIND_WING) near = near && ordinary_speed(x[3]);
     }
     if (!near) {
         veh_rates<KIND, true>(c, x, T, u, k);
@@ -387,7 +374,7 @@ __device__ __forceinline__ void veh_rk4(const VehConst& c, const Limits& L, floa
         for (int st = 0; st < 3; ++st) {
             const float h = st < 2 ? L.half_dt : L.dt;
             advance(h);
-            veh_trig_far<KIND>(x, T, h * k[4], h * k[5], h * k[6], Ts);
+            veh_trig<KIND>(xs, Ts);
             veh_rates<KIND, true>(c, xs, Ts, u, k);
             add(st < 2 ? 2.0f : 1.0f);
         }
