@@ -158,7 +158,7 @@ hipError_t launch_adjoint(bool het, bool gains, bool perm, bool pipe, const AdjA
                           hipStream_t stream);
 size_t adjoint_lds_bytes(bool het, int n_types, bool pipe);
 
-/* Launches whose tape (the 22 rows that every step writes and reads) does
+/* Launches whose tape (the 23 rows that every step writes and reads) does
  * not fit the 256 MB Infinity Cache with room to spare read it with loads
  * that leave the cache to the slots still to come: per step 3.36 -> 3.33 us
  * at 65,536 agents with 50 steps per segment, 3.28 -> 2.97 with 20 (231 MB),

@@ -946,7 +946,7 @@ const void* adjoint_kernel(bool het, bool gains, bool perm, bool pipe, bool stre
 }
 
 bool adjoint_streams(bool pipe, const AdjArgs& a) {
-    const int64_t bytes = (int64_t)a.K * kTapeInt * (int64_t)sizeof(float) * a.tape_ld;
+    const int64_t bytes = (int64_t)a.K * (kTapeInt + 1) * (int64_t)sizeof(float) * a.tape_ld;
     return bytes > kStreamTapeBytes && (pipe || a.n > a.tape_ld);
 }
 

@@ -12,10 +12,10 @@
  * took: a clamp passes the cotangent inside its interval and stops it
  * outside; the error-quaternion sign is a constant; sqrt'(0) is taken as 0.
  * The branches are the forward's own decisions, recorded by the replay of
- * the forward from its checkpoints (the same bits), as are the integrals
- * after their update and the rotor command held through the step; the
- * reverse sweep does not decide any branch itself.  The rounding carries of the forward integrator are not
- * differentiated (the represented value is row + carry, so both have the
+ * the forward from its checkpoints (the same bits), as is the rotor command
+ * held through the step; the controller's integrals are the forward's too, bit
+ * for bit (undo).  The reverse sweep does not decide any branch itself.  The
+ * rounding carries of the forward integrator are not differentiated (the represented value is row + carry, so both have the
  * same cotangent).
  */
 #pragma once
@@ -113,13 +113,24 @@ __device__ __forceinline__ float where(int32_t mask, float x) {
  * and the branch decisions (kBit*). */
 struct Replay {
     float p[3], v[3], q[4], w[3], d[4], ip[3], ia[3], ir[3], dw[3], dc[4];
-    uint32_t bits;
+    uint32_t bits, off;                       /* kBit*, undo offsets */
 };
+
+/* Where the undo offsets are: six in a word of their own, three above the
+ * branch decisions, and above those whether the tape holds the integrals
+ * themselves in their place. */
+constexpr int kUndoWord = 6;
+constexpr int kUndoAt = 16;
+constexpr uint32_t kWholeBit = 1u << 31;
+static_assert(kUndoWord * kUndoBits <= 32 && kUndoAt + (9 - kUndoWord) * kUndoBits <= 31, "the offsets' places");
+__device__ __forceinline__ uint32_t packed_offset(const Replay& a, int k) {
+    return (k < kUndoWord ? a.off >> (kUndoBits * k) : a.bits >> (kUndoAt + kUndoBits * (k - kUndoWord))) & kUndoMax;
+}
 
 /*
  * Reverse of one step.  `a` is its replay, wp the waypoint of this step and
  * k the gains; on return a.ip, a.ia and a.ir are the integrals before the
- * step, as far as they can be told from those after it (see kRefresh).  lam
+ * step where the undo offsets hold them (not kWholeBit).  lam
  * holds the cotangent of
  * the step-end state on entry and of the step-start state on return; gk
  * accumulates the gain cotangents, the last one (kdr) times dt: gk[8] is
@@ -318,7 +329,7 @@ __device__ __forceinline__ void step_vjp(const TypeConst& c, const Limits& L, co
         /* rate loop, and w_prev <- w */
         gk[6] = POTATO_FMA(lal[i], erate, gk[6]);
         gk[7] = POTATO_FMA(lal[i], a.ir[i], gk[7]);
-        a.ir[i] = POTATO_FMA(-erate, L.dt, a.ir[i]);
+        a.ir[i] = undo(a.ir[i], erate, L.dt, packed_offset(a, 6 + i));
         gk[8] = POTATO_FMA(-lal[i], a.dw[i], gk[8]);
         const float l_dw = k.kdr_dt * lal[i];
         const float lw = (lam.w[i] + lam.wprev[i]) - l_dw;
@@ -328,7 +339,7 @@ __device__ __forceinline__ void step_vjp(const TypeConst& c, const Limits& L, co
         /* attitude loop, erate = wdes - w */
         gk[3] = POTATO_FMA(l_er, eatt[i], gk[3]);
         gk[4] = POTATO_FMA(l_er, a.ia[i], gk[4]);
-        a.ia[i] = POTATO_FMA(-eatt[i], L.dt, a.ia[i]);
+        a.ia[i] = undo(a.ia[i], eatt[i], L.dt, packed_offset(a, 3 + i));
         gk[5] = POTATO_FMA(-l_er, a.w[i], gk[5]);
         lam.w[i] = POTATO_FMA(-kda1, l_er, lw);
         lam.ia[i] = where(in_ia[i], POTATO_FMA(k.kia, l_er, lam.ia[i]));
@@ -366,7 +377,7 @@ __device__ __forceinline__ void step_vjp(const TypeConst& c, const Limits& L, co
     for (int i = 0; i < 3; ++i) {
         gk[0] = POTATO_FMA(la[i], e[i], gk[0]);
         gk[1] = POTATO_FMA(la[i], a.ip[i], gk[1]);
-        a.ip[i] = POTATO_FMA(-e[i], L.dt, a.ip[i]);
+        a.ip[i] = undo(a.ip[i], e[i], L.dt, packed_offset(a, i));
         gk[2] = POTATO_FMA(-la[i], a.v[i], gk[2]);
         lam.v[i] = POTATO_FMA(-k.kdp, la[i], lam.v[i]);
         lam.ip[i] = where(in_ip[i], POTATO_FMA(k.kip, la[i], lam.ip[i]));
@@ -466,35 +477,48 @@ __device__ __forceinline__ float tape_load(const float& x) {
 }
 
 /* The integrals before a step are on the tape only where they are needed:
- * the reverse sweep knows those after the step, and where no clamp acted
- * those before it are less the step's increment.  Each such subtraction
- * rounds once, so every agent takes them from the tape at each step whose
- * call-relative index k is a multiple of kRefresh, and an agent at a clamp
- * takes that integral from it at that step (the wave then holds the rows for
- * all its agents).  Nothing of this depends on where segments end or on the
- * other agents of the wave.  One step in kRefresh writes and reads 9 rows
- * more than the other 22 (179 B per agent-step instead of 248; kRefresh =
- * 16 leaves at most 16 half-ulp roundings between two refreshes). */
-constexpr int kRefresh = 16;
+ * the reverse sweep knows those after the step, and undo() gives those before
+ * it from them with a few bits each, exactly the forward's, as if they were
+ * on the tape (23 rows per step instead of 30; backward of 300,007 agents
+ * 16.6 to 14.3-14.9 us per step, of 1,048,576 56 to 51-53).  Where an agent's
+ * offsets do not fit or it is at a clamp, the wave writes the nine rows
+ * themselves, the first in the place of the offsets' word. */
 constexpr uint32_t kBitInt = 7u << (kBitIp - 2) | 0x3fu << (kBitIr - 4);   /* inside all nine clamps */
-__device__ __forceinline__ bool integrals_on_tape(int k, uint32_t bits) {
-    return k % kRefresh == 0 || __ballot((bits & kBitInt) != kBitInt) != 0;
-}
 
 /* A tape slot: the step-start state (rows 0-16: p, v, q, w, rotors), the
- * held command and the branch decisions. */
+ * held command, the branch decisions, and the undo offsets or the integrals. */
 __device__ __forceinline__ void store_tape(float* slot, uint32_t lb, const Agent& a, const float dc[4],
-                                           uint32_t bits) {
+                                           const WayBack& b, const float before[9]) {
     const TapeRows<float> t(slot);
     auto row = [&](int k) -> float& { return elem(t.row(k), lb); };
+    uint32_t wide = 0;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) wide |= b.off[k];
+    const bool whole = __ballot(wide > kUndoMax || (b.bits & kBitInt) != kBitInt) != 0;
+    uint32_t bits = b.bits, word = 0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) { row(k) = a.p[k]; row(3 + k) = a.v[k]; row(10 + k) = a.w[k]; }
 #pragma unroll
     for (int k = 0; k < 4; ++k) { row(6 + k) = a.q[k]; row(13 + k) = a.d[k]; row(kTapeCmd + k) = dc[k]; }
+    if (whole) {
+        bits |= kWholeBit;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) row(kTapeInt + k) = before[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            if (k < kUndoWord)
+                word |= b.off[k] << (kUndoBits * k);
+            else
+                bits |= b.off[k] << (kUndoAt + kUndoBits * (k - kUndoWord));
+        }
+        row(kTapeInt) = __uint_as_float(word);
+    }
     row(kTapeBits) = __uint_as_float(bits);
 }
 
-/* The same without the body rates, which the step after has read already. */
+/* The same without the body rates, which the step after has read already;
+ * integrals on the tape come with load_tape_integrals. */
 template <bool STREAM>
 __device__ __forceinline__ void load_tape(const float* slot, uint32_t lb, Replay& a) {
     const TapeRows<const float> t(slot);
@@ -504,20 +528,15 @@ __device__ __forceinline__ void load_tape(const float* slot, uint32_t lb, Replay
 #pragma unroll
     for (int k = 0; k < 4; ++k) { a.q[k] = row(6 + k); a.d[k] = row(13 + k); a.dc[k] = row(kTapeCmd + k); }
     a.bits = __float_as_uint(row(kTapeBits));
+    a.off = __float_as_uint(row(kTapeInt));
 }
 
-/* The integrals before step k that the agent takes from the tape. */
-__device__ __forceinline__ void load_tape_integrals(const float* slot, uint32_t lb, int k, Replay& a) {
+/* The integrals before the step, where the tape holds them. */
+__device__ __forceinline__ void load_tape_integrals(const float* slot, uint32_t lb, Replay& a) {
     const TapeRows<const float> t(slot);
     auto row = [&](int r) { return elem(t.row(kTapeInt + r), lb); };
-    const bool all = k % kRefresh == 0;
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        const float ip = row(r), ia = row(3 + r), ir = row(6 + r);
-        a.ip[r] = all || !(a.bits >> (kBitIp - r) & 1u) ? ip : a.ip[r];
-        a.ia[r] = all || !(a.bits >> (kBitIa - 2 * r) & 1u) ? ia : a.ia[r];
-        a.ir[r] = all || !(a.bits >> (kBitIr - 2 * r) & 1u) ? ir : a.ir[r];
-    }
+    for (int r = 0; r < 3; ++r) { a.ip[r] = row(r); a.ia[r] = row(3 + r); a.ir[r] = row(6 + r); }
 }
 
 /* Body rates at the start of a step: rows 10-12 of a tape slot. */
@@ -541,31 +560,26 @@ __device__ __forceinline__ void step_wprev(const float* tape, int64_t tape_step,
     }
 }
 
-/* Recomputed forward step k of the call: its start state, held command and
- * branch decisions go to the tape slot, then the state advances (the forward
- * pass's own arithmetic, carries included, so the same bits). */
-__device__ __forceinline__ void recompute_step(const TypeConst& c, const Limits& L, const Gains& g, Agent& a, int k,
+/* Recomputed forward step: what its reverse needs goes to the tape slot,
+ * then the state advances (the forward pass's own arithmetic, carries
+ * included, so the same bits). */
+__device__ __forceinline__ void recompute_step(const TypeConst& c, const Limits& L, const Gains& g, Agent& a,
                                                const float wp[3], float* slot, uint32_t lb) {
     float dc[4], before[9];
-    uint32_t bits;
+    WayBack back;
 #pragma unroll
     for (int r = 0; r < 3; ++r) { before[r] = a.ip[r]; before[3 + r] = a.ia[r]; before[6 + r] = a.ir[r]; }
-    controller<true, true>(c, L, g, a, wp, dc, &bits);
-    store_tape(slot, lb, a, dc, bits);
-    if (integrals_on_tape(k, bits)) {
-        const TapeRows<float> t(slot);
-#pragma unroll
-        for (int r = 0; r < 9; ++r) elem(t.row(kTapeInt + r), lb) = before[r];
-    }
+    controller<true, true>(c, L, g, a, wp, dc, &back);
+    store_tape(slot, lb, a, dc, back, before);
     rk4_step(c, L, a, dc);
 }
 
-/* Reverse of step s of a segment from the tape, step k of the call.  x
+/* Reverse of step s of a segment from the tape.  x
  * carries the integrals after the step and w the body rates at its start,
  * both from the step after it; they come back as those of the step before. */
 template <bool STREAM>
 __device__ __forceinline__ void reverse_step(const TypeConst& c, const Limits& L, const Gains& g, Replay& x,
-                                             float w[3], int s, int k, const float wp[3], const float* tape,
+                                             float w[3], int s, const float wp[3], const float* tape,
                                              int64_t tape_step, uint32_t lb, const float* ckpt_seg, int64_t ld,
                                              uint32_t bo, AgentAdj& lam, float gk[9]) {
     const float* const slot = tape + (int64_t)s * tape_step;
@@ -577,7 +591,7 @@ __device__ __forceinline__ void reverse_step(const TypeConst& c, const Limits& L
     step_vjp(c, L, g, x, wp, lam, gk);
 #pragma unroll
     for (int r = 0; r < 3; ++r) w[r] = wprev[r];
-    if (integrals_on_tape(k, x.bits)) load_tape_integrals(slot, lb, k, x);
+    if (x.bits & kWholeBit) load_tape_integrals(slot, lb, x);
 }
 
 /*
@@ -637,7 +651,7 @@ __device__ __forceinline__ void agent_backward(const TypeConst& c, const Limits&
         for (int s = 0; s < len; ++s) {
             if (k0 + s == next) { ++e; next += period; }
             use_epoch(e);
-            recompute_step(c, L, g, a, k_begin + s, wpv, tape + (int64_t)s * tape_step, lb);
+            recompute_step(c, L, g, a, wpv, tape + (int64_t)s * tape_step, lb);
         }
         /* reverse: start from the epoch of the segment's last step */
         e = resample > 0 ? (k0 + len - 1) / resample : 0;
@@ -654,7 +668,7 @@ __device__ __forceinline__ void agent_backward(const TypeConst& c, const Limits&
             if (s >= len) continue;
             if (k0 + s < first) { --e; first -= period; }
             use_epoch(e);
-            reverse_step<STREAM>(c, L, g, x, w, s, k_begin + s, wpv, tape, tape_step, lb, ck, ld, bo, lam, gk);
+            reverse_step<STREAM>(c, L, g, x, w, s, wpv, tape, tape_step, lb, ck, ld, bo, lam, gk);
         }
     }
 }
@@ -699,7 +713,7 @@ __device__ __forceinline__ void recompute_segment(const TypeConst& c, const Limi
     for (int s = 0; s < len; ++s) {
         if (k0 + s == next) { ++e; next += period; }
         wc.use(e);
-        recompute_step(c, L, g, a, k_begin + s, wc.v, tape + (int64_t)s * tape_step, lb);
+        recompute_step(c, L, g, a, wc.v, tape + (int64_t)s * tape_step, lb);
     }
     if (k_begin + len == steps) {              /* this lane's last segment */
 #pragma unroll
@@ -739,7 +753,7 @@ __device__ __forceinline__ void reverse_segment(const TypeConst& c, const Limits
         if (s >= len) continue;
         if (k0 + s < first) { --e; first -= period; }
         wc.use(e);
-        reverse_step<STREAM>(c, L, g, x, w, s, k_begin + s, wc.v, tape, tape_step, lb, ck, ld, bo, lam, gk);
+        reverse_step<STREAM>(c, L, g, x, w, s, wc.v, tape, tape_step, lb, ck, ld, bo, lam, gk);
     }
 }
 

@@ -159,9 +159,10 @@ __device__ __forceinline__ uint32_t order_entry(const int32_t* perm, uint32_t j,
 /* Rows per step of the adjoint's recomputation tape: the step-start state
  * without its cost, previous body rates and integrals (17 rows: p, v, q, w,
  * rotors), the rotor command the controller held through the step (4), the
- * controller's branch decisions (1, bits as a float) and the three integrals
- * before the step (9), the last only where a wave holds an agent at a clamp
- * (see recompute_step). */
+ * controller's branch decisions (1, bits as a float) and what undoes the
+ * integrals' updates (1, in the first of the last 9 rows) or, in waves with an
+ * agent for which that is not enough, the integrals before the step (9); see
+ * store_tape. */
 constexpr int kTapeRows = 31;
 constexpr int kTapeCmd = 17;      /* first row of the held command */
 constexpr int kTapeBits = 21;     /* row of the branch decisions */
@@ -288,16 +289,37 @@ __device__ __forceinline__ void derivative(const TypeConst& c, const float v[3],
     dJ = c.four_w2 + ssum;
 }
 
+/* An integral's update, undone from its value after it: less the increment,
+ * which rounds once and so misses the value before by some units in the last
+ * place.  undo_offset is that difference, of kUndoBits bits around kUndoZero;
+ * with it undo returns the value before, bit for bit.  It does not fit where
+ * the integral was small against its increment (less than a sixteenth or
+ * so) or a clamp acted. */
+constexpr int kUndoBits = 5;
+constexpr uint32_t kUndoZero = 1u << (kUndoBits - 1), kUndoMax = (1u << kUndoBits) - 1;
+__device__ __forceinline__ uint32_t undo_offset(float before, float after, float e, float dt) {
+    return __float_as_uint(before) - __float_as_uint(POTATO_FMA(-e, dt, after)) + kUndoZero;
+}
+__device__ __forceinline__ float undo(float after, float e, float dt, uint32_t offset) {
+    return __uint_as_float(__float_as_uint(POTATO_FMA(-e, dt, after)) + offset - kUndoZero);
+}
+
+/* What a step leaves for its reverse: the branch decisions, and undo_offset
+ * of the nine integrals' updates (position, attitude, rate). */
+struct WayBack {
+    uint32_t bits, off[9];
+};
+
 /* Position -> attitude -> body-rate PID cascade and mixer, evaluated once
  * per step on the step-start state; returns rotor commands relative to
  * w_ref and updates the controller memory.  CARRY: the position-loop
  * integral keeps its rounding carry in a.ip_lo.  BITS: the branch
- * decisions go to *bits (kBit*; comparisons only, the arithmetic is the
- * same). */
+ * decisions go to back->bits (kBit*; comparisons only, the arithmetic is the
+ * same), and back->off says how to undo the integrals' updates (undo_offset). */
 template <bool CARRY = true, bool BITS = false, bool SPACED = false>
 __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, const Gains& k,
                                            Agent& a, const float wp[3], float dc[4],
-                                           uint32_t* bits = nullptr) {
+                                           WayBack* back = nullptr) {
 #pragma clang fp contract(off)
     /* position loop: error saturated to radius r_sat */
     float e[3] = {wp[0] - a.p[0], wp[1] - a.p[1], wp[2] - a.p[2]};
@@ -318,6 +340,7 @@ __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, 
             a.ip_lo[i] = cl == s ? lo : 0.0f;
         }
         if (BITS) push_bit(b, cl == s);
+        if (BITS) back->off[i] = undo_offset(a.ip[i], cl, e[i], L.dt);
         a.ip[i] = cl;
         acc[i] = POTATO_FMA(-k.kdp, a.v[i], POTATO_FMA(k.kip, cl, k.kpp * e[i]));
     }
@@ -350,14 +373,18 @@ __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, 
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         const float pa = POTATO_FMA(eatt[i], L.dt, a.ia[i]);
-        a.ia[i] = clampf_(pa, -L.iatt_max, L.iatt_max);
-        if (BITS) push_bit(b, a.ia[i] == pa);
+        const float ca = clampf_(pa, -L.iatt_max, L.iatt_max);
+        if (BITS) push_bit(b, ca == pa);
+        if (BITS) back->off[3 + i] = undo_offset(a.ia[i], ca, eatt[i], L.dt);
+        a.ia[i] = ca;
         const float wdes = POTATO_FMA(-k.kda, a.w[i], POTATO_FMA(k.kia, a.ia[i], k.kpa * eatt[i]));
         /* body-rate loop, derivative on the measured rate */
         const float erate = wdes - a.w[i];
         const float pr = POTATO_FMA(erate, L.dt, a.ir[i]);
-        a.ir[i] = clampf_(pr, -L.irate_max, L.irate_max);
-        if (BITS) push_bit(b, a.ir[i] == pr);
+        const float cr = clampf_(pr, -L.irate_max, L.irate_max);
+        if (BITS) push_bit(b, cr == pr);
+        if (BITS) back->off[6 + i] = undo_offset(a.ir[i], cr, erate, L.dt);
+        a.ir[i] = cr;
         alpha[i] = POTATO_FMA(-k.kdr_dt, a.w[i] - a.wprev[i], POTATO_FMA(k.kir, a.ir[i], k.kpr * erate));
         a.wprev[i] = a.w[i];
     }
@@ -378,7 +405,7 @@ __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, 
         if (BITS) push_bit(b, f[i] > 0.0f && f[i] <= c.f_max);
         dc[i] = sqrt_fast<SPACED>(fi * c.inv_kf) - c.w_ref;
     }
-    if (BITS) *bits = b;
+    if (BITS) back->bits = b;
 }
 
 /* Classical RK4 with the command held, then quaternion renormalisation.

@@ -510,3 +510,53 @@ def test_streamed_tape_gives_the_same_gradient(torch_dev, n, types):
     sim.close()
     assert torch.isfinite(out[0]).all() and out[0][30:].abs().max() > 0
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("n", [250, 70016])
+@pytest.mark.parametrize("types", [1, 8])
+@pytest.mark.parametrize("first", [1, 7, 23])
+def test_a_call_in_two_parts_has_the_bits_of_one(torch_dev, n, types, first):
+    """The reverse of step k reads the forward's integrals before it, bit for
+    bit, wherever in a call the step is: a rollout of 60 steps in one call,
+    and in calls of `first` and the rest with the second's cotangents given
+    to the first, give the same cotangents of state and memory (steps,
+    waypoint epochs and budgets counted across the calls; integrals through
+    zero, near and at their clamps, far larger and far smaller than their
+    increments).  Pipelined sweep and one agent per thread."""
+    torch, dev = torch_dev
+    from paper_2308_12698_amd.sim import Simulator
+    rng = np.random.default_rng(first + types)
+    m, steps, every = 250, 60, 20
+    table = [I.base_type()] if types == 1 else [dict(t, budget=b) for t, b in
+                                                zip(I.hetero_types(), (60, 59, 40, 24, 23, 7, 6, 1000))]
+    glob = I.globals_f32(ipos_max=0.5, iatt_max=0.05, irate_max=0.3)
+    s = I.hover_state(rng.uniform(0.0, 20.0, (3, m))).astype(np.float64)
+    s[10:13] = rng.normal(0.0, 0.5, (3, m))
+    s[17:26] = rng.uniform(-1.0, 1.0, (9, m)) * np.repeat([0.5, 0.05, 0.3], 3)[:, None] * 10.0 ** rng.uniform(-6, 0, (9, m))
+    wp = s[0:3] + rng.uniform(-2.0, 2.0, (2, 3, m))
+    gains = np.asarray(I.DEFAULT_GAINS)[:, None] * rng.uniform(0.8, 1.2, (9, m))
+    reps = n // m + 1
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(I.f32(np.tile(a, reps)[..., :n]))).to(dev)
+    ti = None if types == 1 else torch.from_numpy(np.tile(rng.integers(0, types, m).astype(np.uint8), reps)[:n]).to(dev)
+    W, G, lam = up(wp), up(gains), up(rng.normal(size=(30, m)))
+    sim = Simulator(table, glob, mode=1)
+
+    def rollout(parts):
+        x, ca, legs, k = up(s), torch.zeros((10, n), device=dev), [], 0
+        for count in parts:
+            ck = torch.empty((-(-count // every), 40, n), device=dev)
+            sim.step(x, count, 1e-3, type_idx=ti, gains=G, wp=W, resample_every=11, step0=k, ckpt=ck, ckpt_every=every,
+                     carry=ca)
+            legs.append((ck, count, k))
+            k += count
+        g = lam
+        for ck, count, k0 in reversed(legs):
+            g, _ = sim.step_backward(ck, every, count, 1e-3, g, type_idx=ti, gains=G, wp=W, resample_every=11, step0=k0)
+        torch.cuda.synchronize()
+        return x.cpu().numpy(), g.cpu().numpy()
+
+    x1, g1 = rollout((steps,))
+    x2, g2 = rollout((first, steps - first))
+    sim.close()
+    assert np.array_equal(x1, x2) and np.isfinite(g1).all()
+    assert np.array_equal(g1, g2), np.abs(g1 - g2).max()
