@@ -302,11 +302,11 @@ potato_status validate_step(const potato_ctx* ctx, const potato_state* st, const
  * the groups' gaps cost less: 1.12 / 1.57 / 2.75 at 65,536, 1.66 / 1.65 /
  * 2.73 at 131,072, 2.76 / 2.81 / 2.81 at 251,904, 5.50 / 5.33 / 5.33 at
  * 524,288. */
-Tuned default_shape(const Variant& v, const StepArgs& a, bool kinds) {
+Tuned default_shape(const Variant& v, const StepArgs& a) {
     Tuned t{256, a.n <= (int64_t(1) << 24) ? 1000 : 100, 0};
-    if (rollout_spaced(v, a) && !kinds) t.steps = std::min(t.steps, 250);
+    if (rollout_spaced(v, a) && !v.kinds) t.steps = std::min(t.steps, 250);
     if (rollout_grouped(v, a)) {
-        if (kinds)
+        if (v.kinds)
             t.block = a.n <= 65536 ? 256 : a.n <= 131072 ? 512 : 1024;
         else
             t.block = a.n <= 262144 ? 256 : 1024;
@@ -342,7 +342,7 @@ Plan make_plan(potato_ctx* ctx, const potato_state* st, const potato_params* pp,
     a.n_groups = P.v.het && !P.v.perm ? ctx->n_groups : 0;
 
     const potato_options& o = ctx->opts;
-    Tuned t = default_shape(P.v, P.a, ctx->kinds);
+    Tuned t = default_shape(P.v, P.a);
     auto it = ctx->tuned.find(TuneKey{P.v.mode, P.v.het, P.v.gains, P.v.perm, P.v.ckpt});
     if (it != ctx->tuned.end()) t = it->second;
     if (o.form == POTATO_FORM_PLAIN) {
