@@ -171,7 +171,6 @@ Limits make_limits(const potato_limits& L, float dt) {
     r.dt = dt;
     r.half_dt = 0.5f * dt;
     r.dt6 = dt / 6.0f;
-    r.dt6_lo = (float)((double)dt / 6.0 - (double)r.dt6);
     r.quarter_dt = 0.5f * r.half_dt;
     r.dt12 = 0.5f * r.dt6;
     r.inv_dt = 1.0f / dt;
@@ -338,6 +337,7 @@ Plan make_plan(potato_ctx* ctx, const potato_state* st, const potato_params* pp,
     a.alive = pp->alive;
     a.snap = nullptr;
     a.lim = make_limits(ctx->limits, dt);
+    a.dt6_lo = (float)((double)dt / 6.0 - (double)a.lim.dt6);
     if (!P.v.het) a.n_types = 1;      /* homogeneous launch: only type 0 is staged */
     a.n_groups = P.v.het && !P.v.perm ? ctx->n_groups : 0;
 

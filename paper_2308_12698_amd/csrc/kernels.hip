@@ -132,7 +132,7 @@ __device__ __forceinline__ void advance_vehicle(const StepArgs& A, const VehCons
         VehTrig T;
         veh_trig<KIND>(x, T);
         if (MODE == 1) veh_guidance<KIND>(c, x, T, wp, u);
-        veh_rk4<KIND, CARRY>(c, lim, x, T, lo, u);
+        veh_rk4<KIND, CARRY>(c, lim, A.dt6_lo, x, T, lo, u);
     }
 #pragma unroll
     for (int k = 0; k < 7; ++k)

@@ -94,7 +94,6 @@ struct Limits {
     float g, r_sat, r_sat2, ipos_max, iatt_max, irate_max, az_min;
     float dt, half_dt, dt6, inv_dt, dt2_6;   /* dt, dt/2, dt/6, 1/dt, dt^2/6 */
     float quarter_dt, dt12;                  /* half_dt/2, dt6/2 (exact halvings) */
-    float dt6_lo;                            /* dt/6 less its rounding dt6 */
 };
 
 struct Gains {

@@ -325,8 +325,8 @@ constexpr float kNearStep = 0.06f;
  * bits: aircraft 2.1e-7 -> 0.8e-7 m, cars 4.8e-8 -> 1.3e-8 (at the cost of
  * the multiplication and addition that the two fused ones replace). */
 template <int KIND, bool CARRY>
-__device__ __forceinline__ void veh_rk4(const VehConst& c, const Limits& L, float x[7], const VehTrig& T, float lo[7],
-                                        const float u[3]) {
+__device__ __forceinline__ void veh_rk4(const VehConst& c, const Limits& L, float dt6_lo, float x[7], const VehTrig& T,
+                                        float lo[7], const float u[3]) {
 #pragma clang fp contract(off)
     float k[7], acc[7], xs[7];
     VehTrig Ts;
@@ -383,7 +383,7 @@ __device__ __forceinline__ void veh_rk4(const VehConst& c, const Limits& L, floa
     for (int i = 0; i < 7; ++i) {
         if (!veh_row<KIND>(i)) continue;
         if (CARRY) {
-            const float y = POTATO_FMA(L.dt6, acc[i], POTATO_FMA(L.dt6_lo, acc[i], lo[i]));
+            const float y = POTATO_FMA(L.dt6, acc[i], POTATO_FMA(dt6_lo, acc[i], lo[i]));
             const float s = x[i] + y;
             lo[i] = y - (s - x[i]);
             x[i] = s;
