@@ -290,7 +290,12 @@ potato_status validate_step(const potato_ctx* ctx, const potato_state* st, const
  * drift apart and their last ones run alone (1,000 steps in launches of
  * 1,000 / 500 / 250 / 100: 9.73 / 9.47 / 9.29 / 9.6 ms at 1,048,576 agents,
  * 6.79 / 6.52 / 6.41 ms at 700,000, 3.20 / 3.12 / 3.13 at 300,000); open loop
- * and several types gain nothing by it.  Swarms beyond 2^24 agents keep 100,
+ * and several types gain nothing by it.  So do swarms of more than
+ * kSpacedAgents with an alive mask: which SIMDs the live waves share is dealt
+ * anew with every launch, and one deal of a mostly dead swarm may be a poor
+ * one (1,048,576 agents, the last tenth alive: 1.67 / 1.84 / 2.10 us per step
+ * in launches of 100 / 250 / 1,000; all alive 11.18 / 11.03 / 10.89).  Swarms
+ * beyond 2^24 agents keep 100,
  * so that no launch runs much longer than a sixth of a second.
  * Block: 256 threads.  A launch that groups its agents per block fills more
  * of its groups with wider blocks, but a block of 1,024 puts 16 waves on one
@@ -303,7 +308,7 @@ potato_status validate_step(const potato_ctx* ctx, const potato_state* st, const
  * 524,288. */
 Tuned default_shape(const Variant& v, const StepArgs& a) {
     Tuned t{256, a.n <= (int64_t(1) << 24) ? 1000 : 100, 0};
-    if (rollout_spaced(v, a) && !v.kinds) t.steps = std::min(t.steps, 250);
+    if ((rollout_spaced(v, a) && !v.kinds) || (a.alive && a.n > kSpacedAgents)) t.steps = std::min(t.steps, 250);
     if (rollout_grouped(v, a)) {
         if (v.kinds)
             t.block = a.n <= 65536 ? 256 : a.n <= 131072 ? 512 : 1024;

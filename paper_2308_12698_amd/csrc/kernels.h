@@ -136,11 +136,14 @@ bool rollout_lanes(const Variant& v, const StepArgs& a);
 
 /* Closed-loop swarms of more than kSpacedAgents (more than two waves per
  * SIMD) of one quadrotor type, or with cars or aircraft in a processing
- * order and no agents left out, take the spaced rsq and sqrt of quad_step.h:
+ * order, and no agents left out, take the spaced rsq and sqrt of quad_step.h:
  * per step 9.87 -> 9.25 us at 1,048,576 quadrotors, 5.16 -> 4.91 at 524,288,
  * 2.75 -> 2.69 at 262,144, 2.33 -> 2.28 at 140,000 (but 1.53 -> 1.58 at
  * 131,072); mixed kinds in order 2.64 -> 2.38 at 150,000, 2.49 -> 2.43 at
- * 262,144, 4.52 -> 4.36 at 524,288, equal at 1M.  The others lose by it, as
+ * 262,144, 4.52 -> 4.36 at 524,288, equal at 1M.  With an alive mask the host
+ * does not know how many waves are live: quadrotors scattered over a swarm
+ * would gain by it (10.3 -> 9.3 at 1M with a fifth dead), a quarter alive in
+ * one piece loses (1.01 -> 1.16 at 140,000 and 262,144).  The others lose too, as
  * SIMDs come down to one or two waves before the launch ends: quadrotors of
  * several types (2.63 -> 2.85 ms per 1,000 steps of 251,904, their budgets
  * end apart), kinds of which many agents are dead (the quadrotors alone 1.45

@@ -900,9 +900,8 @@ bool rollout_lanes(const Variant& v, const StepArgs& a) {
 }
 
 bool rollout_spaced(const Variant& v, const StepArgs& a) {
-    return v.mode == 1 && !v.ckpt && (v.kinds ? v.perm && !a.alive : !v.het) && a.n > kSpacedAgents;
+    return v.mode == 1 && !v.ckpt && !a.alive && (v.kinds ? v.perm : !v.het) && a.n > kSpacedAgents;
 }
-
 
 const void* rollout_kernel(const Variant& v, const StepArgs& a) {
     if (rollout_lanes(v, a)) {

@@ -84,3 +84,17 @@ def test_quadrotors_of_a_table_with_vehicles(torch_dev, hip, n):
     assert launches(torch_dev, hip, one, n, 1000) == launches(torch_dev, hip, table, n, 1000)
     one.close()
     table.close()
+
+
+@pytest.mark.parametrize("n", [131073, 300000])
+@pytest.mark.parametrize("carry", [True, False])
+def test_masked_swarms_run_the_form_of_fewer_agents(torch_dev, hip, n, carry):
+    """With an alive mask a swarm may hold any number of live agents, all of
+    them in a few waves for instance: its launches take the kernel of swarms
+    of at most 131,072, and up to 250 steps."""
+    sim = simulator()
+    few = launches(torch_dev, hip, sim, 131072, 1000, carry=carry)
+    masked = launches(torch_dev, hip, sim, n, 1000, carry=carry, alive=True)
+    assert [k[0] for k in masked] == 4 * [k[0] for k in few]
+    assert {k[0] for k in launches(torch_dev, hip, sim, n, 1000, carry=carry)} != {k[0] for k in few}
+    sim.close()

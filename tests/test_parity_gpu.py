@@ -845,3 +845,31 @@ def test_single_step_launches_of_small_swarms(torch_dev, n, mode):
     assert np.isfinite(out[0]).all()
     for other in out[1:]:
         assert np.array_equal(out[0], other)
+
+
+@pytest.mark.parametrize("dead", ["none", "scattered", "three quarters in front", "all but the last"])
+@pytest.mark.parametrize("carry", [True, False])
+def test_masked_swarms_of_many_agents(torch_dev, dead, carry):
+    """131,203 quadrotors of one type with an alive mask, agents dead here and
+    there and in one piece: the live ones have the bits that they have
+    without a mask, the dead ones those that they came with."""
+    torch, dev = torch_dev
+    from paper_2308_12698_amd.sim import Simulator
+    n, steps = 131203, 23
+    rng = np.random.default_rng(79)
+    state = I.hover_state(rng.uniform(0.0, 50.0, (3, n)))
+    state[10:13] = I.f32(rng.normal(0.0, 0.5, (3, n)))
+    wp = _dev(torch, dev, I.f32(rng.uniform(0.0, 50.0, (1, 3, n))))
+    alive = {"none": np.ones(n), "scattered": rng.random(n) > 0.4, "three quarters in front": np.arange(n) >= 3 * n // 4,
+             "all but the last": np.arange(n) == n - 1}[dead].astype(np.uint8)
+    sim = Simulator([I.base_type()], I.globals_f32(), mode=1)
+    out = []
+    for mask in (None, alive):
+        st, ct = _dev(torch, dev, state), torch.zeros((10, n), device=dev) if carry else None
+        sim.step(st, steps, 1e-3, wp=wp, carry=ct, alive=_dev(torch, dev, mask))
+        torch.cuda.synchronize()
+        out.append(st.cpu().numpy())
+    sim.close()
+    live = alive == 1
+    assert np.array_equal(out[0][:, live], out[1][:, live])
+    assert np.array_equal(out[1][:, ~live], state[:, ~live])
