@@ -247,7 +247,8 @@ potato_status potato_step(potato_ctx* ctx, const potato_state* state, const pota
  * agent per thread or 1x / 2x the resident blocks) on a scratch copy of the
  * given inputs (the caller's buffers are not modified), store the fastest on
  * the context for this mode, type layout and checkpointing, and return it
- * in *best (may be NULL).  probe_steps is the number of time steps per
+ * in *best (may be NULL).  Calls with other agent counts use it where they
+ * run the same form of the kernel (small, middle and large swarms differ).  probe_steps is the number of time steps per
  * timed trial.  ckpt_every > 0 times the variant that writes checkpoints
  * every ckpt_every steps (into scratch memory), which potato_step runs when
  * given a checkpoint buffer; its result applies to such calls, 0 times and

@@ -44,12 +44,19 @@ potato_status hip_fail(hipError_t e, const char* where) {
 
 bool finite_pos(float x) { return std::isfinite(x) && x > 0.0f; }
 
+/* What an autotuned shape applies to: calls of the same variant whose agent
+ * count and mask take the same form of the kernel (four lanes per agent, one
+ * lane, spaced), since a shape of one says nothing about another. */
 struct TuneKey {
-    int mode, het, gains, perm, ckpt;
+    int mode, het, gains, perm, ckpt, lanes, spaced;
     bool operator<(const TuneKey& o) const {
-        return std::tie(mode, het, gains, perm, ckpt) < std::tie(o.mode, o.het, o.gains, o.perm, o.ckpt);
+        return std::tie(mode, het, gains, perm, ckpt, lanes, spaced) <
+               std::tie(o.mode, o.het, o.gains, o.perm, o.ckpt, o.lanes, o.spaced);
     }
 };
+TuneKey tune_key(const Variant& v, const StepArgs& a) {
+    return TuneKey{v.mode, v.het, v.gains, v.perm, v.ckpt, rollout_lanes(v, a), rollout_spaced(v, a)};
+}
 struct Tuned { int block, steps, grid; };
 
 }  // namespace
@@ -348,7 +355,7 @@ Plan make_plan(potato_ctx* ctx, const potato_state* st, const potato_params* pp,
 
     const potato_options& o = ctx->opts;
     Tuned t = default_shape(P.v, P.a);
-    auto it = ctx->tuned.find(TuneKey{P.v.mode, P.v.het, P.v.gains, P.v.perm, P.v.ckpt});
+    auto it = ctx->tuned.find(tune_key(P.v, P.a));
     if (it != ctx->tuned.end()) t = it->second;
     if (o.form == POTATO_FORM_PLAIN) {
         /* one step per launch is HBM bound: 128-thread blocks measured best
@@ -672,9 +679,9 @@ potato_status potato_autotune(potato_ctx* ctx, const potato_state* state, const 
     (void)hipStreamSynchronize(hs);
     (void)hipFree(scratch);
     if (e != hipSuccess) return hip_fail(e, "potato_autotune");
-    const bool het = params->type != nullptr;
-    ctx->tuned[TuneKey{ctx->opts.mode, het, ctx->opts.mode == 1 && params->gains != nullptr,
-                       het && params->perm != nullptr, ckpt_every > 0}] = win;
+    /* (the scratch memory is gone, its pointer still says that there were checkpoints) */
+    const Plan tuned = make_plan(ctx, state, params, cmds, dt, n_agents, ckpt_scratch, ckpt_every);
+    ctx->tuned[tune_key(tuned.v, tuned.a)] = win;
     drop_graphs(ctx);
     if (best) {
         *best = ctx->opts;

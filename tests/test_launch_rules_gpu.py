@@ -98,3 +98,20 @@ def test_masked_swarms_run_the_form_of_fewer_agents(torch_dev, hip, n, carry):
     assert [k[0] for k in masked] == 4 * [k[0] for k in few]
     assert {k[0] for k in launches(torch_dev, hip, sim, n, 1000, carry=carry)} != {k[0] for k in few}
     sim.close()
+
+
+@pytest.mark.parametrize("tuned,other", [(5000, 200000), (5000, 100000), (140000, 5000), (140000, 20000)])
+def test_a_tuned_shape_stays_with_its_form(torch_dev, hip, tuned, other):
+    """Tuning a swarm of one size fixes the launches of that size and of
+    those that run the same form, and leaves the default of the others."""
+    torch, dev = torch_dev
+    fresh, sim = simulator(), simulator()
+    st, wp = torch.zeros((30, tuned), device=dev), torch.zeros((1, 3, tuned), device=dev)
+    st[6] = 1.0
+    best = sim.autotune(st, 1e-3, probe_steps=25, wp=wp, carry=torch.zeros((10, tuned), device=dev), cache="")
+    for n in (tuned, tuned + 7):
+        got = launches(torch_dev, hip, sim, n, 100)
+        assert [k[2] for k in got] == [best["block"]] * (100 // best["steps_per_launch"])
+    assert launches(torch_dev, hip, sim, other, 1000) == launches(torch_dev, hip, fresh, other, 1000)
+    fresh.close()
+    sim.close()
