@@ -302,23 +302,25 @@ potato_status validate_step(const potato_ctx* ctx, const potato_state* st, const
  * anew with every launch, and one deal of a mostly dead swarm may be a poor
  * one (1,048,576 agents, the last tenth alive: 1.67 / 1.84 / 2.10 us per step
  * in launches of 100 / 250 / 1,000; all alive 11.18 / 11.03 / 10.89).  Swarms
- * beyond 2^24 agents keep 100,
- * so that no launch runs much longer than a sixth of a second.
+ * beyond 2^24 agents take 100: a launch of 2^24 runs 0.15 s with 1,000 steps,
+ * one of 2^30 a second with 100.
  * Block: 256 threads.  A launch that groups its agents per block fills more
- * of its groups with wider blocks, but a block of 1,024 puts 16 waves on one
- * compute unit, so the widest block is taken that still gives every compute
- * unit one: mixed kinds, us per step with 256 / 512 / 1,024: 2.22 / 2.47 /
- * 3.30 at 65,536 agents, 3.01 / 2.59 / 3.45 at 131,072, 4.69 / 3.78 / 3.49 at
- * 251,904, 12.8 / 11.5 / 10.4 at 1,048,576.  With one kind (budgets only)
- * the groups' gaps cost less: 1.12 / 1.57 / 2.75 at 65,536, 1.66 / 1.65 /
- * 2.73 at 131,072, 2.76 / 2.81 / 2.81 at 251,904, 5.50 / 5.33 / 5.33 at
- * 524,288. */
+ * of its groups with wider blocks, and leaves compute units without one where
+ * the swarm is too small for them.  Mixed kinds, us per step with 256 / 512 /
+ * 1,024 threads: 1.76 / 1.76 / 2.58 at 3,000 agents, 2.06 / 1.84 / 2.87 at
+ * 65,536, 2.45 / 1.96 / 3.09 at 131,072, where 512 threads make one block per
+ * compute unit, 3.15 / 3.10 / 3.05 at 140,000, 3.83 / 3.17 / 3.14 at 200,000,
+ * 4.50 / 3.80 / 3.35 at 300,000, 6.37 / 5.72 / 4.96 at 524,288: 512 up to
+ * 131,072, 1,024 beyond.  With one kind (budgets only) the groups' gaps cost
+ * less: 1.06 / 1.51 / 2.65 at 40,000, 1.63 / 1.61 / 2.67 at 131,072, 2.17 /
+ * 2.69 / 2.68 at 180,000, 2.72 / 2.70 / 2.71 at 262,144, 3.62 / 3.28 / 3.32 at
+ * 300,000, 5.41 / 5.38 / 5.13 at 524,288: 256 up to 262,144, 1,024 beyond. */
 Tuned default_shape(const Variant& v, const StepArgs& a) {
     Tuned t{256, a.n <= (int64_t(1) << 24) ? 1000 : 100, 0};
     if ((rollout_spaced(v, a) && !v.kinds) || (a.alive && a.n > kSpacedAgents)) t.steps = std::min(t.steps, 250);
     if (rollout_grouped(v, a)) {
         if (v.kinds)
-            t.block = a.n <= 65536 ? 256 : a.n <= 131072 ? 512 : 1024;
+            t.block = a.n <= 131072 ? 512 : 1024;
         else
             t.block = a.n <= 262144 ? 256 : 1024;
     }

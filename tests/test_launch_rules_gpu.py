@@ -115,3 +115,16 @@ def test_a_tuned_shape_stays_with_its_form(torch_dev, hip, tuned, other):
     assert launches(torch_dev, hip, sim, other, 1000) == launches(torch_dev, hip, fresh, other, 1000)
     fresh.close()
     sim.close()
+
+
+@pytest.mark.parametrize("kinds,n,threads", [(True, 1000, 512), (True, 65536, 512), (True, 65537, 512),
+                                             (True, 131072, 512), (True, 131073, 1024), (False, 16385, 256),
+                                             (False, 262144, 256), (False, 262145, 1024)])
+def test_blocks_of_grouped_launches(torch_dev, hip, kinds, n, threads):
+    """Agents of several kinds, or of one kind with several budgets, in the
+    caller's order: the measured block widths, in one launch."""
+    types = [I.base_type(), I.car_type(), I.wing_type()] if kinds else [dict(I.base_type(), budget=b) for b in (90, 800)]
+    sim = simulator(types)
+    got = launches(torch_dev, hip, sim, n, 1000, types=len(types))
+    assert len(got) == 1 and got[0][2] == threads and got[0][1] <= -(-n // threads)
+    sim.close()
