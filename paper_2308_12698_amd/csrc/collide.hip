@@ -19,10 +19,16 @@
  * indices wrapped to 2^bx x 2^by x 2^bz, where the bits split the budget
  * 2^k >= 2N by the extent of the alive agents' bounding box (so a flat
  * swarm does not leave the buckets of an unused depth empty); buckets are
- * linear with x fastest, and each x row holds two extra ghost columns (a
- * copy of the last column before the first and of the first after the
- * last), so the three x neighbours of any cell are three consecutive
- * buckets and an agent's 12 cells are 4 contiguous bucket ranges.
+ * linear with x fastest, and each x row holds two extra ghost cells (a
+ * copy of the last before the first and of the first after the last), so the
+ * three x neighbours of any cell are consecutive buckets and an agent's 12
+ * cells are 4 contiguous bucket ranges.  Where agents are dense enough to
+ * leave bits of the budget over, a cell edge along x is 2 or 4 columns: an
+ * agent's range is then 2.5 or 2.25 edges long instead of 3, and its
+ * candidates those of 40 or 36 h^3 instead of 48 (27 cells of h: 27 h^3 in 9
+ * ranges).  A lattice of 1,048,576 agents 1.05 contact distances apart takes
+ * 114 us, close packed at 1.02 129 (one column per edge 128 and 160, cells of
+ * h^3 112 and 130); sparse swarms have one column either way.
  * Passes: bounding box (block partials, reduced again by every block of
  * the next kernel, which plans the wrap and stores it); a two-level sort of
  * the items (position and radius or id) into bucket order (per-tile counts
@@ -56,6 +62,7 @@ namespace {
 /* Fewest bits of the ghost-padded x axis: 2^5 columns + 2 ghosts keeps the
  * padding within 1/16 of the bucket budget. */
 constexpr int kMinXBits = 5;
+constexpr int kMaxSplitBits = 2;
 
 /* Cell index along one axis.  The coordinate in cells is clamped to
  * [-2^24, 2^24] before the conversion, so infinite, NaN (max/min return the
@@ -73,11 +80,14 @@ __device__ __forceinline__ int32_t cell_index(float x, float inv_h) {
 __device__ __forceinline__ int32_t wide_cell(int32_t c) { return c >> 1; }
 __device__ __forceinline__ uint32_t near_side(int32_t c) { return (uint32_t)((c & 1) * 2 - 1); }
 
-/* Wrap of the grid: 2^bx x 2^by x 2^bz cells, x rows of 2^bx + 2 buckets. */
+/* Wrap of the grid: 2^bx x 2^by x 2^bz cells, side = 2^f columns per cell
+ * edge, x rows of 2^bx + 2 side buckets. */
 struct Wrap {
-    int bx, by, bz;
+    int bx, by, bz, f;
     uint32_t mx, my, mz;     /* 2^b - 1 */
-    uint32_t row;            /* 2^bx + 2 */
+    uint32_t side;
+    uint32_t row;
+    float per_edge;          /* side */
 };
 
 /* e >= 1 */
@@ -85,9 +95,11 @@ __device__ __forceinline__ int ceil_log2(int64_t e) { return e > 1 ? 64 - __clzl
 
 __device__ __forceinline__ Wrap wrap_of(const int32_t* b) {
     Wrap w;
-    w.bx = b[0]; w.by = b[1]; w.bz = b[2];
+    w.bx = b[0]; w.by = b[1]; w.bz = b[2]; w.f = b[3];
     w.mx = (1u << b[0]) - 1u; w.my = (1u << b[1]) - 1u; w.mz = (1u << b[2]) - 1u;
-    w.row = (1u << b[0]) + 2u;
+    w.side = 1u << b[3];
+    w.row = (1u << b[0]) + 2u * w.side;
+    w.per_edge = (float)w.side;
     return w;
 }
 
@@ -95,7 +107,9 @@ __device__ __forceinline__ Wrap wrap_of(const int32_t* b) {
  * max x, y, z, in cells): start from the bits that cover each extent, then
  * take bits away, each time from the axis whose extent is the smallest
  * multiple of its halved wrap (it gains the fewest wraps), x not below
- * kMinXBits.  Every block of k_coll_hist computes the same wrap and one
+ * kMinXBits.  Bits that are left over, as in swarms with several agents per
+ * cell, make up to 4 columns of a cell edge: the candidates of an agent then
+ * come from 2.5 or 2.25 edges along x instead of 3.  Every block of k_coll_hist computes the same wrap and one
  * stores its bits for the later kernels of the pass. */
 __device__ __forceinline__ Wrap plan_wrap(const int32_t* box, int k) {
     int64_t e[3];
@@ -103,7 +117,7 @@ __device__ __forceinline__ Wrap plan_wrap(const int32_t* box, int k) {
         const int64_t lo = box[a], hi = box[3 + a];
         e[a] = hi >= lo ? hi - lo + 1 : 1;       /* no alive agent: any wrap */
     }
-    int b[3] = {ceil_log2(e[0]), ceil_log2(e[1]), ceil_log2(e[2])};
+    int b[4] = {ceil_log2(e[0]), ceil_log2(e[1]), ceil_log2(e[2]), 0};
     if (b[0] < kMinXBits) b[0] = kMinXBits;
     while (b[0] + b[1] + b[2] > k) {
         int best = -1;
@@ -114,10 +128,12 @@ __device__ __forceinline__ Wrap plan_wrap(const int32_t* box, int k) {
         }
         --b[best];
     }
+    b[3] = min(k - (b[0] + b[1] + b[2]), kMaxSplitBits);
+    b[0] += b[3];
     return wrap_of(b);
 }
 
-/* Bucket of wrapped cell (column col = wrapped x + 1, wrapped y, wrapped z). */
+/* Bucket of wrapped cell (column col = wrapped x + side, wrapped y, wrapped z). */
 __device__ __forceinline__ uint32_t bucket_of(const Wrap& w, uint32_t col, uint32_t wy, uint32_t wz) {
     return col + w.row * (wy | (wz << w.by));
 }
@@ -214,16 +230,16 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t n_blocks) {
 /* Wrapped cell of a position. */
 __device__ __forceinline__ void wrapped_cell(const Wrap& w, float x, float y, float z, float inv_h, uint32_t& wx,
                                              uint32_t& wy, uint32_t& wz) {
-    wx = (uint32_t)cell_index(x, inv_h) & w.mx;
+    wx = (uint32_t)cell_index(x, inv_h * w.per_edge) & w.mx;
     wy = (uint32_t)wide_cell(cell_index(y, inv_h)) & w.my;
     wz = (uint32_t)wide_cell(cell_index(z, inv_h)) & w.mz;
 }
 
-/* An agent in the first wrapped column also sits in the ghost column after
- * the last, one in the last column in the ghost column before the first:
- * the bucket offset of its ghost, or 0. */
+/* An agent in the first cell edge's columns also sits in the ghost columns
+ * after the last, one in the last edge's in those before the first: the
+ * bucket offset of its ghost, or 0. */
 __device__ __forceinline__ int32_t ghost_offset(const Wrap& w, uint32_t wx) {
-    return wx == 0 ? (int32_t)(w.mx + 1) : (wx == w.mx ? -(int32_t)(w.mx + 1) : 0);
+    return wx < w.side ? (int32_t)(w.mx + 1) : (wx > w.mx - w.side ? -(int32_t)(w.mx + 1) : 0);
 }
 
 /* Bucket of an item: the agent's own bucket, or for a ghost copy (id with
@@ -231,7 +247,7 @@ __device__ __forceinline__ int32_t ghost_offset(const Wrap& w, uint32_t wx) {
 __device__ __forceinline__ uint32_t item_bucket(const Wrap& w, const float4& q, int32_t id, float inv_h) {
     uint32_t wx, wy, wz;
     wrapped_cell(w, q.x, q.y, q.z, inv_h, wx, wy, wz);
-    const uint32_t b = bucket_of(w, wx + 1, wy, wz);
+    const uint32_t b = bucket_of(w, wx + w.side, wy, wz);
     return id < 0 ? (uint32_t)((int32_t)b + ghost_offset(w, wx)) : b;
 }
 
@@ -310,6 +326,7 @@ __global__ void __launch_bounds__(kTileBlock) k_coll_hist(const float* rows, int
         wrap[0] = w.bx;
         wrap[1] = w.by;
         wrap[2] = w.bz;
+        wrap[3] = w.f;
     }
     for (int32_t p = threadIdx.x; p < parts; p += kTileBlock) cnt[p] = 0;
     __syncthreads();
@@ -320,7 +337,7 @@ __global__ void __launch_bounds__(kTileBlock) k_coll_hist(const float* rows, int
             if (!on[r]) continue;
             uint32_t wx, wy, wz;
             wrapped_cell(w, px[r], py[r], pz[r], inv_h, wx, wy, wz);
-            const uint32_t b = bucket_of(w, wx + 1, wy, wz);
+            const uint32_t b = bucket_of(w, wx + w.side, wy, wz);
             atomicAdd(&cnt[b >> s], 1);
             const int32_t g = ghost_offset(w, wx);
             if (g != 0) atomicAdd(&cnt[(uint32_t)((int32_t)b + g) >> s], 1);
@@ -373,7 +390,7 @@ __global__ void __launch_bounds__(kTileBlock) k_coll_part(const float* rows, int
             const int32_t i = (int32_t)(base + threadIdx.x + r * kTileBlock);
             uint32_t wx, wy, wz;
             wrapped_cell(w, q[r].x, q[r].y, q[r].z, inv_h, wx, wy, wz);
-            const uint32_t b = bucket_of(w, wx + 1, wy, wz);
+            const uint32_t b = bucket_of(w, wx + w.side, wy, wz);
             const int32_t slot = atomicAdd(&cur[b >> s], 1);
             tpos[slot] = q[r];
             if (!ONE_RADIUS) tid[slot] = i;
@@ -558,7 +575,7 @@ __global__ void __launch_bounds__(256) k_coll_query(const float4* spos, const in
             if (!ONE_RADIUS) pk = spos[k];
             uint32_t wx, wy, wz;
             wrapped_cell(w, pk.x, pk.y, pk.z, inv_h, wx, wy, wz);
-            /* the 4 (y, z) rows: bucket range of columns wx .. wx + 2 (ghost-padded);
+            /* the 4 (y, z) rows: bucket range of columns wx .. wx + 2 side (ghost-padded);
              * an axis wrapped to a single cell has no other row */
             const uint32_t ny = (wy + near_side(cell_index(pk.y, inv_h))) & w.my;
             const uint32_t nz = (wz + near_side(cell_index(pk.z, inv_h))) & w.mz;
@@ -567,7 +584,7 @@ __global__ void __launch_bounds__(256) k_coll_query(const float4* spos, const in
             for (int r = 0; r < kRanges; ++r) {
                 const uint32_t b0 = bucket_of(w, wx, r & 1 ? ny : wy, r & 2 ? nz : wz);
                 lo[r] = start[b0];
-                hi[r] = start[b0 + 3];
+                hi[r] = start[b0 + 2 * w.side + 1];
             }
             if (w.my == 0) hi[1] = lo[1], hi[3] = lo[3];
             if (w.mz == 0) hi[2] = lo[2], hi[3] = lo[3];
@@ -812,7 +829,7 @@ constexpr int64_t workspace_for(int64_t n) {
     /* items (x, y, z, r) in partition order and in bucket order [2n] each
      * first (16-byte aligned: agents and ghosts); their ids [2n] each;
      * bucket starts [parts << s]; partition-tile offsets [parts * tiles + 1];
-     * chunk totals of their scan [chunks]; bits of the wrap [3 of 6]; the
+     * chunk totals of their scan [chunks]; bits of the wrap [4 of 6]; the
      * bounding box's per-block partials [kBoxWords]; the query's per-block counts of dead agents */
     const int64_t blocks = (n + 255) / 256;
     return 16 * 4 * n + 4 * (4 * n + (q.parts << q.s) + cells + 1 + chunks + 6 + kBoxWords + blocks) + 256;

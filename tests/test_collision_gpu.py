@@ -343,3 +343,36 @@ def test_detection_on_the_grid_at_cell_edges(oracle, torch_dev, shape, typed):
                                              None if ti is None else np.minimum(ti, 2))
     assert np.array_equal(got, ref) and died == ref_died
     assert 0 < died < int(alive.sum())
+
+
+def assert_decisions(oracle, torch_dev, pos, types, ti, alive):
+    """The GPU's decisions on positions [3, n] are the brute-force
+    reference's bit for bit; returns how many died."""
+    state = I.hover_state(pos.astype(np.float32).astype(np.float64))
+    got, died = gpu_detect(torch_dev, state, types, alive, ti)
+    ref, ref_died = oracle.detect_collisions(state, [t["radius"] for t in types], alive,
+                                             None if ti is None else np.minimum(ti, len(types) - 1))
+    assert np.array_equal(got, ref) and died == ref_died
+    return died
+
+
+@pytest.mark.parametrize("bits", [(6, 5, 5), (5, 5, 5), (6, 4, 4), (4, 5, 5), (5, 4, 4), (6, 4, 2), (9, 1, 1), (11, 0, 0)])
+@pytest.mark.parametrize("typed", [False, True])
+def test_columns_of_a_cell_edge(oracle, torch_dev, bits, typed):
+    """The grid of 14,000 agents has 2^15 buckets.  Boxes of 2^bits cells per
+    axis (an edge long in x, two in y and z) that wrap, that just fit, and
+    that leave one, two or more bits, which split each cell edge along x into
+    2 or 4 columns; half of the agents at the faces of those columns, on both
+    sides of the origin, dead agents."""
+    rng = np.random.default_rng(sum(b << 4 * i for i, b in enumerate(bits)) + typed)
+    n = 14000
+    types = [I.base_type()] + ([I.base_type(arm=0.3), I.base_type(arm=0.05)] if typed else [])
+    ti = rng.integers(0, 3, n).astype(np.uint8) if typed else None
+    h = float(np.float32(2.02) * np.float32(max(t["radius"] for t in types)))
+    cells = np.array([1 << bits[0], 2 << bits[1], 2 << bits[2]])[:, None]     # in edges
+    pos = rng.uniform(0.0, 1.0, (3, n)) * (cells - 0.02) + 0.01
+    at = rng.random(n) < 0.5
+    face = np.clip(np.round(pos[:, at] * 4.0) / 4.0, 0.25, cells - 0.25)
+    pos[:, at] = face + rng.choice([-1e-3, -1e-6, 0.0, 1e-6, 1e-3], (3, int(at.sum())))
+    alive = (rng.random(n) > 0.1).astype(np.uint8)
+    assert assert_decisions(oracle, torch_dev, (pos - cells // 2) * h, types, ti, alive) > 0
