@@ -376,3 +376,60 @@ def test_columns_of_a_cell_edge(oracle, torch_dev, bits, typed):
     pos[:, at] = face + rng.choice([-1e-3, -1e-6, 0.0, 1e-6, 1e-3], (3, int(at.sum())))
     alive = (rng.random(n) > 0.1).astype(np.uint8)
     assert assert_decisions(oracle, torch_dev, (pos - cells // 2) * h, types, ti, alive) > 0
+
+
+@pytest.mark.parametrize("typed", [False, True])
+def test_line_on_the_grid(oracle, torch_dev, typed):
+    """17,000 agents along a line of 4,000 cells, of which every fourth holds
+    16 and the one between two such a single one: one y row and one z layer
+    (an agent's four ranges become one), four columns per cell edge, and more
+    items in a bucket partition than the sort assembles in LDS, spread over
+    many buckets.  The single ones survive."""
+    rng = np.random.default_rng(16 + typed)
+    types = [I.base_type()] + ([I.base_type(arm=0.05)] if typed else [])
+    h = float(np.float32(2.02) * np.float32(types[0]["radius"]))
+    cells = np.concatenate([np.repeat(np.arange(0, 4000, 4), 16), np.arange(2, 4000, 4)])
+    n = cells.size
+    order = rng.permutation(n)
+    pos = np.empty((3, n))
+    pos[0] = (cells + rng.uniform(0.05, 0.95, n)) * h
+    pos[1], pos[2] = 8.5 * h + rng.uniform(-0.3, 0.3, n) * h, 20.5 * h + rng.uniform(-0.3, 0.3, n) * h
+    ti = rng.integers(0, 2, n).astype(np.uint8) if typed else None
+    alive = (rng.random(n) > 0.02).astype(np.uint8)
+    died = assert_decisions(oracle, torch_dev, pos[:, order], types, ti, alive)
+    assert 0.5 * n < died <= 16000
+
+
+def test_degenerate_geometry_on_the_grid(oracle, torch_dev):
+    """As test_detection_degenerate_geometry, with 15,000 agents: coincident
+    ones beyond the sort's LDS staging, pairs far from the origin, one corner
+    of huge negative coordinates, NaN and infinite positions."""
+    rng = np.random.default_rng(100)
+    n = 15000
+    pos = rng.uniform(0.0, 50.0, (3, n))
+    pos[:, 0:5000] = 10.0
+    base = np.stack([rng.uniform(-1e4, 1e4, 500), rng.uniform(-1e4, 1e4, 500), np.full(500, 5e3)])
+    pos[:, 5000:6000:2] = base
+    pos[:, 5001:6000:2] = base + np.array([[0.2], [0.0], [0.0]])
+    pos[:, 6000:8000] = rng.uniform(-3e6, -2.9e6, (3, 2000))
+    for k, bad in enumerate((np.nan, np.nan, np.inf, -np.inf)):
+        pos[k % 3, 8000 + 50 * k:8050 + 50 * k] = bad
+    alive = np.ones(n, np.uint8)
+    alive[::97] = 0
+    assert assert_decisions(oracle, torch_dev, pos, [I.base_type()], None, alive) > 5000
+
+
+@pytest.mark.parametrize("n", [12289, 13311, 13312, 13313])
+@pytest.mark.parametrize("typed", [False, True])
+def test_the_largest_swarms_of_the_pairs_pass(oracle, torch_dev, n, typed):
+    """Sizes around 13,312 agents, the largest that every pair of is tested
+    (two tiles per wave throughout), and beyond."""
+    rng = np.random.default_rng(n)
+    side = (n / 4.0) ** (1.0 / 3.0)
+    pos = rng.uniform(0.0, side, (3, n))
+    pos[:, : n // 4] = rng.uniform(0.0, side, (3, 1))
+    pos[0, n - 3], pos[1, n - 5], pos[2, n - 7] = np.nan, np.inf, -np.inf
+    types = [I.base_type()] + ([I.base_type(arm=0.4), I.base_type(arm=0.05)] if typed else [])
+    ti = rng.integers(0, 5, n).astype(np.uint8) if typed else None      # 3 and 4 read as the last type
+    alive = (rng.random(n) > 0.1).astype(np.uint8)
+    assert assert_decisions(oracle, torch_dev, pos, types, ti, alive) > 0
