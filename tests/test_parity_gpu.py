@@ -873,3 +873,70 @@ def test_masked_swarms_of_many_agents(torch_dev, dead, carry):
     live = alive == 1
     assert np.array_equal(out[0][:, live], out[1][:, live])
     assert np.array_equal(out[1][:, ~live], state[:, ~live])
+
+
+def budget_swarm(n, budgets, seed, steps):
+    """Quadrotors of len(budgets) airframes with these step budgets, labels
+    shuffled with uneven shares, waypoints redrawn halfway; more than 16,384
+    of them, so that a launch takes one lane per agent."""
+    assert n > 16384
+    types = [dict(t, budget=b) for t, b in zip(I.hetero_types(len(budgets), seed_stream=5), budgets)]
+    rng = np.random.default_rng(seed)
+    share = rng.uniform(0.2, 1.0, len(budgets))
+    labels = rng.choice(len(budgets), n, p=share / share.sum()).astype(np.uint8)
+    pos = rng.uniform(0.0, 30.0, (3, n))
+    return I.Swarm("budgets", 1, 1e-3, steps, I.hover_state(pos), types, I.globals_f32(), type_idx=labels,
+                   wp=I.f32(pos + rng.uniform(-3.0, 3.0, (2, 3, n))), resample_every=steps // 2)
+
+
+def run_budgets(torch_dev, sw, ordered, *, alive=None, gains=None, carry=True, **opts):
+    torch, dev = torch_dev
+    from paper_2308_12698_amd.sim import Simulator
+    sim = Simulator(sw.types, sw.glob, mode=1, debug=True, **opts)
+    st, ti = _dev(torch, dev, sw.state), _dev(torch, dev, sw.type_idx)
+    sim.step(st, sw.n_steps, sw.dt, type_idx=ti, perm=sim.order_by_type(ti) if ordered else None,
+             wp=_dev(torch, dev, sw.wp), resample_every=sw.resample_every, gains=_dev(torch, dev, gains),
+             carry=carry_zeros(torch_dev, sw.n) if carry else None, alive=_dev(torch, dev, alive))
+    torch.cuda.synchronize()
+    out = st.cpu().numpy()
+    sim.close()
+    return out
+
+
+EIGHT = (200, 180, 150, 120, 90, 60, 30, 1)
+
+
+@pytest.mark.parametrize("opts", [dict(), dict(block=512, grid_blocks=1), dict(block=1024, grid_blocks=2),
+                                  dict(block=64, steps_per_launch=200, grid_blocks=3), dict(block=256, grid_blocks=7),
+                                  dict(block=128, steps_per_launch=25, use_graph=True), dict(form="plain")])
+def test_grouped_one_lane_launches_equal_the_type_order(torch_dev, opts):
+    """Eight budget classes of 16,601 agents in the caller's order, grouped
+    per block (k_rollout with group_agents), against the type order: one
+    round of blocks, one to seven blocks of several chunks each, all block
+    widths, a captured graph, one step per launch; then with dead agents,
+    per-agent gains and no carries."""
+    sw = budget_swarm(16601, EIGHT, 1, 200)
+    opts = dict(dict(form="fused", steps_per_launch=50), **opts)
+    assert np.array_equal(run_budgets(torch_dev, sw, False, **opts), run_budgets(torch_dev, sw, True, steps_per_launch=50))
+    rng = np.random.default_rng(2)
+    gains = I.f32(np.asarray(I.DEFAULT_GAINS)[:, None] * rng.uniform(0.8, 1.2, (9, sw.n)))
+    alive = (rng.random(sw.n) > 0.2).astype(np.uint8)
+    for kw in (dict(alive=alive), dict(gains=gains), dict(alive=alive, gains=gains, carry=False)):
+        got = run_budgets(torch_dev, sw, False, **kw, **opts)
+        assert np.array_equal(got, run_budgets(torch_dev, sw, True, **kw))
+        if "alive" in kw:
+            assert np.array_equal(got[:, alive == 0], sw.state[:, alive == 0])
+
+
+@pytest.mark.parametrize("budgets", [EIGHT, (200, 120, 60), (200, 200), tuple(range(12, 156, 12))])
+def test_one_lane_launches_of_several_budgets_match_oracle(oracle, torch_dev, budgets):
+    """Eight and three budget classes (grouped per block), one class and
+    twelve (not grouped: the plain groups of 64 of k_rollout), 20,011 agents
+    in the caller's order: bitwise the type order, and 2,000 sampled agents
+    within the tolerance of the reference."""
+    sw = budget_swarm(20011, budgets, len(budgets), 200)
+    got = run_budgets(torch_dev, sw, False)
+    assert np.array_equal(got, run_budgets(torch_dev, sw, True, steps_per_launch=30))
+    pick = np.sort(np.random.default_rng(3).choice(sw.n, 2000, replace=False))
+    sub = I.subset(sw, pick)
+    assert_parity(got[:, pick].astype(np.float64), oracle_rollout(oracle, sub, 200), sub)

@@ -328,3 +328,36 @@ def test_pipe_rejects_invalid_use(torch_dev):
     pipe.sync()
     pipe.close()
     sim.close()
+
+
+@pytest.mark.parametrize("ordered", [False, True])
+def test_pipe_snapshots_of_one_lane_launches_with_budgets(torch_dev, ordered):
+    """17,003 quadrotors (one lane per agent) of eight budgets, shuffled, with
+    dead agents: snapshots and final state of a pipe in the caller's order
+    (grouped per block) and in the type order are those of plain calls with
+    the positions copied after each interval, bit for bit."""
+    torch, dev = torch_dev
+    from paper_2308_12698_amd.sim import Pipe, Simulator
+    n, every, count = 17003, 40, 3
+    rng = np.random.default_rng(17)
+    types = [dict(t, budget=b) for t, b in zip(I.hetero_types(), (500, 120, 100, 81, 80, 41, 30, 1))]
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    start = I.hover_state(rng.uniform(0.0, 30.0, (3, n)))
+    wp = I.f32(start[0:3] + rng.uniform(-3.0, 3.0, (3, n)))
+    ti, alive = up(rng.integers(0, 8, n).astype(np.uint8)), up((rng.random(n) > 0.2).astype(np.uint8))
+    sim = Simulator(types, I.globals_f32(), mode=1)
+    perm = sim.order_by_type(ti) if ordered else None
+    ref, ca, want = up(start), torch.zeros((10, n), device=dev), []
+    for k in range(count):
+        sim.step(ref, every, 1e-3, type_idx=ti, wp=up(wp[None]), step0=k * every, alive=alive, carry=ca)
+        want.append(ref[0:3].clone())
+    pipe = Pipe(sim, n)
+    st, ct = up(start), torch.zeros((10, n), device=dev)
+    snaps = torch.empty((count, 3, n), dtype=torch.float32, pin_memory=True)
+    pipe.push(wp)
+    pipe.run(st, every * count, 1e-3, snap_every=every, snaps=snaps, type_idx=ti, perm=perm, alive=alive, carry=ct)
+    pipe.sync()
+    assert torch.equal(st, ref) and torch.equal(ct, ca)
+    assert torch.equal(snaps, torch.stack(want).cpu())
+    pipe.close()
+    sim.close()
