@@ -296,7 +296,9 @@ potato_status validate_step(const potato_ctx* ctx, const potato_state* st, const
  * spaced form of one type take 250: over more steps the waves of a SIMD
  * drift apart and their last ones run alone (1,000 steps in launches of
  * 1,000 / 500 / 250 / 100: 9.73 / 9.47 / 9.29 / 9.6 ms at 1,048,576 agents,
- * 6.79 / 6.52 / 6.41 ms at 700,000, 3.20 / 3.12 / 3.13 at 300,000); open loop
+ * 6.79 / 6.52 / 6.41 ms at 700,000, 3.20 / 3.12 / 3.13 at 300,000; at
+ * 1,048,576 on other machines 9.50 and 9.25, 9.69 and 9.53, 9.52 and 9.58 with
+ * 1,000 and 250); open loop
  * and several types gain nothing by it.  So do swarms of more than
  * kSpacedAgents with an alive mask: which SIMDs the live waves share is dealt
  * anew with every launch, and one deal of a mostly dead swarm may be a poor

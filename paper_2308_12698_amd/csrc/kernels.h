@@ -127,7 +127,11 @@ const void* rollout_kernel(const Variant& v, const StepArgs& a);
  * does in wider accesses: 4.20 us per launch against 4.86 at 10,000 agents,
  * 4.07 against 4.65 at 16,384; from two steps on four lanes are as fast.
  * With per-agent types four lanes are faster then too (4.5 against 10.5 us
- * at 1,000 agents: no grouping by class). */
+ * at 1,000 agents: no grouping by class).  Swarms that run at once on streams
+ * of their own share the SIMDs, which four lanes per agent fill sooner: 1,000
+ * steps of two swarms of 1,000 to 16,384 agents take 0.55 to 1.0 ms (1.0 to
+ * 1.4 with one lane), of four 1.0 to 1.9 (1.0 to 2.6), but of four of 5,000
+ * agents 1.9 against 1.46. */
 #ifndef POTATO_LANE_AGENTS
 #define POTATO_LANE_AGENTS 16384
 #endif
@@ -143,12 +147,13 @@ bool rollout_lanes(const Variant& v, const StepArgs& a);
  * 262,144, 4.52 -> 4.36 at 524,288, equal at 1M.  With an alive mask the host
  * does not know how many waves are live: quadrotors scattered over a swarm
  * would gain by it (10.3 -> 9.3 at 1M with a fifth dead), a quarter alive in
- * one piece loses (1.01 -> 1.16 at 140,000 and 262,144).  The others lose too, as
- * SIMDs come down to one or two waves before the launch ends: quadrotors of
- * several types (2.63 -> 2.85 ms per 1,000 steps of 251,904, their budgets
- * end apart), kinds of which many agents are dead (the quadrotors alone 1.45
- * -> 1.54 us per step at 262,144 in order, 2.1 -> 3.0 in the caller's), and
- * kinds in the caller's order gain nothing (2.95 either way). */
+ * one piece loses (1.01 -> 1.16 at 140,000 and 262,144).
+ * The others lose too: quadrotors of several types (2.63 -> 2.85 ms per 1,000
+ * steps of 251,904, nearly all of which run every step; the spaced loop reads
+ * its constants from LDS in every step, there by lane from entries of 176
+ * bytes), kinds of which many agents are dead (the quadrotors alone 1.45 ->
+ * 1.54 us per step at 262,144 in order, 2.1 -> 3.0 in the caller's), and kinds
+ * in the caller's order gain nothing (2.95 either way). */
 #ifndef POTATO_SPACED_AGENTS
 #define POTATO_SPACED_AGENTS 131072
 #endif

@@ -207,10 +207,14 @@ __device__ __forceinline__ float clampf_(float x, float lo, float hi) {
 }
 
 /* v_rsq_f32 and v_sqrt_f32.  SPACED: with an s_nop before and after, the
- * same instruction and bits.  A wave's transcendental instruction costs the
+ * same bits.  A wave's transcendental instruction costs the
  * other waves of its SIMD their turns for some 100 clocks: a stream with one
  * rsq in 64 instructions issues one per 3.8 clocks instead of one per 2.1,
- * and with the two s_nop one per 2.5.  The step has 8 of them in 520.  Worth
+ * and with the two s_nop one per 2.5.  The step has 8 of them in 520.  (The
+ * compiled loop differs in more: around these blocks the compiler reads some
+ * 25 of the step's constants from LDS in every step, in 10 reads, which the
+ * plain loop keeps in registers, and branches around the saturation's rsq:
+ * 570 instructions instead of 538.)  Worth
  * it from three waves per SIMD on (rollout_spaced); the waits of one or two
  * waves are not filled by others (0.94 -> 1.07 us per step at 65,536
  * agents). */
