@@ -116,15 +116,21 @@ struct Replay {
     uint32_t bits, off;                       /* kBit*, undo offsets */
 };
 
-/* Where the undo offsets are: six in a word of their own, three above the
- * branch decisions, and above those whether the tape holds the integrals
- * themselves in their place. */
-constexpr int kUndoWord = 6;
-constexpr int kUndoAt = 16;
+/* Where the undo offsets are: five of the attitude and rate integrals' in a
+ * word of their own, the sixth and the position's above the branch
+ * decisions, and above those whether the tape holds the integrals themselves
+ * in their place. */
+constexpr int kUndoWord = 5;
+constexpr int kUndoAt = 16, kUndoPosAt = kUndoAt + kUndoRate;
 constexpr uint32_t kWholeBit = 1u << 31;
-static_assert(kUndoWord * kUndoBits <= 32 && kUndoAt + (9 - kUndoWord) * kUndoBits <= 31, "the offsets' places");
-__device__ __forceinline__ uint32_t packed_offset(const Replay& a, int k) {
-    return (k < kUndoWord ? a.off >> (kUndoBits * k) : a.bits >> (kUndoAt + kUndoBits * (k - kUndoWord))) & kUndoMax;
+static_assert(kUndoWord * kUndoRate <= 32 && kUndoPosAt + 3 * kUndoPos <= 31, "the offsets' places");
+__device__ __forceinline__ uint32_t field(uint32_t word, int at, int bits) { return word >> at & ((1u << bits) - 1u); }
+/* of the position's integral i, of the attitude's (k = i) and the rate's (k = 3 + i) */
+__device__ __forceinline__ uint32_t pos_offset(const Replay& a, int i) {
+    return field(a.bits, kUndoPosAt + kUndoPos * i, kUndoPos);
+}
+__device__ __forceinline__ uint32_t rate_offset(const Replay& a, int k) {
+    return k < kUndoWord ? field(a.off, kUndoRate * k, kUndoRate) : field(a.bits, kUndoAt, kUndoRate);
 }
 
 /*
@@ -329,7 +335,7 @@ __device__ __forceinline__ void step_vjp(const TypeConst& c, const Limits& L, co
         /* rate loop, and w_prev <- w */
         gk[6] = POTATO_FMA(lal[i], erate, gk[6]);
         gk[7] = POTATO_FMA(lal[i], a.ir[i], gk[7]);
-        a.ir[i] = undo(a.ir[i], erate, L.dt, packed_offset(a, 6 + i));
+        a.ir[i] = undo<kUndoRate>(a.ir[i], erate, L.dt, rate_offset(a, 3 + i));
         gk[8] = POTATO_FMA(-lal[i], a.dw[i], gk[8]);
         const float l_dw = k.kdr_dt * lal[i];
         const float lw = (lam.w[i] + lam.wprev[i]) - l_dw;
@@ -339,7 +345,7 @@ __device__ __forceinline__ void step_vjp(const TypeConst& c, const Limits& L, co
         /* attitude loop, erate = wdes - w */
         gk[3] = POTATO_FMA(l_er, eatt[i], gk[3]);
         gk[4] = POTATO_FMA(l_er, a.ia[i], gk[4]);
-        a.ia[i] = undo(a.ia[i], eatt[i], L.dt, packed_offset(a, 3 + i));
+        a.ia[i] = undo<kUndoRate>(a.ia[i], eatt[i], L.dt, rate_offset(a, i));
         gk[5] = POTATO_FMA(-l_er, a.w[i], gk[5]);
         lam.w[i] = POTATO_FMA(-kda1, l_er, lw);
         lam.ia[i] = where(in_ia[i], POTATO_FMA(k.kia, l_er, lam.ia[i]));
@@ -377,7 +383,7 @@ __device__ __forceinline__ void step_vjp(const TypeConst& c, const Limits& L, co
     for (int i = 0; i < 3; ++i) {
         gk[0] = POTATO_FMA(la[i], e[i], gk[0]);
         gk[1] = POTATO_FMA(la[i], a.ip[i], gk[1]);
-        a.ip[i] = undo(a.ip[i], e[i], L.dt, packed_offset(a, i));
+        a.ip[i] = undo<kUndoPos>(a.ip[i], e[i], L.dt, pos_offset(a, i));
         gk[2] = POTATO_FMA(-la[i], a.v[i], gk[2]);
         lam.v[i] = POTATO_FMA(-k.kdp, la[i], lam.v[i]);
         lam.ip[i] = where(in_ip[i], POTATO_FMA(k.kip, la[i], lam.ip[i]));
@@ -480,7 +486,7 @@ __device__ __forceinline__ float tape_load(const float& x) {
  * the reverse sweep knows those after the step, and undo() gives those before
  * it from them with a few bits each, exactly the forward's, as if they were
  * on the tape (23 rows per step instead of 30; backward of 300,007 agents
- * 16.6 to 14.3-14.9 us per step, of 1,048,576 56 to 51-53).  Where an agent's
+ * 16.6 to 14.3-14.9 us per step, of 1,048,576 56 to 51-52.6).  Where an agent's
  * offsets do not fit or it is at a clamp, the wave writes the nine rows
  * themselves, the first in the place of the offsets' word. */
 constexpr uint32_t kBitInt = 7u << (kBitIp - 2) | 0x3fu << (kBitIr - 4);   /* inside all nine clamps */
@@ -493,8 +499,8 @@ __device__ __forceinline__ void store_tape(float* slot, uint32_t lb, const Agent
     auto row = [&](int k) -> float& { return elem(t.row(k), lb); };
     uint32_t wide = 0;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) wide |= b.off[k];
-    const bool whole = __ballot(wide > kUndoMax || (b.bits & kBitInt) != kBitInt) != 0;
+    for (int k = 0; k < 9; ++k) wide |= b.off[k] >> (k < 3 ? kUndoPos : kUndoRate);
+    const bool whole = __ballot(wide != 0 || (b.bits & kBitInt) != kBitInt) != 0;
     uint32_t bits = b.bits, word = 0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) { row(k) = a.p[k]; row(3 + k) = a.v[k]; row(10 + k) = a.w[k]; }
@@ -506,12 +512,10 @@ __device__ __forceinline__ void store_tape(float* slot, uint32_t lb, const Agent
         for (int k = 0; k < 9; ++k) row(kTapeInt + k) = before[k];
     } else {
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            if (k < kUndoWord)
-                word |= b.off[k] << (kUndoBits * k);
-            else
-                bits |= b.off[k] << (kUndoAt + kUndoBits * (k - kUndoWord));
-        }
+        for (int k = 0; k < 3; ++k) bits |= b.off[k] << (kUndoPosAt + kUndoPos * k);
+#pragma unroll
+        for (int k = 0; k < kUndoWord; ++k) word |= b.off[3 + k] << (kUndoRate * k);
+        bits |= b.off[3 + kUndoWord] << kUndoAt;
         row(kTapeInt) = __uint_as_float(word);
     }
     row(kTapeBits) = __uint_as_float(bits);

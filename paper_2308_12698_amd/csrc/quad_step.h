@@ -294,17 +294,20 @@ __device__ __forceinline__ void derivative(const TypeConst& c, const float v[3],
 
 /* An integral's update, undone from its value after it: less the increment,
  * which rounds once and so misses the value before by some units in the last
- * place.  undo_offset is that difference, of kUndoBits bits around kUndoZero;
+ * place.  undo_offset is that difference, of BITS bits around their middle;
  * with it undo returns the value before, bit for bit.  It does not fit where
- * the integral was small against its increment (less than a sixteenth or
- * so) or a clamp acted. */
-constexpr int kUndoBits = 5;
-constexpr uint32_t kUndoZero = 1u << (kUndoBits - 1), kUndoMax = (1u << kUndoBits) - 1;
+ * the integral was small against its increment (less than a thirtieth or so
+ * with the attitude and rate integrals' 6 bits) or a clamp acted.  The
+ * position's integrals, whose carries add a unit either way, seldom pass
+ * through zero and take 3. */
+constexpr int kUndoPos = 3, kUndoRate = 6;
+template <int BITS>
 __device__ __forceinline__ uint32_t undo_offset(float before, float after, float e, float dt) {
-    return __float_as_uint(before) - __float_as_uint(POTATO_FMA(-e, dt, after)) + kUndoZero;
+    return __float_as_uint(before) - __float_as_uint(POTATO_FMA(-e, dt, after)) + (1u << (BITS - 1));
 }
+template <int BITS>
 __device__ __forceinline__ float undo(float after, float e, float dt, uint32_t offset) {
-    return __uint_as_float(__float_as_uint(POTATO_FMA(-e, dt, after)) + offset - kUndoZero);
+    return __uint_as_float(__float_as_uint(POTATO_FMA(-e, dt, after)) + offset - (1u << (BITS - 1)));
 }
 
 /* What a step leaves for its reverse: the branch decisions, and undo_offset
@@ -343,7 +346,7 @@ __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, 
             a.ip_lo[i] = cl == s ? lo : 0.0f;
         }
         if (BITS) push_bit(b, cl == s);
-        if (BITS) back->off[i] = undo_offset(a.ip[i], cl, e[i], L.dt);
+        if (BITS) back->off[i] = undo_offset<kUndoPos>(a.ip[i], cl, e[i], L.dt);
         a.ip[i] = cl;
         acc[i] = POTATO_FMA(-k.kdp, a.v[i], POTATO_FMA(k.kip, cl, k.kpp * e[i]));
     }
@@ -378,7 +381,7 @@ __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, 
         const float pa = POTATO_FMA(eatt[i], L.dt, a.ia[i]);
         const float ca = clampf_(pa, -L.iatt_max, L.iatt_max);
         if (BITS) push_bit(b, ca == pa);
-        if (BITS) back->off[3 + i] = undo_offset(a.ia[i], ca, eatt[i], L.dt);
+        if (BITS) back->off[3 + i] = undo_offset<kUndoRate>(a.ia[i], ca, eatt[i], L.dt);
         a.ia[i] = ca;
         const float wdes = POTATO_FMA(-k.kda, a.w[i], POTATO_FMA(k.kia, a.ia[i], k.kpa * eatt[i]));
         /* body-rate loop, derivative on the measured rate */
@@ -386,7 +389,7 @@ __device__ __forceinline__ void controller(const TypeConst& c, const Limits& L, 
         const float pr = POTATO_FMA(erate, L.dt, a.ir[i]);
         const float cr = clampf_(pr, -L.irate_max, L.irate_max);
         if (BITS) push_bit(b, cr == pr);
-        if (BITS) back->off[6 + i] = undo_offset(a.ir[i], cr, erate, L.dt);
+        if (BITS) back->off[6 + i] = undo_offset<kUndoRate>(a.ir[i], cr, erate, L.dt);
         a.ir[i] = cr;
         alpha[i] = POTATO_FMA(-k.kdr_dt, a.w[i] - a.wprev[i], POTATO_FMA(k.kir, a.ir[i], k.kpr * erate));
         a.wprev[i] = a.w[i];
